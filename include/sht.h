@@ -97,13 +97,17 @@ enum {
 typedef struct sht_plan_opts {
     double cutoff;     /* Legendre values below this magnitude at the start of
                           each l-chain are skipped (App. A.2: 1e-30). */
-    double dd_sin;     /* rings with sin(theta) below this threshold run the
-                          recurrence in compensated double-double arithmetic;
-                          < 0 selects the default 0.1 * L / 4095.  FP64
-                          recurrences lose ~L eps / sin(theta) near the poles. */
+    double dd_sin;     /* rings with sin(theta) below this threshold run a
+                          recurrence that is stable near the poles, where the
+                          plain FP64 one loses ~L eps / sin(theta).  < 0 selects
+                          the default 0.1 * L / 4095 and, in synthesis, the
+                          recurrence split about its solution at the pole
+                          (relative error ~1e-14); a value >= 0 runs them in
+                          compensated double-double arithmetic. */
     int nthreads;      /* host threads for plan construction; 0 = all cores */
     int rings_per_lane;/* rings each lane of the FP64 Legendre kernel owns:
-                          1, 2 or 4 (0 = default 2); a tuning knob */
+                          1, 2 or 4 (0 = chosen by the transform's size); a
+                          tuning knob */
     int ring_threads;  /* workgroup size of the ring FFT kernel: 256, 512 or
                           1024 (0 = default 512); a tuning knob */
     int host_only;     /* 1: build host tables only (no device memory); such a
@@ -168,7 +172,8 @@ typedef struct sht_plan_info {
                                  starts rounded down to a chunk boundary) */
     long long n_step_dd;      /* executed steps in compensated ring blocks */
     long long n_step_lanes;   /* lane-steps the Legendre kernel issues (idle
-                                 lanes of partially active waves included) */
+                                 lanes of partially active waves included) at
+                                 rings_per_lane rings a lane (0: at 2) */
     size_t device_bytes;      /* device memory held by the plan */
     double build_seconds;     /* wall time of sht_plan */
     /* butterfly (zero unless eps > 0) */

@@ -26,6 +26,7 @@
 #include <cstring>
 
 #include "butterfly_common.h"
+#include "dpp.h"
 
 namespace sht {
 
@@ -137,50 +138,6 @@ __device__ __forceinline__ void id_block(const BfArgs<S> &a, int node, int ch, i
             default: break;
         }
     }
-}
-
-// acc[c] += x_c * p for c < N, where x_c is the value that lane c of the
-// lane's 16-lane row holds in rv: each FP64 FMA reads rv through the DPP
-// broadcast (row_newbcast), so the per-row operands need neither one LDS
-// broadcast read per value nor a register each.  One asm block per call:
-// its leading s_nop gives the two wait states that a DPP read needs after a
-// vector-ALU write of rv, and nothing can be scheduled inside it.
-#define SHT_FMAC_BC(c, o) "v_fmac_f64_dpp %" #o ", %[rv], %[p] row_newbcast:" #c " row_mask:0xf bank_mask:0xf\n"
-template <int N>
-__device__ __forceinline__ void fmac_row_bcast(double *acc, double rv, double p);
-template <>
-__device__ __forceinline__ void fmac_row_bcast<2>(double *acc, double rv, double p) {
-    asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) : "+v"(acc[0]), "+v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
-}
-template <>
-__device__ __forceinline__ void fmac_row_bcast<4>(double *acc, double rv, double p) {
-    asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3)
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
-        : [rv] "v"(rv), [p] "v"(p));
-}
-template <>
-__device__ __forceinline__ void fmac_row_bcast<8>(double *acc, double rv, double p) {
-    asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3) SHT_FMAC_BC(4, 4)
-            SHT_FMAC_BC(5, 5) SHT_FMAC_BC(6, 6) SHT_FMAC_BC(7, 7)
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-          "+v"(acc[7])
-        : [rv] "v"(rv), [p] "v"(p));
-}
-template <>
-__device__ __forceinline__ void fmac_row_bcast<16>(double *acc, double rv, double p) {
-    fmac_row_bcast<8>(acc, rv, p);
-    asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3) SHT_FMAC_BC(12, 4)
-            SHT_FMAC_BC(13, 5) SHT_FMAC_BC(14, 6) SHT_FMAC_BC(15, 7)
-        : "+v"(acc[8]), "+v"(acc[9]), "+v"(acc[10]), "+v"(acc[11]), "+v"(acc[12]), "+v"(acc[13]), "+v"(acc[14]),
-          "+v"(acc[15])
-        : [rv] "v"(rv), [p] "v"(p));
-}
-#undef SHT_FMAC_BC
-
-// The value of lane K of each 16-lane row, in every lane of that row.
-template <int K>
-__device__ __forceinline__ double row_bcast(double x) {
-    return __builtin_amdgcn_mov_dpp(x, 0x150 + K, 0xF, 0xF, false);
 }
 
 // One residual piece on one wave: R rings per lane (lane j: rings j + 64 r,

@@ -1,0 +1,65 @@
+// FP64 multiply-adds whose one operand is broadcast within each 16-lane row
+// by DPP (gfx950 row_newbcast), and the plain broadcast of such a value.
+#pragma once
+#include <hip/hip_runtime.h>
+
+namespace sht {
+
+// acc[c] += x_c * p for c < N (N even), where x_c is the value that lane
+// C0 + c of the lane's 16-lane row holds in rv: each FP64 FMA reads rv
+// through the DPP broadcast (row_newbcast), so the per-row operands need
+// neither one LDS broadcast read per value nor a register each.  In each asm
+// block the leading s_nop gives the two wait states that a DPP read needs
+// after a vector-ALU write of rv, and nothing can be scheduled inside it.
+#define SHT_FMAC_BC(c, o) "v_fmac_f64_dpp %" #o ", %[rv], %[p] row_newbcast:" #c " row_mask:0xf bank_mask:0xf\n"
+template <int N, int C0 = 0>
+__device__ __forceinline__ void fmac_row_bcast(double *acc, double rv, double p) {
+    static_assert(N % 2 == 0 && C0 % 2 == 0 && C0 + N <= 16, "lanes of one row, in pairs");
+    if constexpr (N > 8) {
+        fmac_row_bcast<8, C0>(acc, rv, p);
+        fmac_row_bcast<N - 8, C0 + 8>(acc + 8, rv, p);
+    } else if constexpr (C0 == 8) {
+        if constexpr (N == 2)
+            asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) : "+v"(acc[0]), "+v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
+        else if constexpr (N == 4)
+            asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3)
+                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+                : [rv] "v"(rv), [p] "v"(p));
+        else if constexpr (N == 8)
+            asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3) SHT_FMAC_BC(12, 4)
+                    SHT_FMAC_BC(13, 5) SHT_FMAC_BC(14, 6) SHT_FMAC_BC(15, 7)
+                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
+                  "+v"(acc[7])
+                : [rv] "v"(rv), [p] "v"(p));
+        else
+            static_assert(N == 2, "unsupported lane count");
+    } else {
+        static_assert(C0 == 0, "rows are read from lane 0 or 8");
+        if constexpr (N == 2)
+            asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) : "+v"(acc[0]), "+v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
+        else if constexpr (N == 4)
+            asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3)
+                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+                : [rv] "v"(rv), [p] "v"(p));
+        else if constexpr (N == 6)
+            asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3) SHT_FMAC_BC(4, 4)
+                    SHT_FMAC_BC(5, 5)
+                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5])
+                : [rv] "v"(rv), [p] "v"(p));
+        else
+            asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3) SHT_FMAC_BC(4, 4)
+                    SHT_FMAC_BC(5, 5) SHT_FMAC_BC(6, 6) SHT_FMAC_BC(7, 7)
+                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
+                  "+v"(acc[7])
+                : [rv] "v"(rv), [p] "v"(p));
+    }
+}
+#undef SHT_FMAC_BC
+
+// The value of lane K of each 16-lane row, in every lane of that row.
+template <int K>
+__device__ __forceinline__ double row_bcast(double x) {
+    return __builtin_amdgcn_mov_dpp(x, 0x150 + K, 0xF, 0xF, false);
+}
+
+}  // namespace sht

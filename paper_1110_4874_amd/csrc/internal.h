@@ -168,6 +168,12 @@ struct sht_plan_s {
 
     // ---- device copies ------------------------------------------------
     double *d_z2_hi = nullptr, *d_z2_lo = nullptr;
+    // split recurrence near the poles: groups [0, pole_groups) of 64 rings
+    // (0: those rings run in double-double), sin^2 of the north rings,
+    // coefficients and start differences
+    int pole_groups = 0;
+    double *d_coef_sc = nullptr;  // scaled recurrence
+    double *d_s2 = nullptr, *d_coef_pole = nullptr, *d_start_d = nullptr;
     int *d_ring_J = nullptr, *d_ring_s = nullptr, *d_ring_M = nullptr;
     long long *d_ring_off = nullptr, *d_ring_bs_off = nullptr, *d_coef_off = nullptr;
     double *d_coef_hi = nullptr, *d_coef_lo = nullptr;
@@ -206,25 +212,31 @@ namespace sht {
 // once per device (noalloc.hip).
 int noalloc_scratch(int dev, void **out);
 
-// Argument block of the brute-force Legendre waves (legendre.hip): one
-// plan, one pass of up to 4 maps.
+// Argument block of the brute-force Legendre workgroups (legendre.hip): one
+// plan, one pass of up to 8 maps.
 struct LegArgs {
     const double *__restrict__ z2_hi;
     const double *__restrict__ z2_lo;
+    const double *__restrict__ s2;  // sin^2(theta)
     const long long *__restrict__ coef_off;
     const double *__restrict__ coef_hi;
     const double *__restrict__ coef_lo;
+    const double *__restrict__ coef_sc;    // scaled recurrence: {b, -b d, f, 1/f}
+    const double *__restrict__ coef_pole;  // split recurrence: {h, -beta, r, 0}
     const int *__restrict__ start_idx;
     const double *__restrict__ start_val;
     const double *__restrict__ start_lo;
+    const double *__restrict__ start_d;    // split recurrence: d at the chain start
     const int *__restrict__ grp_lo;
     const int *__restrict__ grp_hi;
     const double *__restrict__ alm;
     double *__restrict__ q;
-    int L, nrings, n_north, np, n_dd_pad, ng;
-    int nmaps, map0;  // map stride of alm/q and first map of this pass
-    int dd_groups;    // 64-ring groups run in double-double (from the pole)
-    int fp_blocks;    // FP64 ring blocks of R groups after them
+    int L, nrings, n_north, np, n_dd_pad, n_pole_pad, ng;
+    int nmaps, map0;   // map stride of alm/q and first map of this pass
+    int pole_groups;   // 64-ring groups run by the split recurrence (from the pole)
+    int dd_groups;     // or, in double-double
+    int first_plain;   // the groups after them run the plain recurrence
+    int pole_blocks, plain_blocks;  // blocks of R groups of each
 };
 
 // Argument block of the ring FFT workgroups (ring.hip): one plan, one ring
@@ -315,20 +327,28 @@ hipError_t launch_butterfly_adjoint(const sht_plan_s *p, int nmaps, const double
 // and one ring-queue launch per ring size class (items {argument block,
 // item of that class}).  The Legendre items come in one list per XCD.
 LegArgs leg_args(const sht_plan_s *p, int nmaps, int map0, int R, const double *alm, double *q);
-// Work-queue batches on the brute-force path: one persistent launch per wave
-// shape (0, 1: compensated waves of 2 or 1 maps; 2, 3, 4: FP64 waves of 4,
-// 2 or 1 maps).
-constexpr int kQueueShapes = 5;
+int leg_pass_maps(int left);  // maps of the next pass with `left` maps to go
+// Device table of the scaled recurrence (d_coef_sc).
+hipError_t fill_scaled_coef(const sht_plan_s *p);
+// Device tables of the split recurrence (d_coef_pole, d_start_d) from the
+// uploaded ones.
+hipError_t fill_pole_tables(const sht_plan_s *p);
+// Work-queue batches on the brute-force path: one persistent launch per pass
+// shape (0, 1: double-double waves of 2 or 1 maps; 2: workgroups of 8 maps;
+// 3 .. 8: of 6 .. 1 maps).
+constexpr int kQueueShapes = 9;
 // Internal streams for fork/join inside one call (batch.cpp).
 constexpr int kMaxStreams = 8;
 int pool_streams(int dev, hipStream_t *out);
 int queue_shape(bool dd, int nb);
+int queue_rings(int nb, int R);  // rings per lane of a pass of nb maps
+int queue_threads(int shape);    // threads of a workgroup of the shape's launch
 hipError_t legendre_queue_grid(int shape, int rings_per_lane, int *grid);
 // items {pass, m, ring block, first map}: per shape eight lists back to back,
 // cut into chunks; chunk c covers items [chunk_off[c], chunk_off[c+1]) and
 // list x of shape v the chunks [list_off[9v+x], list_off[9v+x+1]); counter:
-// 5 x 8 x 16 unsigned of device memory, cleared by launch_queue_reset before
-// the shapes' launches; grid: waves of the shape's launch (0: no items).
+// 9 x 8 x 16 unsigned of device memory, cleared by launch_queue_reset before
+// the shapes' launches; grid: workgroups of the shape's launch (0: no items).
 hipError_t launch_queue_reset(unsigned *counter, hipStream_t st);
 hipError_t launch_legendre_queue(int shape, const LegArgs *passes, const int4 *items, const unsigned *chunk_off,
                                  const unsigned *list_off, unsigned *counter, int rings_per_lane, int grid,

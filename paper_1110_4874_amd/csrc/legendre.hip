@@ -4,273 +4,369 @@
 //   q_m(+-z_k) = q^even_m(z_k) +- q^odd_m(z_k),
 //   q^t_m(z)   = sum_i P~_{m+t+2i}^m(z) a_{m+t+2i, m}
 //
-// One wavefront handles one order m and a block of 64 x R north rings;
-// every lane owns R rings (R = 1, 2 or 4, a plan parameter) and runs both
-// parity chains of the two-step recurrence for them.  The recurrence coefficients
-// and the a_lm of the current l are the same for every lane, so they are
-// read as wave-uniform (scalar) loads and used straight from SGPRs; P~ never
-// leaves VGPRs (the GPU form of the paper's register-resident SSE kernel).
-// The even/odd fold of Eqs. 13-14 is fused into the store: each lane writes
-// ring k and its mirror 4N-2-k.
+// One workgroup of two wavefronts handles one order m and a block of 64 x R
+// north rings; wave t runs the two-step recurrence of parity t with R rings
+// per lane, so the even and the odd chain advance side by side.  The
+// recurrence coefficients and the a_lm of a chain step are the same for every
+// lane: the wave fetches them a chunk of kChunk steps ahead with coalesced
+// loads, stages them as rows of 16 (32) doubles in its own LDS slot, and the
+// FP64 multiply-adds read them from one register per row through DPP row
+// broadcasts.  P~ never leaves VGPRs (the GPU form of the paper's
+// register-resident SSE kernel).  The even/odd fold of Eqs. 13-14 is fused
+// into the store: the waves swap their sums through LDS and write ring k and
+// its mirror 4N-2-k.
 //
 // Chains start at the plan's precomputed values (first l above the cutoff,
 // rounded down to a multiple of kChunk chain steps), so a lane joins the
-// wave-uniform l loop only at chunk boundaries.  Ring blocks nearest the
-// poles, where a z-based FP64 recurrence loses ~l eps / sin(theta), run the
-// same recurrence in double-double arithmetic.
+// wave-uniform loop only at chunk boundaries.
+//
+// The two-step recurrence runs in the scaling P~_l = f_l mu_l with f_{l+2} f_l
+// = 1 / c_l, which makes its last coefficient -1:
+//   mu_{l+2} = b_l (z^2 - d_l) mu_l - mu_{l-2},  b_l = f_l^2
+// (c_l, d_l of App. A.2; f stays within the square root of the range of c).
+// Two FP64 operations a step instead of three; the f_l go into the staged
+// a_lm.
+//
+// Near the poles a z-based FP64 recurrence loses ~l eps / sin(theta): z^2
+// carries sin^2(theta) with an absolute error of eps.  The ring groups there
+// run the recurrence split about its solution at the pole (the idea of
+// Reinsch's modification of Clenshaw's recurrence): with r_l the ratio
+// P~_{l+2}/P~_l at theta -> 0, P~_{l+2} = (r_l + h_l - sin^2 beta_l) P~_l -
+// h_l r_{l-2} P~_{l-2} exactly, so
+//   P~_{l+2} = r_l P~_l + d_l,   d_{l+2} = h_{l+2} d_l - sin^2 beta_{l+2} P~_{l+2}
+// where sin^2(theta) enters with its own relative accuracy.  Four FP64
+// operations a step instead of three; relative errors of 2e-15 to 2e-14 at
+// L = 4095 for sin(theta) <= 0.1 (double-double arithmetic, which these rings
+// ran before at about 45 operations a step and chain, made one wave's serial
+// chain the length of the whole launch below L ~ 2000).
 #include "ddmath.h"
+#include "dpp.h"
 #include "internal.h"
 
 namespace sht {
 
+// Staged row of a chain step: a_lm of NB maps (2 NB values), then the two
+// (split recurrence: three) coefficients, in rows of 16 doubles, or of 32
+// where they do not fit.
+template <int NB, bool POLE>
+constexpr int leg_row() {
+    return 2 * NB + (POLE ? 3 : 2) <= 16 ? 16 : 32;
+}
+// LDS doubles of one wave: two staged chunks, and the chains' start values
+// (R rings) whose room holds one ring group's sums at the fold.
+template <int NB, int R>
+constexpr int leg_wave_lds() {
+    return 2 * kChunk * leg_row<NB, true>() + (R * 128 > 128 * NB ? R * 128 : 128 * NB);
+}
 
-
-// One wave: order m, rings of the 64-ring groups g0 .. g0+R-1 (R per lane).
-// Groups at or past a.ng do not exist (partial last block) and are skipped.
-template <int NB, int R, bool DD>
-__device__ __forceinline__ void legendre_wave(const LegArgs &a, const int m, const int g0) {
-    const int lane = threadIdx.x;
+// One workgroup: order m, rings of the 64-ring groups g0 .. min(g0 + R, gend) - 1
+// (R per lane); wave t = threadIdx.x / 64 runs parity t.  POLE: the split
+// recurrence of the file's head, else the scaled two-step recurrence.
+template <int NB, int R, bool POLE>
+__device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const int g0, const int gend, double *lds) {
+    constexpr int NC = 2 * NB;
+    constexpr int CW = leg_row<NB, POLE>(), CS = kChunk * CW, E = CS / 64;
+    constexpr int CO = NC % 16;           // lane of the first coefficient within its 16-lane row
+    static_assert(NC + (POLE ? 3 : 2) <= 16 || NC == 16, "the coefficients share one 16-lane row");
+    constexpr int KU = 4;                 // rows read from LDS at once
+    const int t = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int L = a.L;
+    const int n = L - m - t >= 0 ? (L - m - t) / 2 + 1 : 0;  // chain length
+    double *room = lds + t * leg_wave_lds<NB, R>();
+    double *stg = room + (leg_wave_lds<NB, R>() - 2 * CS);
+    const double4 *cf = reinterpret_cast<const double4 *>(POLE ? a.coef_pole : a.coef_sc) + a.coef_off[m] + t;
 
-    int k[R];
-    bool gv[R];
+    int sid[R], lo = kDead, hi = -1;
+    double x[R], P0[R], P1[R], acc[R][NC];
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        gv[r] = g0 + r < a.ng;
-        k[r] = (g0 + r) * kLanes + lane;
-    }
-
-    // wave-uniform chain range of this block
-    int lo = kDead, hi = -1;
-#pragma unroll
-    for (int r = 0; r < R; r++) {
-        if (!gv[r]) continue;
-        lo = min(lo, a.grp_lo[(size_t)m * a.ng + g0 + r]);
-        hi = max(hi, a.grp_hi[(size_t)m * a.ng + g0 + r]);
-    }
-    const int n0 = (L - m) / 2 + 1;                    // even chain length
-    const int n1 = (L - m >= 1) ? (L - m - 1) / 2 + 1 : 0;  // odd chain length
-
-    double accE_r[R][NB], accE_i[R][NB], accO_r[R][NB], accO_i[R][NB];
-#pragma unroll
-    for (int r = 0; r < R; r++)
-#pragma unroll
-        for (int b = 0; b < NB; b++) accE_r[r][b] = accE_i[r][b] = accO_r[r][b] = accO_i[r][b] = 0.0;
-
-    if (lo < n0) {
-        double z2h[R], z2l[R];
-        int sid[R][2];
-        dd p0[R][2], p1[R][2];
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-            const int kk = gv[r] ? k[r] : 0;
-            z2h[r] = a.z2_hi[kk];
-            z2l[r] = DD ? a.z2_lo[kk] : 0.0;
-#pragma unroll
-            for (int t = 0; t < 2; t++) {
-                size_t row = (size_t)(2 * m + t);
-                sid[r][t] = gv[r] ? a.start_idx[row * a.np + kk] : kDead;
-                p0[r][t] = {0.0, 0.0};
-                p1[r][t] = {0.0, 0.0};
-            }
+        const bool ok = g0 + r < gend;
+        const int g = ok ? g0 + r : g0, k = g * kLanes + lane;
+        const size_t row = (size_t)(2 * m + t);
+        sid[r] = ok ? a.start_idx[row * a.np + k] : kDead;
+        x[r] = POLE ? a.s2[k] : a.z2_hi[k];
+        // start values wait in LDS until their chain joins
+        double v0 = a.start_val[row * 2 * a.np + k];
+        double v1 = POLE ? a.start_d[row * a.n_pole_pad + k] : a.start_val[(row * 2 + 1) * a.np + k];
+        if (!POLE) {
+            const int i = sid[r] == kDead ? 0 : sid[r];
+            v0 *= cf[2 * i].w;
+            v1 *= cf[2 * i + 2].w;
         }
-        const long long cbase = a.coef_off[m];
-        const double *__restrict__ ch = a.coef_hi + 4 * cbase;
-        const double *__restrict__ cl = a.coef_lo + 4 * cbase;
-        const size_t aoff = (size_t)m * (2 * L + 3 - m) / 2;
-        const double *__restrict__ al = a.alm + 2 * (aoff * a.nmaps + a.map0);
-        const int astride = 2 * a.nmaps;  // doubles between consecutive l
+        *reinterpret_cast<double2 *>(room + 2 * (r * 64 + lane)) = make_double2(v0, v1);
+        if (ok) {
+            lo = min(lo, a.grp_lo[(size_t)m * a.ng + g]);
+            hi = max(hi, a.grp_hi[(size_t)m * a.ng + g]);
+        }
+        P0[r] = P1[r] = 0.0;
+#pragma unroll
+        for (int c = 0; c < NC; c++) acc[r][c] = 0.0;
+    }
 
-        auto inject = [&](int c) {
+    if (lo < n) {
+        // this lane's staged values: rows lane / CW (+ 64 / CW per e) of a
+        // chunk, component lane % CW, of rows clamped to the last.  The loads are unconditional (a
+        // select on them would become a branch that waits for memory); rows
+        // past the last are overwritten with zeros in LDS.
+        const int comp = lane % CW;
+        const bool is_a = comp < NC;
+        const double *base;
+        unsigned stride;
+        if (is_a) {
+            base = a.alm + 2 * (((size_t)m * (2 * L + 3 - m) / 2 + t) * a.nmaps + a.map0) + comp;
+            stride = 4u * (unsigned)a.nmaps;
+        } else {
+            base = reinterpret_cast<const double *>(cf + 2) + min(comp - NC, POLE ? 2 : 1);
+            stride = 8u;
+        }
+        const double f1 = is_a ? 1.0 : 0.0, f0 = 1.0 - f1;  // factor of a staged value: f_l, or 1 for a coefficient
+        const double *fb = reinterpret_cast<const double *>(cf) + 2;
+        double pre[E], fac[E];
+        auto fetch = [&](int c) {  // rows c .. c + kChunk - 1
 #pragma unroll
-            for (int r = 0; r < R; r++)
-#pragma unroll
-                for (int t = 0; t < 2; t++)
-                    if (sid[r][t] == c) {
-                        // start values are read when the chain joins (once per
-                        // chain), not kept in registers for the whole wave
-                        const size_t row = (size_t)(2 * m + t);
-                        const int kk = k[r];
-                        p0[r][t].h = a.start_val[(row * 2 + 0) * a.np + kk];
-                        p1[r][t].h = a.start_val[(row * 2 + 1) * a.np + kk];
-                        p0[r][t].l = DD ? a.start_lo[(row * 2 + 0) * a.n_dd_pad + kk] : 0.0;
-                        p1[r][t].l = DD ? a.start_lo[(row * 2 + 1) * a.n_dd_pad + kk] : 0.0;
-                    }
-        };
-
-        // operands of chain step i (the same for every lane: scalar loads)
-        struct Ops {
-            double be, abe, ge, bo, abo, go;
-            double er[NB], ei[NB], orr[NB], oi[NB];
-        };
-        auto load_ops = [&](int i, bool odd_ok) {
-            Ops o;
-            // entries l = m + 2i + 2 (even chain) and the next one (odd chain)
-            const double4 *ce = reinterpret_cast<const double4 *>(ch) + (2 * i + 2);
-            const double4 e4 = ce[0], o4 = ce[1];
-            o.be = e4.x;
-            o.abe = e4.y;
-            o.ge = e4.z;
-            o.bo = o4.x;
-            o.abo = o4.y;
-            o.go = o4.z;
-            const double *ape = al + (size_t)(2 * i) * astride;
-#pragma unroll
-            for (int b = 0; b < NB; b++) {
-                o.er[b] = ape[2 * b];
-                o.ei[b] = ape[2 * b + 1];
-                o.orr[b] = odd_ok ? ape[astride + 2 * b] : 0.0;
-                o.oi[b] = odd_ok ? ape[astride + 2 * b + 1] : 0.0;
+            for (int e = 0; e < E; e++) {
+                const unsigned i = (unsigned)min(c + (lane + 64 * e) / CW, n - 1);
+                pre[e] = base[(size_t)i * stride];
+                if (!POLE) fac[e] = fb[8 * i];
             }
-            return o;
         };
-
-        // one chain step i for both parities: accumulate P(i) a_l, advance
-        auto compute = [&](const Ops &o, int i) {
-            if constexpr (!DD) {
-                (void)i;
+        auto stage = [&](int sl, int c) {  // rows c .. c + kChunk - 1
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const double pe = p0[r][0].h, po = p0[r][1].h;
+            for (int e = 0; e < E; e++)
+                stg[sl * CS + lane + 64 * e] = POLE ? pre[e] : pre[e] * __builtin_fma(fac[e], f1, f0);
+            if (c + kChunk > n) {
 #pragma unroll
-                    for (int b = 0; b < NB; b++) {
-                        accE_r[r][b] = __builtin_fma(pe, o.er[b], accE_r[r][b]);
-                        accE_i[r][b] = __builtin_fma(pe, o.ei[b], accE_i[r][b]);
-                        accO_r[r][b] = __builtin_fma(po, o.orr[b], accO_r[r][b]);
-                        accO_i[r][b] = __builtin_fma(po, o.oi[b], accO_i[r][b]);
-                    }
-                    const double Ae = __builtin_fma(z2h[r], o.be, o.abe);
-                    const double Ao = __builtin_fma(z2h[r], o.bo, o.abo);
-                    const double ne = __builtin_fma(Ae, p1[r][0].h, o.ge * pe);
-                    const double no = __builtin_fma(Ao, p1[r][1].h, o.go * po);
-                    p0[r][0].h = p1[r][0].h;
-                    p1[r][0].h = ne;
-                    p0[r][1].h = p1[r][1].h;
-                    p1[r][1].h = no;
-                }
-            } else {
-                const double *cle = cl + 4 * (2 * i + 2);
-                const dd Be = {o.be, cle[0]}, ABe = {o.abe, cle[1]}, Ge = {o.ge, cle[2]};
-                const dd Bo = {o.bo, cle[4]}, ABo = {o.abo, cle[5]}, Go = {o.go, cle[6]};
+                for (int e = 0; e < E; e++)
+                    if (c + (lane + 64 * e) / CW >= n) stg[sl * CS + lane + 64 * e] = 0.0;
+            }
+        };
+        auto step = [&](double rv, double rc) {
+            const double c0 = row_bcast<CO>(rc), c1 = row_bcast<CO + 1>(rc);
+            const double c2 = POLE ? row_bcast<(CO + 2) % 16>(rc) : 0.0;
 #pragma unroll
-                for (int r = 0; r < R; r++) {
-                    const double pe = p0[r][0].h, po = p0[r][1].h;
-#pragma unroll
-                    for (int b = 0; b < NB; b++) {
-                        accE_r[r][b] = __builtin_fma(pe, o.er[b], accE_r[r][b]);
-                        accE_i[r][b] = __builtin_fma(pe, o.ei[b], accE_i[r][b]);
-                        accO_r[r][b] = __builtin_fma(po, o.orr[b], accO_r[r][b]);
-                        accO_i[r][b] = __builtin_fma(po, o.oi[b], accO_i[r][b]);
-                    }
-                    const dd z2 = {z2h[r], z2l[r]};
-                    const dd Ae = dd_add(dd_mul(z2, Be), ABe);
-                    const dd Ao = dd_add(dd_mul(z2, Bo), ABo);
-                    const dd ne = dd_add(dd_mul(Ae, p1[r][0]), dd_mul(Ge, p0[r][0]));
-                    const dd no = dd_add(dd_mul(Ao, p1[r][1]), dd_mul(Go, p0[r][1]));
-                    p0[r][0] = p1[r][0];
-                    p1[r][0] = ne;
-                    p0[r][1] = p1[r][1];
-                    p1[r][1] = no;
+            for (int r = 0; r < R; r++) {
+                fmac_row_bcast<NC>(acc[r], rv, P0[r]);
+                if constexpr (POLE) {  // c0 = h, c1 = -beta (both of the next l), c2 = r
+                    const double nx = __builtin_fma(c2, P0[r], P1[r]);
+                    P1[r] = __builtin_fma(c0, P1[r], (c1 * x[r]) * nx);
+                    P0[r] = nx;
+                } else {
+                    const double nx = __builtin_fma(__builtin_fma(x[r], c0, c1), P1[r], -P0[r]);
+                    P0[r] = P1[r];
+                    P1[r] = nx;
                 }
             }
         };
-
-        // chunks where both chains are inside l <= L
-        const int c_full = (n1 / kChunk) * kChunk;
-        int c = lo;
-        for (; c < c_full; c += kChunk) {
-            if (c <= hi) inject(c);
+        fetch(lo);
+        stage(0, lo);
+        fetch(lo + kChunk);
+        int sl = 0;
+        for (int c = lo; c < n; c += kChunk, sl ^= 1) {
+            if (c <= hi) {
 #pragma unroll
-            for (int u = 0; u < kChunk; u++) compute(load_ops(c + u, true), c + u);
-        }
-        // tail: the odd chain may end first
-        for (; c < n0; c += kChunk) {
-            if (c <= hi) inject(c);
-            for (int u = 0; u < kChunk; u++) {
-                int i = c + u;
-                if (i >= n0) break;
-                compute(load_ops(i, i < n1), i);
+                for (int r = 0; r < R; r++)
+                    if (sid[r] == c) {
+                        const double2 s = *reinterpret_cast<const double2 *>(room + 2 * (r * 64 + lane));
+                        P0[r] = s.x;
+                        P1[r] = s.y;
+                    }
             }
+            const double *cur = stg + sl * CS + (lane & 15);
+#pragma unroll
+            for (int u0 = 0; u0 < kChunk; u0 += KU) {
+                double rv[KU], rc[KU];
+#pragma unroll
+                for (int u = 0; u < KU; u++) {
+                    rv[u] = cur[(u0 + u) * CW];
+                    rc[u] = CW == 16 ? rv[u] : cur[(u0 + u) * CW + 16];
+                }
+#pragma unroll
+                for (int u = 0; u < KU; u++) step(rv[u], rc[u]);
+            }
+            stage(sl ^ 1, c + kChunk);
+            fetch(c + 2 * kChunk);
         }
     }
 
-    // fused even/odd fold and store (Eqs. 13-14)
+    // fused even/odd fold and store (Eqs. 13-14), one ring group at a time:
+    // wave 0 stores the north rings, wave 1 their mirrors
+    const double *other = lds + (1 - t) * leg_wave_lds<NB, R>();
 #pragma unroll
     for (int r = 0; r < R; r++) {
-        if (!gv[r] || k[r] >= a.n_north) continue;
-        const int kn = k[r], ks = a.nrings - 1 - k[r];
-        double *qn = a.q + 2 * (((size_t)kn * (a.L + 1) + m) * a.nmaps + a.map0);
-        double *qs = a.q + 2 * (((size_t)ks * (a.L + 1) + m) * a.nmaps + a.map0);
+        if (g0 + r >= gend) break;
+        if (r) __syncthreads();  // the previous group has been read
+#pragma unroll
+        for (int c = 0; c < NC; c++) room[c * 64 + lane] = acc[r][c];
+        __syncthreads();
+        const int k = (g0 + r) * kLanes + lane, ks = a.nrings - 1 - k;
+        if (k >= a.n_north || (t && ks == k)) continue;
+        double2 *q = reinterpret_cast<double2 *>(a.q) + ((size_t)(t ? ks : k) * (L + 1) + m) * a.nmaps + a.map0;
 #pragma unroll
         for (int b = 0; b < NB; b++) {
-            double nr = accE_r[r][b] + accO_r[r][b], ni = accE_i[r][b] + accO_i[r][b];
-            double sr = accE_r[r][b] - accO_r[r][b], si = accE_i[r][b] - accO_i[r][b];
-            if (m == 0) ni = si = 0.0;  // real field: Im a_l0 is ignored
-            *reinterpret_cast<double2 *>(qn + 2 * b) = make_double2(nr, ni);
-            if (ks != kn) *reinterpret_cast<double2 *>(qs + 2 * b) = make_double2(sr, si);
+            const double ore = other[(2 * b) * 64 + lane], oim = other[(2 * b + 1) * 64 + lane];
+            double2 v = t ? make_double2(ore - acc[r][2 * b], oim - acc[r][2 * b + 1])
+                          : make_double2(acc[r][2 * b] + ore, acc[r][2 * b + 1] + oim);
+            if (m == 0) v.y = 0.0;  // real field: Im a_l0 is ignored
+            q[b] = v;
         }
     }
 }
 
-// One launch covers every (m, ring block).  Workgroups are dispatched
-// round-robin over the 8 XCDs: block b runs on XCD b % 8, and the ring
-// blocks of one order m take consecutive slots of one XCD so that its L2
-// serves the m's coefficient and a_lm stream to all of them.  Orders are
-// visited from m = 0 (the longest chains) upward.  Within an order the
-// compensated (double-double) waves nearest the poles come first, one 64-ring
-// group each, so their long chains start early; they take the maps two at a
-// time to stay inside the FP64 waves' register budget.  The FP64 waves
-// follow with R groups each.
+// The block of work rb of an order: pole blocks first (R groups each, the
+// last one partial), then the plain ones.
 template <int NB, int R>
-__global__ __launch_bounds__(64, (R == 4 ? 2 : 4)) void k_legendre(LegArgs a) {
-    const int nrb = a.dd_groups + a.fp_blocks;
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int m = 8 * (slot / nrb) + xcd;
-    const int rb = slot % nrb;
-    if (m > a.L) return;
-    if (rb < a.dd_groups) {
-        constexpr int NBD = NB < 2 ? NB : 2;
-        for (int b0 = 0; b0 < NB; b0 += NBD) {
-            LegArgs ab = a;
-            ab.map0 = a.map0 + b0;
-            legendre_wave<NBD, 1, true>(ab, m, rb);
+__device__ __forceinline__ void leg_item(const LegArgs &a, const int m, const int rb, double *lds) {
+    if (rb < a.pole_blocks)
+        leg_block<NB, R, true>(a, m, rb * R, a.pole_groups, lds);
+    else
+        leg_block<NB, R, false>(a, m, a.first_plain + (rb - a.pole_blocks) * R, a.ng, lds);
+}
+
+// Double-double form of the recurrence, for plans whose dd_sin was chosen by
+// the caller (and for polar groups that reach too far from the pole for the
+// split recurrence): one wave, order m, the 64 rings of group g, both
+// parities.
+template <int NB>
+__device__ __forceinline__ void legendre_dd_wave(const LegArgs &a, const int m, const int g) {
+    const int lane = threadIdx.x;
+    const int L = a.L;
+    const int k = g * kLanes + lane;
+    // wave-uniform chain range
+    const int lo = a.grp_lo[(size_t)m * a.ng + g], hi = a.grp_hi[(size_t)m * a.ng + g];
+    const int n0 = (L - m) / 2 + 1;                         // even chain length
+    const int n1 = (L - m >= 1) ? (L - m - 1) / 2 + 1 : 0;  // odd chain length
+
+    double acc[2][2 * NB];  // [parity][map, re/im]
+#pragma unroll
+    for (int c = 0; c < 2 * NB; c++) acc[0][c] = acc[1][c] = 0.0;
+
+    if (lo < n0) {
+        const dd z2 = {a.z2_hi[k], a.z2_lo[k]};
+        int sid[2];
+        dd p0[2], p1[2];
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            sid[t] = a.start_idx[(size_t)(2 * m + t) * a.np + k];
+            p0[t] = p1[t] = {0.0, 0.0};
         }
-    } else {
-        legendre_wave<NB, R, false>(a, m, a.dd_groups + (rb - a.dd_groups) * R);
+        const double *__restrict__ ch = a.coef_hi + 4 * a.coef_off[m];
+        const double *__restrict__ cl = a.coef_lo + 4 * a.coef_off[m];
+        const double *__restrict__ al = a.alm + 2 * ((size_t)m * (2 * L + 3 - m) / 2 * a.nmaps + a.map0);
+        const int astride = 2 * a.nmaps;  // doubles between consecutive l
+        for (int i = lo; i < n0; i++) {
+            if (i % kChunk == 0 && i <= hi) {
+#pragma unroll
+                for (int t = 0; t < 2; t++)
+                    if (sid[t] == i) {
+                        const size_t row = (size_t)(2 * m + t) * 2;
+                        p0[t] = {a.start_val[row * a.np + k], a.start_lo[row * a.n_dd_pad + k]};
+                        p1[t] = {a.start_val[(row + 1) * a.np + k], a.start_lo[(row + 1) * a.n_dd_pad + k]};
+                    }
+            }
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                const double *ap = al + (size_t)(2 * i + t) * astride;
+#pragma unroll
+                for (int c = 0; c < 2 * NB; c++)
+                    acc[t][c] = __builtin_fma(p0[t].h, t == 0 || i < n1 ? ap[c] : 0.0, acc[t][c]);
+                const int e = 4 * (2 * i + 2 + t);
+                const dd A = dd_add(dd_mul(z2, {ch[e], cl[e]}), {ch[e + 1], cl[e + 1]});
+                const dd nx = dd_add(dd_mul(A, p1[t]), dd_mul({ch[e + 2], cl[e + 2]}, p0[t]));
+                p0[t] = p1[t];
+                p1[t] = nx;
+            }
+        }
+    }
+    if (k >= a.n_north) return;
+    const int ks = a.nrings - 1 - k;
+    double2 *qn = reinterpret_cast<double2 *>(a.q) + ((size_t)k * (L + 1) + m) * a.nmaps + a.map0;
+    double2 *qs = reinterpret_cast<double2 *>(a.q) + ((size_t)ks * (L + 1) + m) * a.nmaps + a.map0;
+#pragma unroll
+    for (int b = 0; b < NB; b++) {
+        const double er = acc[0][2 * b], ei = acc[0][2 * b + 1], od = acc[1][2 * b], oi = acc[1][2 * b + 1];
+        qn[b] = make_double2(er + od, m == 0 ? 0.0 : ei + oi);  // real field: Im a_l0 is ignored
+        if (ks != k) qs[b] = make_double2(er - od, m == 0 ? 0.0 : ei - oi);
     }
 }
+
+template <int NB>
+__global__ __launch_bounds__(64) void k_legendre_dd(LegArgs a) {
+    legendre_dd_wave<NB>(a, blockIdx.x / a.dd_groups, blockIdx.x % a.dd_groups);
+}
+
+// Order of the work of one XCD (workgroups are dealt to the 8 XCDs round
+// robin): eight consecutive orders of each 64, all their blocks, so that the
+// XCD's L2 serves an order's coefficient and a_lm stream to all its blocks
+// and gathers the 16 NB-byte stores of neighbouring orders of a ring into
+// whole lines.  Every other 64 orders are dealt in reverse, which evens out
+// the chain lengths.  Low orders (the longest chains) come first.
+__device__ __forceinline__ int leg_order(int xcd, int s) {
+    const int j = s >> 3;
+    return 64 * j + 8 * (j & 1 ? 7 - xcd : xcd) + (s & 7);
+}
+
+// One launch covers every (m, ring block).
+template <int NB, int R>
+__global__ __launch_bounds__(128, (R == 4 ? 4 : 1)) void k_legendre(LegArgs a) {
+    __shared__ __attribute__((aligned(16))) double lds[2 * leg_wave_lds<NB, R>()];
+    const int nrb = a.pole_blocks + a.plain_blocks;
+    const int slot = blockIdx.x >> 3, s = slot / nrb;
+    const int m = leg_order(blockIdx.x & 7, s);
+    if (m > a.L) return;
+    // an XCD deals its workgroups to its shader engines round robin: the
+    // first block of each order moves on by one, so that no engine gets the
+    // same (long or short) ring blocks of every order
+    leg_item<NB, R>(a, m, (slot + s) % nrb, lds);
+}
+
+// Rings per lane of a pass of nb maps: the plan's choice, or by the number
+// of wavefronts at one ring per lane.  More rings per lane share a step's
+// operand reads, but cut the number of wavefronts and run a lane's rings from
+// the earliest of their chains.  Measured at 1, 2 and 4 rings, four maps:
+// L = 255 (2048 wavefronts) 12.2, 15.2, 23.6 us; L = 511 (8192) 42, 47, 62 us;
+// L = 767 (18432) 109, 98, 123 us; L = 1023 (32768) 225, 195, 224 us; L = 2047
+// (131072) -, 1404, 1361 us.  Above four maps the state of four rings does
+// not fit the registers.
+static int leg_rings(const sht_plan_s *p, int nb) {
+    int R = p->opts.rings_per_lane;
+    if (R != 1 && R != 2 && R != 4) {
+        const long long waves = 2LL * (p->L + 1) * (p->n_north_pad / kLanes);
+        R = waves >= 65536 ? 4 : waves >= 12288 ? 2 : 1;
+    }
+    return nb > 4 ? std::min(R, 2) : R;
+}
+
+// Maps of the next pass with `left` maps to go.
+int leg_pass_maps(int left) { return left >= 8 ? 8 : left == 7 ? 4 : left; }
 
 template <int NB, int R>
 static hipError_t launch_nbr(const sht_plan_s *p, LegArgs a, hipStream_t st) {
-    const int morders = (p->L + 1 + 7) / 8 * 8;  // orders rounded up to the XCD count
-    a.dd_groups = p->n_dd_groups;
-    a.fp_blocks = (a.ng - p->n_dd_groups + R - 1) / R;
-    const long long grid = (long long)morders * (a.dd_groups + a.fp_blocks);
-    hipLaunchKernelGGL((k_legendre<NB, R>), dim3((unsigned)grid), dim3(kLanes), 0, st, a);
+    const long long grid = (long long)((p->L + 64) / 64 * 64) * (a.pole_blocks + a.plain_blocks);
+    if (grid > 0) hipLaunchKernelGGL((k_legendre<NB, R>), dim3((unsigned)grid), dim3(128), 0, st, a);
     return hipGetLastError();
 }
 
 template <int NB>
-static hipError_t launch_nb(const sht_plan_s *p, LegArgs a, hipStream_t st) {
-    switch (p->rings_per_lane) {
-        case 1: return launch_nbr<NB, 1>(p, a, st);
-        case 4: return launch_nbr<NB, 4>(p, a, st);
-        default: return launch_nbr<NB, 2>(p, a, st);
+static hipError_t launch_nb(const sht_plan_s *p, const LegArgs &a, int R, hipStream_t st) {
+    if constexpr (NB <= 4) {
+        if (R == 4) return launch_nbr<NB, 4>(p, a, st);
     }
+    return R == 1 ? launch_nbr<NB, 1>(p, a, st) : launch_nbr<NB, 2>(p, a, st);
 }
 
 // Persistent form for batches of requests (the many-transform regime of
-// Sec. 3.4): one launch per wave shape (compensated waves of 2 or 1 maps,
-// FP64 waves of 4, 2 or 1 maps) for every request of a batch, so that each
-// launch runs one specialised body at its own occupancy.  Work items {pass,
-// m, ring block, first map} of one shape come in eight lists, one per XCD
-// (the items of one pass and order share a list, so that XCD's L2 serves the
-// order's coefficient and a_lm stream to all of them), each sorted longest
-// first and cut into chunks that shrink along the list.  A wave takes chunks
-// from its own XCD's list through a device counter (a vector-memory atomic)
-// and, once that list is exhausted, from the others in turn; it leaves when
-// every counter has passed the end of its list, so every wave reaches the
-// exit.  The wave body is k_legendre's.
+// Sec. 3.4): one launch per pass shape (double-double waves of 2 or 1 maps,
+// workgroups of 8, 6, 5, 4, 3, 2 or 1 maps) for every request of a batch, so
+// that each launch runs one specialised body at its own occupancy.  Work
+// items {pass, m, ring block, first map} of one shape come in eight lists,
+// one per XCD (the items of one pass and order share a list, so that XCD's L2
+// serves the order's coefficient and a_lm stream to all of them), each sorted
+// longest first and cut into chunks that shrink along the list.  A workgroup
+// takes chunks from its own XCD's list through a device counter (a
+// vector-memory atomic) and, once that list is exhausted, from the others in
+// turn; it leaves when every counter has passed the end of its list, so every
+// workgroup reaches the exit.  The bodies are k_legendre's and
+// k_legendre_dd's.
 constexpr int kQueueLists = 8;
 constexpr int kQueueStride = 16;  // counters 64 bytes apart
 
@@ -280,19 +376,22 @@ __global__ void k_queue_reset(unsigned *c) {
 }
 
 template <int NB, int R, bool DD>
-__global__ __launch_bounds__(64, (R == 4 ? 2 : 4)) void k_legendre_queue(const LegArgs *__restrict__ passes,
-                                                                         const int4 *__restrict__ items,
-                                                                         const unsigned *__restrict__ chunk_off,
-                                                                         const unsigned *__restrict__ list_off,
-                                                                         unsigned *__restrict__ counter) {
+__global__ __launch_bounds__(DD ? 64 : 128) void k_legendre_queue(const LegArgs *__restrict__ passes,
+                                                                  const int4 *__restrict__ items,
+                                                                  const unsigned *__restrict__ chunk_off,
+                                                                  const unsigned *__restrict__ list_off,
+                                                                  unsigned *__restrict__ counter) {
+    __shared__ __attribute__((aligned(16))) double lds[DD ? 2 : 2 * leg_wave_lds<NB, R>()];
+    __shared__ unsigned taken;
     const int home = blockIdx.x & (kQueueLists - 1);  // workgroups are dealt to the XCDs round robin
     for (int s = 0; s < kQueueLists; s++) {
         const int x = (home + s) & (kQueueLists - 1);
         const unsigned lo = list_off[x], cnt = list_off[x + 1] - lo;
         for (;;) {
-            unsigned c = 0;
-            if (threadIdx.x == 0) c = atomicAdd(counter + x * kQueueStride, 1u);
-            c = __shfl(c, 0);
+            __syncthreads();  // the previous item has left the LDS, and every thread has read `taken`
+            if (threadIdx.x == 0) taken = atomicAdd(counter + x * kQueueStride, 1u);
+            __syncthreads();
+            const unsigned c = __builtin_amdgcn_readfirstlane(taken);
             if (c >= cnt) break;
             const unsigned i0 = chunk_off[lo + c], i1 = chunk_off[lo + c + 1];
             for (unsigned i = i0; i < i1; i++) {
@@ -301,10 +400,12 @@ __global__ __launch_bounds__(64, (R == 4 ? 2 : 4)) void k_legendre_queue(const L
                 const int rb = __builtin_amdgcn_readfirstlane(w.z), b0 = __builtin_amdgcn_readfirstlane(w.w);
                 LegArgs a = passes[pi];
                 a.map0 += b0;
-                if (DD)
-                    legendre_wave<NB, 1, true>(a, m, rb);
-                else
-                    legendre_wave<NB, R, false>(a, m, a.dd_groups + (rb - a.dd_groups) * R);
+                if constexpr (DD) {
+                    legendre_dd_wave<NB>(a, m, rb);
+                } else {
+                    if (i != i0) __syncthreads();  // the previous item has left the LDS
+                    leg_item<NB, R>(a, m, rb, lds);
+                }
             }
         }
     }
@@ -314,11 +415,16 @@ typedef void (*QueueKernel)(const LegArgs *, const int4 *, const unsigned *, con
 
 template <int R>
 static QueueKernel queue_kernel_r(int shape) {
+    constexpr int R2 = R < 2 ? R : 2;
     switch (shape) {
         case 0: return k_legendre_queue<2, 1, true>;
         case 1: return k_legendre_queue<1, 1, true>;
-        case 2: return k_legendre_queue<4, R, false>;
-        case 3: return k_legendre_queue<2, R, false>;
+        case 2: return k_legendre_queue<8, R2, false>;
+        case 3: return k_legendre_queue<6, R2, false>;
+        case 4: return k_legendre_queue<5, R2, false>;
+        case 5: return k_legendre_queue<4, R, false>;
+        case 6: return k_legendre_queue<3, R, false>;
+        case 7: return k_legendre_queue<2, R, false>;
         default: return k_legendre_queue<1, R, false>;
     }
 }
@@ -331,17 +437,19 @@ static QueueKernel queue_kernel(int shape, int R) {
     }
 }
 
-int queue_shape(bool dd, int nb) { return dd ? (nb >= 2 ? 0 : 1) : (nb >= 4 ? 2 : nb >= 2 ? 3 : 4); }
+int queue_shape(bool dd, int nb) { return dd ? (nb >= 2 ? 0 : 1) : nb >= 8 ? 2 : 9 - nb; }
+int queue_rings(int nb, int R) { return nb > 4 ? std::min(R, 2) : R; }
+int queue_threads(int shape) { return shape < 2 ? 64 : 128; }
 
-// Waves of the persistent launch of one shape: as many as the current device
-// keeps resident at once.
+// Workgroups of the persistent launch of one shape: as many as the current
+// device keeps resident at once.
 hipError_t legendre_queue_grid(int shape, int rings_per_lane, int *grid) {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)queue_kernel(shape, rings_per_lane), 64,
-                                                         0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)queue_kernel(shape, rings_per_lane),
+                                                         queue_threads(shape), 0);
     *grid = std::max(std::max(per_cu, 1) * std::max(cus, 1) / kQueueLists, 1) * kQueueLists;
     return e;
 }
@@ -356,23 +464,28 @@ hipError_t launch_legendre_queue(int shape, const LegArgs *passes, const int4 *i
                                  hipStream_t st) {
     if (shape < 0 || shape >= kQueueShapes || grid < 0) return hipErrorInvalidValue;
     if (grid == 0) return hipSuccess;  // no items of this shape
-    hipLaunchKernelGGL(queue_kernel(shape, rings_per_lane), dim3((unsigned)grid), dim3(64), 0, st, passes, items,
-                       chunk_off, list_off + shape * (kQueueLists + 1), counter + shape * kQueueLists * kQueueStride);
+    hipLaunchKernelGGL(queue_kernel(shape, rings_per_lane), dim3((unsigned)grid), dim3(queue_threads(shape)), 0, st,
+                       passes, items, chunk_off, list_off + shape * (kQueueLists + 1),
+                       counter + shape * kQueueLists * kQueueStride);
     return hipGetLastError();
 }
 
 // Argument block of one pass (maps map0 .. map0 + nb - 1 of nmaps) for
-// waves of R rings per lane.
+// R rings per lane.
 LegArgs leg_args(const sht_plan_s *p, int nmaps, int map0, int R, const double *alm, double *q) {
     LegArgs a;
     a.z2_hi = p->d_z2_hi;
     a.z2_lo = p->d_z2_lo;
+    a.s2 = p->d_s2;
     a.coef_off = p->d_coef_off;
     a.coef_hi = p->d_coef_hi;
     a.coef_lo = p->d_coef_lo;
+    a.coef_pole = p->d_coef_pole;
+    a.coef_sc = p->d_coef_sc;
     a.start_idx = p->d_start_idx;
     a.start_val = p->d_start_val;
     a.start_lo = p->d_start_lo;
+    a.start_d = p->d_start_d;
     a.grp_lo = p->d_grp_lo;
     a.grp_hi = p->d_grp_hi;
     a.alm = alm;
@@ -382,55 +495,138 @@ LegArgs leg_args(const sht_plan_s *p, int nmaps, int map0, int R, const double *
     a.n_north = p->n_north;
     a.np = p->n_north_pad;
     a.n_dd_pad = std::max(p->n_dd_pad, 1);
+    a.n_pole_pad = std::max(p->pole_groups, 1) * kLanes;
     a.ng = p->n_north_pad / kLanes;
     a.nmaps = nmaps;
     a.map0 = map0;
-    a.dd_groups = p->n_dd_groups;
-    a.fp_blocks = (a.ng - p->n_dd_groups + R - 1) / R;
+    a.pole_groups = p->pole_groups;
+    a.dd_groups = p->pole_groups > 0 ? 0 : p->n_dd_groups;
+    a.first_plain = a.pole_groups + a.dd_groups;
+    a.pole_blocks = (a.pole_groups + R - 1) / R;
+    a.plain_blocks = (a.ng - a.first_plain + R - 1) / R;
     return a;
 }
 
 hipError_t launch_legendre(const sht_plan_s *p, int nmaps, const double *alm, double *q,
                            hipStream_t stream) {
-    LegArgs a;
-    a.z2_hi = p->d_z2_hi;
-    a.z2_lo = p->d_z2_lo;
-    a.coef_off = p->d_coef_off;
-    a.coef_hi = p->d_coef_hi;
-    a.coef_lo = p->d_coef_lo;
-    a.start_idx = p->d_start_idx;
-    a.start_val = p->d_start_val;
-    a.start_lo = p->d_start_lo;
-    a.grp_lo = p->d_grp_lo;
-    a.grp_hi = p->d_grp_hi;
-    a.alm = alm;
-    a.q = q;
-    a.L = p->L;
-    a.nrings = p->nrings;
-    a.n_north = p->n_north;
-    a.np = p->n_north_pad;
-    a.n_dd_pad = std::max(p->n_dd_pad, 1);
-    a.dd_groups = a.fp_blocks = 0;
-    a.ng = p->n_north_pad / kLanes;
-    a.nmaps = nmaps;
     hipError_t e = hipSuccess;
-    // maps in passes of 4, then 2, then 1
-    int b = 0;
-    while (b < nmaps && e == hipSuccess) {
-        a.map0 = b;
-        int left = nmaps - b;
-        if (left >= 4) {
-            e = launch_nb<4>(p, a, stream);
-            b += 4;
-        } else if (left >= 2) {
-            e = launch_nb<2>(p, a, stream);
-            b += 2;
-        } else {
-            e = launch_nb<1>(p, a, stream);
-            b += 1;
+    for (int b = 0; b < nmaps && e == hipSuccess;) {
+        const int nb = leg_pass_maps(nmaps - b), R = leg_rings(p, nb);
+        const LegArgs a = leg_args(p, nmaps, b, R, alm, q);
+        switch (nb) {
+            case 8: e = launch_nb<8>(p, a, R, stream); break;
+            case 6: e = launch_nb<6>(p, a, R, stream); break;
+            case 5: e = launch_nb<5>(p, a, R, stream); break;
+            case 4: e = launch_nb<4>(p, a, R, stream); break;
+            case 3: e = launch_nb<3>(p, a, R, stream); break;
+            case 2: e = launch_nb<2>(p, a, R, stream); break;
+            default: e = launch_nb<1>(p, a, R, stream); break;
         }
+        b += nb;
+    }
+    // double-double rings, two maps at a time
+    const LegArgs d = leg_args(p, nmaps, 0, 1, alm, q);
+    for (int b = 0; d.dd_groups > 0 && b < nmaps && e == hipSuccess;) {
+        const int nb = std::min(2, nmaps - b);
+        LegArgs a = d;
+        a.map0 = b;
+        const dim3 grid((unsigned)((p->L + 1) * d.dd_groups));
+        if (nb == 2)
+            hipLaunchKernelGGL(k_legendre_dd<2>, grid, dim3(64), 0, stream, a);
+        else
+            hipLaunchKernelGGL(k_legendre_dd<1>, grid, dim3(64), 0, stream, a);
+        e = hipGetLastError();
+        b += nb;
     }
     return e;
+}
+
+// ---- tables of the scaled and the split recurrence, made once per plan ------
+// With D = ((l+1)^2 - m^2)((l+2)^2 - m^2) and Q_l = sqrt((2l+5) / ((2l+1) D)):
+//   beta_l = (2l+3)(2l+1) Q_l,  r_l = (l+1+m)(l+2+m) Q_l,
+//   h_l = (l-m)(l-1-m) (2l+3)/(2l-1) Q_l.
+// Entry e = l - m of order m (at the plan's coefficient offsets) holds
+// {h_l, -beta_l, r_{l-2}, 0}; entries 0 and 1 are not used.
+__device__ __forceinline__ dd pole_Q(double l, double m) {
+    const dd D = dd_mul({(l + 1 - m) * (l + 1 + m), 0.0}, {(l + 2 - m) * (l + 2 + m), 0.0});
+    return dd_sqrt(dd_div({2 * l + 5, 0.0}, dd_mul({2 * l + 1, 0.0}, D)));
+}
+
+__global__ __launch_bounds__(256) void k_pole_coef(const long long *__restrict__ coef_off, double4 *__restrict__ out) {
+    const int m = blockIdx.x;
+    const long long base = coef_off[m], cnt = coef_off[m + 1] - base;
+    for (long long e = threadIdx.x; e < cnt; e += 256) {
+        double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
+        if (e >= 2) {
+            const double l = (double)(m + e), mm = m;
+            const dd Q = pole_Q(l, mm);
+            v.x = dd_mul(dd_div(dd_mul({(l - mm) * (l - 1 - mm), 0.0}, {2 * l + 3, 0.0}), {2 * l - 1, 0.0}), Q).h;
+            v.y = -dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, Q).h;
+            v.z = dd_mul({(l - 1 + mm) * (l + mm), 0.0}, pole_Q(l - 2, mm)).h;
+        }
+        out[base + e] = v;
+    }
+}
+
+// d = P~_{l+2} - r_l P~_l at each chain's start, l = m + t + 2 start_idx, from
+// the stored start values (with their low parts on the first n_dd_pad rings;
+// farther from the pole d no longer cancels).
+__global__ __launch_bounds__(256) void k_pole_start(LegArgs a, double *__restrict__ out) {
+    const int row = blockIdx.x, m = row >> 1, t = row & 1;
+    for (int k = threadIdx.x; k < a.n_pole_pad; k += 256) {
+        const int i = a.start_idx[(size_t)row * a.np + k];
+        double d = 0.0;
+        if (i < kDead) {
+            const size_t r2 = (size_t)row * 2;
+            dd p0 = {a.start_val[r2 * a.np + k], 0.0}, p1 = {a.start_val[(r2 + 1) * a.np + k], 0.0};
+            if (k < a.n_dd_pad) {
+                p0.l = a.start_lo[r2 * a.n_dd_pad + k];
+                p1.l = a.start_lo[(r2 + 1) * a.n_dd_pad + k];
+            }
+            const double l = m + t + 2.0 * i;
+            const dd r = dd_mul({(l + 1 + m) * (l + 2 + m), 0.0}, pole_Q(l, m));
+            d = dd_sub(p1, dd_mul(r, p0)).h;
+        }
+        out[(size_t)row * a.n_pole_pad + k] = d;
+    }
+}
+
+// Scaled recurrence: entry e = l - m of order m holds {b_l, -b_l d_l, f_l,
+// 1 / f_l}, f_m = f_{m+1} = 2; one thread per order and parity follows the
+// product of the c_l in double-double.
+__global__ __launch_bounds__(64) void k_scaled_coef(const long long *__restrict__ coef_off, double4 *__restrict__ out,
+                                                    int rows) {
+    const int row = blockIdx.x * 64 + threadIdx.x;
+    if (row >= rows) return;
+    const int m = row >> 1;
+    const long long base = coef_off[m], cnt = coef_off[m + 1] - base;
+    const double mm = m;
+    dd f = {2.0, 0.0};
+    for (long long e = row & 1; e < cnt; e += 2) {
+        const double l = mm + e;
+        const dd b = dd_mul(f, f);
+        const dd d = dd_div({2 * l * (l + 1) - 2 * mm * mm - 1, 0.0}, {(2 * l - 1) * (2 * l + 3), 0.0});
+        out[base + e] = make_double4(b.h, -dd_mul(b, d).h, f.h, 1.0 / f.h);
+        // 1 / c_l = (2l+3) sqrt((2l+1)(2l+5) / D) = (2l+3)(2l+1) Q_l
+        f = dd_div(dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, pole_Q(l, mm)), f);
+    }
+}
+
+hipError_t fill_scaled_coef(const sht_plan_s *p) {
+    const int rows = 2 * (p->L + 1);
+    hipLaunchKernelGGL(k_scaled_coef, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, nullptr, p->d_coef_off,
+                       reinterpret_cast<double4 *>(p->d_coef_sc), rows);
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : hipStreamSynchronize(nullptr);
+}
+
+hipError_t fill_pole_tables(const sht_plan_s *p) {
+    hipLaunchKernelGGL(k_pole_coef, dim3((unsigned)(p->L + 1)), dim3(256), 0, nullptr, p->d_coef_off,
+                       reinterpret_cast<double4 *>(p->d_coef_pole));
+    const LegArgs a = leg_args(p, 1, 0, 1, nullptr, nullptr);
+    hipLaunchKernelGGL(k_pole_start, dim3((unsigned)(2 * (p->L + 1))), dim3(256), 0, nullptr, a, p->d_start_d);
+    hipError_t e = hipGetLastError();
+    return e != hipSuccess ? e : hipStreamSynchronize(nullptr);
 }
 
 }  // namespace sht

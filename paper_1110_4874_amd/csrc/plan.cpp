@@ -509,6 +509,12 @@ static hipError_t up(T **dst, const std::vector<T> &src, size_t *bytes) {
     return e;
 }
 
+// Reach of the split recurrence from the poles, as sin(theta) of the last
+// ring of a 64-ring group: its relative error (L = 4095, against long
+// double) is 2e-15 to 2e-14 up to 0.1 and 4e-14 at 0.4, where the plain
+// recurrence's is 1e-12 and 3e-13; the two meet at 0.7.
+constexpr double kPoleSin = 0.3, kPoleSinMax = 0.6;
+
 int upload_tables(sht_plan_s *p) {
     size_t b = 0;
     hipError_t e = hipSuccess;
@@ -523,7 +529,6 @@ int upload_tables(sht_plan_s *p) {
     UP(d_ring_bs_off, ring_bs_off);
     UP(d_coef_off, coef_off);
     UP(d_coef_hi, coef_hi);
-    UP(d_coef_lo, coef_lo);
     UP(d_start_idx, start_idx);
     UP(d_start_val, start_val);
     UP(d_start_lo, start_lo);
@@ -535,6 +540,44 @@ int upload_tables(sht_plan_s *p) {
     UP(d_ring_chirp_off, ring_chirp_off);
     UP(d_pol_ring, pol_ring);
     UP(d_pol_K, pol_K);
+    // Rings nearest the poles: the split recurrence when the plan has the
+    // default threshold and its polar groups end within kPoleSinMax, where
+    // that recurrence is at least as accurate as the plain one; else
+    // double-double, which needs the coefficients' low parts (and so does the
+    // interpolation form).  The split recurrence also takes the groups that
+    // end below kPoleSin: the plain one loses 10x more there, at one FP64
+    // operation less a step.
+    p->pole_groups = 0;
+    std::vector<double> s2(p->n_north_pad, 1.0);
+    for (int k = 0; k < p->n_north; k++) {
+        ld z, w;
+        int J, s;
+        long long off;
+        ring_geometry(p->nside, k + 1, &z, &w, &J, &s, &off);
+        s2[k] = (double)w;
+    }
+    auto group_sin = [&](int g) { return sqrt(s2[std::min((g + 1) * kLanes, p->n_north) - 1]); };
+    if (p->opts.dd_sin < 0 && p->n_dd_groups > 0 && group_sin(p->n_dd_groups - 1) <= kPoleSinMax) {
+        int g = p->n_dd_groups;
+        while (g < p->n_north_pad / kLanes && group_sin(g) <= kPoleSin) g++;
+        p->pole_groups = g;
+    }
+    UP(d_coef_lo, coef_lo);
+    {
+        const size_t nc = p->coef_hi.size() * sizeof(double);
+        if (e == hipSuccess) e = hipMalloc((void **)&p->d_coef_sc, nc);
+        if (e == hipSuccess) e = fill_scaled_coef(p);
+        b += nc;
+    }
+    if (p->pole_groups > 0) {
+        const size_t nc = p->coef_hi.size() * sizeof(double),
+                     ns = (size_t)(p->L + 1) * 2 * p->pole_groups * kLanes * sizeof(double);
+        if (e == hipSuccess) e = up(&p->d_s2, s2, &b);
+        if (e == hipSuccess) e = hipMalloc((void **)&p->d_coef_pole, nc);
+        if (e == hipSuccess) e = hipMalloc((void **)&p->d_start_d, ns);
+        if (e == hipSuccess) e = fill_pole_tables(p);
+        b += nc + ns;
+    }
 #undef UP
     for (auto &rc : p->classes)
         if (e == hipSuccess) e = up(&rc.d_rings, rc.rings, &b);
@@ -602,7 +645,7 @@ int upload_tables(sht_plan_s *p) {
 }
 
 void free_device_tables(sht_plan_s *p) {
-    void *ptrs[] = {p->d_z2_hi,     p->d_z2_lo,     p->d_ring_J,     p->d_ring_s,   p->d_ring_M,
+    void *ptrs[] = {p->d_z2_hi,     p->d_z2_lo,     p->d_s2,         p->d_coef_sc,   p->d_coef_pole, p->d_start_d,    p->d_ring_J,     p->d_ring_s,   p->d_ring_M,
                     p->d_ring_off,  p->d_ring_bs_off, p->d_coef_off, p->d_coef_hi,  p->d_coef_lo,
                     p->d_start_idx, p->d_start_val, p->d_start_lo,   p->d_grp_lo,   p->d_grp_hi,
                     p->d_tw,        p->d_bs_table,  p->d_chirp,      p->d_ring_chirp_off,
@@ -618,7 +661,8 @@ void free_device_tables(sht_plan_s *p) {
     for (auto &rc : p->classes)
         if (rc.d_rings) (void)hipFree(rc.d_rings), rc.d_rings = nullptr;
 
-    p->d_z2_hi = p->d_z2_lo = nullptr;
+    p->d_z2_hi = p->d_z2_lo = p->d_s2 = p->d_coef_sc = p->d_coef_pole = p->d_start_d = nullptr;
+    p->pole_groups = 0;
     p->d_ring_J = p->d_ring_s = p->d_ring_M = nullptr;
     p->d_ring_off = p->d_ring_bs_off = p->d_coef_off = nullptr;
     p->d_coef_hi = p->d_coef_lo = nullptr;

@@ -4,7 +4,7 @@
 // transforms need more blocking than it built).
 //
 // sht_batch_create splits every request into the work items of the
-// brute-force Legendre phase, one per (pass of up to 4 maps, order m, ring
+// brute-force Legendre phase, one per (pass of up to 8 maps, order m, ring
 // block), estimates each item's cost from the plan's chain starts (chain
 // steps times rings, compensated ring blocks weighted by their extra
 // arithmetic), deals the items of each (pass, order) to one of eight lists,
@@ -33,7 +33,7 @@ using namespace sht;
 
 namespace {
 
-constexpr double kDdCost = 4.0;  // compensated step relative to an FP64 step
+constexpr double kDdCost = 4.0;  // double-double step relative to an FP64 step
 
 struct RingGroup {
     int lds_entries = 0;
@@ -77,7 +77,7 @@ struct sht_batch_s {
     unsigned *d_list_off = nullptr;   // [shape][9] list boundaries (chunk indices), one list per XCD
     unsigned *d_counter = nullptr;    // [shape][8] counters, 64 bytes apart
     long long nitems = 0, npasses = 0, nchunks = 0;
-    int grid[kQueueShapes] = {};  // waves of each persistent Legendre launch (0: none)
+    int grid[kQueueShapes] = {};  // workgroups of each persistent Legendre launch (0: none)
     // fork/join over internal streams: independent launches of a run (wave
     // shapes, map-group widths, ring classes) overlap
     hipStream_t st[kMaxStreams] = {};
@@ -281,36 +281,32 @@ int build_brute(sht_batch_s *b, const sht_batch_opts *o) {
         off += req_ws_bytes(q, b->path, b->fp32);
         const int ng = p->n_north_pad / kLanes;
         for (int m0 = 0; m0 < q.nmaps;) {
-            const int left = q.nmaps - m0, nb = left >= 4 ? 4 : left >= 2 ? 2 : 1;
-            const LegArgs a = leg_args(p, q.nmaps, m0, R, q.alm, qbuf);
+            const int nb = leg_pass_maps(q.nmaps - m0), Rp = queue_rings(nb, R);
+            const LegArgs a = leg_args(p, q.nmaps, m0, Rp, q.alm, qbuf);
             const int pi = (int)passes.size();
             passes.push_back(a);
-            const int nrb = a.dd_groups + a.fp_blocks;
             for (int m = 0; m <= p->L; m++) {
                 const int n0 = (p->L - m) / 2 + 1;
-                for (int rb = 0; rb < nrb; rb++) {
-                    int lo = kDead, nrg;
-                    double w;
-                    const bool dd = rb < a.dd_groups;
-                    if (dd) {
-                        lo = p->grp_lo[(size_t)m * ng + rb];
-                        nrg = 1;
-                        w = kDdCost;
-                    } else {
-                        const int g0 = a.dd_groups + (rb - a.dd_groups) * R;
-                        nrg = std::min(R, ng - g0);
-                        for (int g = g0; g < g0 + nrg; g++) lo = std::min(lo, p->grp_lo[(size_t)m * ng + g]);
-                        w = 1.0;
-                    }
-                    const double steps = lo < n0 ? (double)(n0 - lo) : 0.0;
-                    // compensated waves take the maps two at a time
-                    for (int b0 = 0; b0 < nb; b0 += dd ? 2 : nb) {
-                        const int nw = dd ? std::min(2, nb - b0) : nb;
-                        // chain steps (both parities) times rings, plus the stores
-                        const double cost = w * steps * nrg * (5.0 + 4.0 * nw) + 64.0 * nrg * nw;
-                        items.push_back({cost, make_int4(pi, m, rb, b0), queue_shape(dd, nw)});
-                    }
+                auto steps = [&](int g0, int g1) {  // chain steps of the groups [g0, g1)
+                    int lo = kDead;
+                    for (int g = g0; g < g1; g++) lo = std::min(lo, p->grp_lo[(size_t)m * ng + g]);
+                    return lo < n0 ? (double)(n0 - lo) : 0.0;
+                };
+                // chain steps (both parities) times rings, plus the stores
+                for (int rb = 0; rb < a.pole_blocks + a.plain_blocks; rb++) {
+                    const bool pole = rb < a.pole_blocks;
+                    const int g0 = pole ? rb * Rp : a.first_plain + (rb - a.pole_blocks) * Rp;
+                    const int g1 = std::min(g0 + Rp, pole ? a.pole_groups : ng);
+                    const double cost = steps(g0, g1) * (g1 - g0) * (5.0 + 4.0 * nb) + 64.0 * (g1 - g0) * nb;
+                    items.push_back({cost, make_int4(pi, m, rb, 0), queue_shape(false, nb)});
                 }
+                // double-double waves take the maps two at a time
+                for (int g = 0; g < a.dd_groups; g++)
+                    for (int b0 = 0; b0 < nb; b0 += 2) {
+                        const int nw = std::min(2, nb - b0);
+                        const double cost = kDdCost * steps(g, g + 1) * (5.0 + 4.0 * nw) + 64.0 * nw;
+                        items.push_back({cost, make_int4(pi, m, g, b0), queue_shape(true, nw)});
+                    }
             }
             m0 += nb;
         }
@@ -568,11 +564,12 @@ int sht_batch_run(const sht_batch_t *b, void *stream) {
         join(0, k);
     } else {
         e = launch_queue_reset(b->d_counter, st);
-        fork(0, kQueueShapes);
+        const int k = std::min(kQueueShapes, kMaxStreams);
+        fork(0, k);
         for (int v = 0; v < kQueueShapes && e == hipSuccess; v++)
             e = launch_legendre_queue(v, b->d_passes, b->d_items, b->d_chunk_off, b->d_list_off, b->d_counter,
-                                      b->rings_per_lane, b->grid[v], b->st[v]);
-        join(0, kQueueShapes);
+                                      b->rings_per_lane, b->grid[v], b->st[v % kMaxStreams]);
+        join(0, k);
     }
     // phase 1: one ring launch per ring size class
     const int kr = std::min((int)b->groups.size(), kMaxStreams);
@@ -595,7 +592,7 @@ int sht_batch_stats(const sht_batch_t *b, long long *items, int *launches, int *
     *waves = 0;
     for (int v = 0; v < kQueueShapes; v++) {
         *launches += b->grid[v] > 0;
-        *waves += b->grid[v];
+        *waves += b->grid[v] * (queue_threads(v) / 64);
     }
     if (b->path == SHT_PATH_BUTTERFLY) {
         *items = 0;
