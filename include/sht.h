@@ -100,9 +100,9 @@ typedef struct sht_plan_opts {
     double dd_sin;     /* rings with sin(theta) below this threshold run a
                           recurrence that is stable near the poles, where the
                           plain FP64 one loses ~L eps / sin(theta).  < 0 selects
-                          the default 0.1 * L / 4095 and, in synthesis, the
-                          recurrence split about its solution at the pole
-                          (relative error ~1e-14); a value >= 0 runs them in
+                          the default 0.1 * L / 4095 and the recurrence
+                          split about its solution at the pole (relative
+                          error ~1e-14); a value >= 0 runs them in
                           compensated double-double arithmetic. */
     int nthreads;      /* host threads for plan construction; 0 = all cores */
     int rings_per_lane;/* rings each lane of the FP64 Legendre kernel owns:

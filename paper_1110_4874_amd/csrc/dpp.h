@@ -1,5 +1,6 @@
-// FP64 multiply-adds whose one operand is broadcast within each 16-lane row
-// by DPP (gfx950 row_newbcast), and the plain broadcast of such a value.
+// Wave helpers of the FP64 kernels: multiply-adds whose one operand is
+// broadcast within each 16-lane row by DPP (gfx950 row_newbcast), the plain
+// broadcast of such a value, and the order of an XCD's work.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -60,6 +61,18 @@ __device__ __forceinline__ void fmac_row_bcast(double *acc, double rv, double p)
 template <int K>
 __device__ __forceinline__ double row_bcast(double x) {
     return __builtin_amdgcn_mov_dpp(x, 0x150 + K, 0xF, 0xF, false);
+}
+
+// Order m of item s of XCD xcd (workgroups are dealt to the 8 XCDs round
+// robin): eight consecutive orders of each 64, so that the XCD's L2 serves an
+// order's coefficient and a_lm stream to all its blocks, and gathers the 16
+// bytes per map of neighbouring orders of a ring into whole lines.  Every
+// other 64 orders are dealt in reverse, which evens out the chain lengths.
+// Low orders (the longest chains) come first.  Orders past L are skipped by
+// the caller; items go up to (L + 64) / 64 * 8.
+__device__ __forceinline__ int xcd_order(int xcd, int s) {
+    const int j = s >> 3;
+    return 64 * j + 8 * (j & 1 ? 7 - xcd : xcd) + (s & 7);
 }
 
 }  // namespace sht

@@ -34,7 +34,8 @@
 // P~_{l+2}/P~_l at theta -> 0, P~_{l+2} = (r_l + h_l - sin^2 beta_l) P~_l -
 // h_l r_{l-2} P~_{l-2} exactly, so
 //   P~_{l+2} = r_l P~_l + d_l,   d_{l+2} = h_{l+2} d_l - sin^2 beta_{l+2} P~_{l+2}
-// where sin^2(theta) enters with its own relative accuracy.  Four FP64
+// where sin^2(theta) enters with its own relative accuracy (in the scaled
+// variables with the coefficients scaled likewise).  Four FP64
 // operations a step instead of three; relative errors of 2e-15 to 2e-14 at
 // L = 4095 for sin(theta) <= 0.1 (double-double arithmetic, which these rings
 // ran before at about 45 operations a step and chain, made one wave's serial
@@ -74,30 +75,23 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
     const int n = L - m - t >= 0 ? (L - m - t) / 2 + 1 : 0;  // chain length
     double *room = lds + t * leg_wave_lds<NB, R>();
     double *stg = room + (leg_wave_lds<NB, R>() - 2 * CS);
-    const double4 *cf = reinterpret_cast<const double4 *>(POLE ? a.coef_pole : a.coef_sc) + a.coef_off[m] + t;
+    const double4 *cf = reinterpret_cast<const double4 *>(a.coef_sc) + a.coef_off[m] + t;
 
     int sid[R], lo = kDead, hi = -1;
     double x[R], P0[R], P1[R], acc[R][NC];
+    const size_t row = (size_t)(2 * m + t);
+    const double *v0p = a.start_val + row * 2 * a.np;
+    const double *v1p = POLE ? a.start_d + row * a.n_pole_pad : v0p + a.np;
+    double s0[R], s1[R];
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const bool ok = g0 + r < gend;
-        const int g = ok ? g0 + r : g0, k = g * kLanes + lane;
-        const size_t row = (size_t)(2 * m + t);
-        sid[r] = ok ? a.start_idx[row * a.np + k] : kDead;
+    for (int r = 0; r < R; r++) {  // groups past the last repeat it and never start
+        const int g = min(g0 + r, gend - 1), k = g * kLanes + lane;
+        sid[r] = a.start_idx[row * a.np + k] | (g0 + r < gend ? 0 : kDead);
         x[r] = POLE ? a.s2[k] : a.z2_hi[k];
-        // start values wait in LDS until their chain joins
-        double v0 = a.start_val[row * 2 * a.np + k];
-        double v1 = POLE ? a.start_d[row * a.n_pole_pad + k] : a.start_val[(row * 2 + 1) * a.np + k];
-        if (!POLE) {
-            const int i = sid[r] == kDead ? 0 : sid[r];
-            v0 *= cf[2 * i].w;
-            v1 *= cf[2 * i + 2].w;
-        }
-        *reinterpret_cast<double2 *>(room + 2 * (r * 64 + lane)) = make_double2(v0, v1);
-        if (ok) {
-            lo = min(lo, a.grp_lo[(size_t)m * a.ng + g]);
-            hi = max(hi, a.grp_hi[(size_t)m * a.ng + g]);
-        }
+        s0[r] = v0p[k];
+        s1[r] = v1p[k];
+        lo = min(lo, a.grp_lo[(size_t)m * a.ng + g]);
+        hi = max(hi, a.grp_hi[(size_t)m * a.ng + g]);
         P0[r] = P1[r] = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; c++) acc[r][c] = 0.0;
@@ -116,7 +110,7 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             base = a.alm + 2 * (((size_t)m * (2 * L + 3 - m) / 2 + t) * a.nmaps + a.map0) + comp;
             stride = 4u * (unsigned)a.nmaps;
         } else {
-            base = reinterpret_cast<const double *>(cf + 2) + min(comp - NC, POLE ? 2 : 1);
+            base = (POLE ? a.coef_pole : a.coef_sc) + 4 * (a.coef_off[m] + t + 2) + min(comp - NC, POLE ? 2 : 1);
             stride = 8u;
         }
         const double f1 = is_a ? 1.0 : 0.0, f0 = 1.0 - f1;  // factor of a staged value: f_l, or 1 for a coefficient
@@ -127,13 +121,13 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             for (int e = 0; e < E; e++) {
                 const unsigned i = (unsigned)min(c + (lane + 64 * e) / CW, n - 1);
                 pre[e] = base[(size_t)i * stride];
-                if (!POLE) fac[e] = fb[8 * i];
+                fac[e] = fb[8 * i];
             }
         };
         auto stage = [&](int sl, int c) {  // rows c .. c + kChunk - 1
 #pragma unroll
             for (int e = 0; e < E; e++)
-                stg[sl * CS + lane + 64 * e] = POLE ? pre[e] : pre[e] * __builtin_fma(fac[e], f1, f0);
+                stg[sl * CS + lane + 64 * e] = pre[e] * __builtin_fma(fac[e], f1, f0);
             if (c + kChunk > n) {
 #pragma unroll
                 for (int e = 0; e < E; e++)
@@ -146,7 +140,7 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
 #pragma unroll
             for (int r = 0; r < R; r++) {
                 fmac_row_bcast<NC>(acc[r], rv, P0[r]);
-                if constexpr (POLE) {  // c0 = h, c1 = -beta (both of the next l), c2 = r
+                if constexpr (POLE) {  // c0 = h, c1 = -b (both of the next l), c2 = r
                     const double nx = __builtin_fma(c2, P0[r], P1[r]);
                     P1[r] = __builtin_fma(c0, P1[r], (c1 * x[r]) * nx);
                     P0[r] = nx;
@@ -158,6 +152,13 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             }
         };
         fetch(lo);
+        // start values in the scaled variables wait in LDS until their chain joins
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int i = sid[r] >= kDead ? 0 : sid[r];
+            *reinterpret_cast<double2 *>(room + 2 * (r * 64 + lane)) =
+                make_double2(s0[r] * cf[2 * i].w, POLE ? s1[r] : s1[r] * cf[2 * i + 2].w);
+        }
         stage(0, lo);
         fetch(lo + kChunk);
         int sl = 0;
@@ -294,24 +295,13 @@ __global__ __launch_bounds__(64) void k_legendre_dd(LegArgs a) {
     legendre_dd_wave<NB>(a, blockIdx.x / a.dd_groups, blockIdx.x % a.dd_groups);
 }
 
-// Order of the work of one XCD (workgroups are dealt to the 8 XCDs round
-// robin): eight consecutive orders of each 64, all their blocks, so that the
-// XCD's L2 serves an order's coefficient and a_lm stream to all its blocks
-// and gathers the 16 NB-byte stores of neighbouring orders of a ring into
-// whole lines.  Every other 64 orders are dealt in reverse, which evens out
-// the chain lengths.  Low orders (the longest chains) come first.
-__device__ __forceinline__ int leg_order(int xcd, int s) {
-    const int j = s >> 3;
-    return 64 * j + 8 * (j & 1 ? 7 - xcd : xcd) + (s & 7);
-}
-
-// One launch covers every (m, ring block).
+// One launch covers every (m, ring block), in the order of xcd_order().
 template <int NB, int R>
 __global__ __launch_bounds__(128, (R == 4 ? 4 : 1)) void k_legendre(LegArgs a) {
     __shared__ __attribute__((aligned(16))) double lds[2 * leg_wave_lds<NB, R>()];
     const int nrb = a.pole_blocks + a.plain_blocks;
     const int slot = blockIdx.x >> 3, s = slot / nrb;
-    const int m = leg_order(blockIdx.x & 7, s);
+    const int m = xcd_order(blockIdx.x & 7, s);
     if (m > a.L) return;
     // an XCD deals its workgroups to its shader engines round robin: the
     // first block of each order moves on by one, so that no engine gets the
@@ -323,15 +313,15 @@ __global__ __launch_bounds__(128, (R == 4 ? 4 : 1)) void k_legendre(LegArgs a) {
 // of wavefronts at one ring per lane.  More rings per lane share a step's
 // operand reads, but cut the number of wavefronts and run a lane's rings from
 // the earliest of their chains.  Measured at 1, 2 and 4 rings, four maps:
-// L = 255 (2048 wavefronts) 12.2, 15.2, 23.6 us; L = 511 (8192) 42, 47, 62 us;
-// L = 767 (18432) 109, 98, 123 us; L = 1023 (32768) 225, 195, 224 us; L = 2047
-// (131072) -, 1404, 1361 us.  Above four maps the state of four rings does
-// not fit the registers.
+// L = 255 (2048 wavefronts) 12.0, 14.6, 22.4 us; L = 511 (8192) 41, 39, 69 us;
+// L = 767 (18432) 106, 97, 122 us; L = 1023 (32768) 223, 193, 220 us; L = 2047
+// (131072) -, 1329, 1352 us; one map: L = 1023 140, 115, 122 us, L = 2047 -, 797,
+// 733 us.  Above two maps the state of four rings leaves too few wavefronts.
 static int leg_rings(const sht_plan_s *p, int nb) {
     int R = p->opts.rings_per_lane;
     if (R != 1 && R != 2 && R != 4) {
         const long long waves = 2LL * (p->L + 1) * (p->n_north_pad / kLanes);
-        R = waves >= 65536 ? 4 : waves >= 12288 ? 2 : 1;
+        R = waves >= 65536 && nb <= 2 ? 4 : waves >= 8192 ? 2 : 1;
     }
     return nb > 4 ? std::min(R, 2) : R;
 }
@@ -543,52 +533,11 @@ hipError_t launch_legendre(const sht_plan_s *p, int nmaps, const double *alm, do
 
 // ---- tables of the scaled and the split recurrence, made once per plan ------
 // With D = ((l+1)^2 - m^2)((l+2)^2 - m^2) and Q_l = sqrt((2l+5) / ((2l+1) D)):
-//   beta_l = (2l+3)(2l+1) Q_l,  r_l = (l+1+m)(l+2+m) Q_l,
+//   beta_l = 1 / c_l = (2l+3)(2l+1) Q_l,  r_l = (l+1+m)(l+2+m) Q_l,
 //   h_l = (l-m)(l-1-m) (2l+3)/(2l-1) Q_l.
-// Entry e = l - m of order m (at the plan's coefficient offsets) holds
-// {h_l, -beta_l, r_{l-2}, 0}; entries 0 and 1 are not used.
 __device__ __forceinline__ dd pole_Q(double l, double m) {
     const dd D = dd_mul({(l + 1 - m) * (l + 1 + m), 0.0}, {(l + 2 - m) * (l + 2 + m), 0.0});
     return dd_sqrt(dd_div({2 * l + 5, 0.0}, dd_mul({2 * l + 1, 0.0}, D)));
-}
-
-__global__ __launch_bounds__(256) void k_pole_coef(const long long *__restrict__ coef_off, double4 *__restrict__ out) {
-    const int m = blockIdx.x;
-    const long long base = coef_off[m], cnt = coef_off[m + 1] - base;
-    for (long long e = threadIdx.x; e < cnt; e += 256) {
-        double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
-        if (e >= 2) {
-            const double l = (double)(m + e), mm = m;
-            const dd Q = pole_Q(l, mm);
-            v.x = dd_mul(dd_div(dd_mul({(l - mm) * (l - 1 - mm), 0.0}, {2 * l + 3, 0.0}), {2 * l - 1, 0.0}), Q).h;
-            v.y = -dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, Q).h;
-            v.z = dd_mul({(l - 1 + mm) * (l + mm), 0.0}, pole_Q(l - 2, mm)).h;
-        }
-        out[base + e] = v;
-    }
-}
-
-// d = P~_{l+2} - r_l P~_l at each chain's start, l = m + t + 2 start_idx, from
-// the stored start values (with their low parts on the first n_dd_pad rings;
-// farther from the pole d no longer cancels).
-__global__ __launch_bounds__(256) void k_pole_start(LegArgs a, double *__restrict__ out) {
-    const int row = blockIdx.x, m = row >> 1, t = row & 1;
-    for (int k = threadIdx.x; k < a.n_pole_pad; k += 256) {
-        const int i = a.start_idx[(size_t)row * a.np + k];
-        double d = 0.0;
-        if (i < kDead) {
-            const size_t r2 = (size_t)row * 2;
-            dd p0 = {a.start_val[r2 * a.np + k], 0.0}, p1 = {a.start_val[(r2 + 1) * a.np + k], 0.0};
-            if (k < a.n_dd_pad) {
-                p0.l = a.start_lo[r2 * a.n_dd_pad + k];
-                p1.l = a.start_lo[(r2 + 1) * a.n_dd_pad + k];
-            }
-            const double l = m + t + 2.0 * i;
-            const dd r = dd_mul({(l + 1 + m) * (l + 2 + m), 0.0}, pole_Q(l, m));
-            d = dd_sub(p1, dd_mul(r, p0)).h;
-        }
-        out[(size_t)row * a.n_pole_pad + k] = d;
-    }
 }
 
 // Scaled recurrence: entry e = l - m of order m holds {b_l, -b_l d_l, f_l,
@@ -620,9 +569,54 @@ hipError_t fill_scaled_coef(const sht_plan_s *p) {
     return e != hipSuccess ? e : hipStreamSynchronize(nullptr);
 }
 
+// Split recurrence in the scaled variables (P~_l = f_l mu_l, d_l of the pair
+// (l, l+2) scaled like P~_{l+2}): entry e holds {h_l f_l / f_{l+2},
+// -beta_l f_l / f_{l+2}, r_{l-2} f_{l-2} / f_l, 0}; entries 0 and 1 are not used.
+__global__ __launch_bounds__(256) void k_pole_coef(const long long *__restrict__ coef_off,
+                                                   const double4 *__restrict__ sc, double4 *__restrict__ out) {
+    const int m = blockIdx.x;
+    const long long base = coef_off[m], cnt = coef_off[m + 1] - base;
+    for (long long e = threadIdx.x; e < cnt; e += 256) {
+        double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
+        if (e >= 2 && e + 2 < cnt) {
+            const double l = (double)(m + e), mm = m;
+            const dd Qf = dd_mul(pole_Q(l, mm), dd_div({sc[base + e].z, 0.0}, {sc[base + e + 2].z, 0.0}));
+            v.x = dd_mul(dd_div(dd_mul({(l - mm) * (l - 1 - mm), 0.0}, {2 * l + 3, 0.0}), {2 * l - 1, 0.0}), Qf).h;
+            v.y = -dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, Qf).h;
+            v.z = dd_mul(dd_mul({(l - 1 + mm) * (l + mm), 0.0}, pole_Q(l - 2, mm)),
+                         dd_div({sc[base + e - 2].z, 0.0}, {sc[base + e].z, 0.0})).h;
+        }
+        out[base + e] = v;
+    }
+}
+
+// (P~_{l+2} - r_l P~_l) / f_{l+2} at each chain's start, l = m + t + 2 start_idx,
+// from the stored start values (with their low parts on the first n_dd_pad
+// rings; farther from the pole the difference no longer cancels).
+__global__ __launch_bounds__(256) void k_pole_start(LegArgs a, double *__restrict__ out) {
+    const int row = blockIdx.x, m = row >> 1, t = row & 1;
+    const double4 *sc = reinterpret_cast<const double4 *>(a.coef_sc) + a.coef_off[m] + t;
+    for (int k = threadIdx.x; k < a.n_pole_pad; k += 256) {
+        const int i = a.start_idx[(size_t)row * a.np + k];
+        double d = 0.0;
+        if (i < kDead) {
+            const size_t r2 = (size_t)row * 2;
+            dd p0 = {a.start_val[r2 * a.np + k], 0.0}, p1 = {a.start_val[(r2 + 1) * a.np + k], 0.0};
+            if (k < a.n_dd_pad) {
+                p0.l = a.start_lo[r2 * a.n_dd_pad + k];
+                p1.l = a.start_lo[(r2 + 1) * a.n_dd_pad + k];
+            }
+            const double l = m + t + 2.0 * i;
+            const dd r = dd_mul({(l + 1 + m) * (l + 2 + m), 0.0}, pole_Q(l, m));
+            d = dd_div(dd_sub(p1, dd_mul(r, p0)), {sc[2 * i + 2].z, 0.0}).h;
+        }
+        out[(size_t)row * a.n_pole_pad + k] = d;
+    }
+}
+
 hipError_t fill_pole_tables(const sht_plan_s *p) {
     hipLaunchKernelGGL(k_pole_coef, dim3((unsigned)(p->L + 1)), dim3(256), 0, nullptr, p->d_coef_off,
-                       reinterpret_cast<double4 *>(p->d_coef_pole));
+                       reinterpret_cast<const double4 *>(p->d_coef_sc), reinterpret_cast<double4 *>(p->d_coef_pole));
     const LegArgs a = leg_args(p, 1, 0, 1, nullptr, nullptr);
     hipLaunchKernelGGL(k_pole_start, dim3((unsigned)(2 * (p->L + 1))), dim3(256), 0, nullptr, a, p->d_start_d);
     hipError_t e = hipGetLastError();

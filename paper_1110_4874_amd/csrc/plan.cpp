@@ -559,10 +559,15 @@ int upload_tables(sht_plan_s *p) {
     auto group_sin = [&](int g) { return sqrt(s2[std::min((g + 1) * kLanes, p->n_north) - 1]); };
     if (p->opts.dd_sin < 0 && p->n_dd_groups > 0 && group_sin(p->n_dd_groups - 1) <= kPoleSinMax) {
         int g = p->n_dd_groups;
-        while (g < p->n_north_pad / kLanes && group_sin(g) <= kPoleSin) g++;
+        const int ng = p->n_north_pad / kLanes;
+        while (g < ng && group_sin(g) <= kPoleSin) g++;
+        // an even number where it can be: waves of two groups are whole
+        if (g % 2 && g < ng && group_sin(g) <= kPoleSinMax) g++;
         p->pole_groups = g;
     }
-    UP(d_coef_lo, coef_lo);
+    if (p->ip.built || (p->n_dd_groups > 0 && p->pole_groups == 0)) {
+        UP(d_coef_lo, coef_lo);
+    }
     {
         const size_t nc = p->coef_hi.size() * sizeof(double);
         if (e == hipSuccess) e = hipMalloc((void **)&p->d_coef_sc, nc);

@@ -50,3 +50,29 @@ def test_polar_groups(gpu, L, N, R):
         err_dd = _err(dd, alm, rings)
         print(f"L={L} N={N} B={B}: {err:.2e}, double-double {err_dd:.2e}")
         assert err <= TOL and err_dd <= TOL, (B, err, err_dd)
+
+
+# the adjoint's waves: one and two ring groups a wave, passes of 1 to 8 maps,
+# polar groups (even and odd numbers), more groups than one launch covers
+@pytest.mark.parametrize("L,N", [(7, 4), (33, 33), (127, 64), (250, 130), (300, 150), (700, 400)])
+@pytest.mark.parametrize("R", [0, 1, 2])
+def test_adjoint_rings_per_wave_and_maps(gpu, L, N, R):
+    p = gpu.Plan(L, N, rings_per_lane=R)
+    y = np.random.default_rng(L + N).standard_normal((11, 12 * N * N))
+    ref = oracle.adjoint(L, N, y)
+    for B in (1, 2, 3, 4, 5, 6, 8, 11) if L < 700 else (1, 3, 11):
+        g = p.adjoint(torch.from_numpy(y[:B]).cuda()).cpu().numpy()
+        err = np.max(np.abs(g - ref[:, :B])) / np.max(np.abs(ref))
+        assert err <= TOL, (L, N, R, B, err)
+
+
+def test_adjoint_over_several_launches(gpu):
+    # 20 and 36 ring groups, one a wave: 16 groups per launch, added in place
+    for L, N, R in ((60, 640, 1), (40, 1152, 2)):
+        y = np.random.default_rng(N).standard_normal((3, 12 * N * N))
+        ref = oracle.adjoint(L, N, y)
+        for dd in (None, 0.05):  # 0.05: the first groups in double-double
+            p = gpu.Plan(L, N, rings_per_lane=R, dd_sin=dd)
+            g = p.adjoint(torch.from_numpy(y).cuda()).cpu().numpy()
+            err = np.max(np.abs(g - ref)) / np.max(np.abs(ref))
+            assert err <= TOL, (L, N, dd, err)
