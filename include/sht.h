@@ -108,8 +108,9 @@ typedef struct sht_plan_opts {
     int rings_per_lane;/* rings each lane of the FP64 Legendre kernel owns:
                           1, 2 or 4 (0 = chosen by the transform's size); a
                           tuning knob */
-    int ring_threads;  /* workgroup size of the ring FFT kernel: 256, 512 or
-                          1024 (0 = default 512); a tuning knob */
+    int ring_threads;  /* 0, 256, 512 or 1024: kept for programs that set it; the
+                          ring FFT sizes its thread groups by the ring (64 to
+                          256 threads) */
     int host_only;     /* 1: build host tables only (no device memory); such a
                           plan can be inspected but not executed */
     /* Butterfly compression (eps > 0 plans only; Sec. 3.2 and 3.4): */
@@ -389,8 +390,8 @@ typedef struct sht_batch_opts {
     size_t workspace_bytes;
     int rings_per_lane;       /* work-queue batches: rings per lane of the Legendre
                                  waves, 1, 2 or 4 (0 = 2); a tuning knob */
-    int ring_threads;         /* work-queue batches: ring FFT workgroup size, 256,
-                                 512 or 1024 (0 = 512); a tuning knob */
+    int ring_threads;         /* work-queue batches: 0, 256, 512 or 1024, checked
+                                 but without effect (as in sht_plan_opts) */
 } sht_batch_opts;
 
 void sht_batch_opts_default(sht_batch_opts *o);

@@ -115,11 +115,34 @@ struct InterpPlan {
     double build_seconds = 0.0;
 };
 
+// Passes of the ring FFT of size 2^lg: r1 (outermost), r2 and r3 (innermost)
+// radix-2 stages in registers.  Up to 16 points a thread; 512 runs as three
+// passes of 8 so that all 64 threads have work.
+struct RingShape {
+    int r1, r2, r3;
+};
+__host__ __device__ constexpr RingShape ring_shape(int lg) {
+    return lg <= 4   ? RingShape{0, 0, lg}
+           : lg == 5 ? RingShape{2, 0, 3}
+           : lg == 6 ? RingShape{3, 0, 3}
+           : lg == 7 ? RingShape{3, 0, 4}
+           : lg == 8 ? RingShape{4, 0, 4}
+           : lg == 9 ? RingShape{3, 3, 3}
+                     : RingShape{4, lg - 8, 4};
+}
+
+// Rings of one ring-kernel launch: those whose transform takes `threads`
+// threads (64 up to 1024 points, 128 for 2048, 256 for 4096).
+struct RingSet {
+    int threads = 64, max_size = 0;
+    std::vector<int> rings;
+    int *d_rings = nullptr;
+};
+
 struct RingClass {
     int lds_entries;              // complex entries of the FFT buffer (before padding)
     bool wrap = false;            // some ring has J/2 <= L (q staged through LDS)
     std::vector<int> rings;       // ring indices (host)
-    int *d_rings = nullptr;       // device copy
 };
 
 }  // namespace sht
@@ -154,7 +177,8 @@ struct sht_plan_s {
     std::vector<double> bs_table;              // chirp spectra, bit-reversed, scaled by 1/M
     std::vector<double> chirp;                 // exp(+i pi k^2 / n), k < n, per distinct Bluestein n
     std::vector<long long> ring_chirp_off;     // [nrings] offset (complex entries) into chirp
-    std::vector<sht::RingClass> classes;
+    std::vector<sht::RingClass> classes;      // in plan files; the kernels use ring_sets
+    sht::RingSet ring_sets[3];                 // made at upload, longest transforms first
 
     // polarized synthesis near the poles: north rings [0, pol_n) (and their
     // mirrors) whose sin(theta) is below the threshold where the reduction
@@ -258,9 +282,7 @@ struct RingArgs {
     double *__restrict__ map;
     int L, nrings, nmaps;
     long long npix;
-    int fft_entries;  // padded FFT buffer entries of this launch's class
-    int stage;        // LDS entries past the FFT buffer (wrapped rings' reduction room)
-    int mpw;          // maps of one ring per workgroup (1, 2 or 4; divides nmaps)
+    int fft_entries;  // LDS entries of a thread group
     // adjoint direction: pixel values in, weighted phases ybar out
     const double *__restrict__ map_in;
     double2 *__restrict__ ybar;
@@ -354,8 +376,7 @@ hipError_t launch_legendre_queue(int shape, const LegArgs *passes, const int4 *i
                                  const unsigned *list_off, unsigned *counter, int rings_per_lane, int grid,
                                  hipStream_t st);
 RingArgs ring_args(const sht_plan_s *p, int nmaps, const double *q, double *map);
-size_t ring_class_shape(int lds_entries, bool wrap, int T, int *fft_entries, int *stage);
-int ring_maps_per_wg(int lds_entries, int nmaps);
+int ring_group_entries(int S, int T);  // LDS entries of a group of T threads, transforms up to S
 hipError_t launch_ring_queue(int T, const RingArgs *args, const int2 *items, long long nitems, size_t lds,
                              hipStream_t st);
 hipError_t ring_queue_prepare(int T);

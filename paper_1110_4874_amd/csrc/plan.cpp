@@ -535,7 +535,6 @@ int upload_tables(sht_plan_s *p) {
     UP(d_grp_lo, grp_lo);
     UP(d_grp_hi, grp_hi);
     UP(d_tw, tw);
-    UP(d_bs_table, bs_table);
     UP(d_chirp, chirp);
     UP(d_ring_chirp_off, ring_chirp_off);
     UP(d_pol_ring, pol_ring);
@@ -584,8 +583,31 @@ int upload_tables(sht_plan_s *p) {
         b += nc + ns;
     }
 #undef UP
-    for (auto &rc : p->classes)
-        if (e == hipSuccess) e = up(&rc.d_rings, rc.rings, &b);
+    // ring launches, longest transforms first, and the chirp spectra in the
+    // order the innermost FFT pass reads them: [element][group]
+    std::vector<double> bs(p->bs_table.size());
+    std::vector<std::pair<int, int>> by_size;
+    for (int r = 0; r < p->nrings; r++) by_size.push_back({-(p->ring_M[r] ? p->ring_M[r] : p->ring_J[r] / 2), r});
+    std::stable_sort(by_size.begin(), by_size.end());
+    for (int c = 0; c < 3; c++) {
+        p->ring_sets[c] = RingSet();
+        p->ring_sets[c].threads = 256 >> c;
+    }
+    for (const auto &[neg, r] : by_size) {
+        const int S = -neg, lg = ilog2(S), r3 = ring_shape(lg).r3, ng = S >> r3;
+        RingSet &rs = p->ring_sets[S > 2048 ? 0 : S > 1024 ? 1 : 2];
+        rs.max_size = std::max(rs.max_size, S);
+        rs.rings.push_back(r);
+        if (!p->ring_M[r]) continue;
+        const double *src = p->bs_table.data() + 2 * p->ring_bs_off[r];
+        double *dst = bs.data() + 2 * p->ring_bs_off[r];
+        for (int g = 0; g < ng; g++)
+            for (int k = 0; k < (1 << r3); k++)
+                for (int q = 0; q < 2; q++) dst[2 * (k * ng + g) + q] = src[2 * ((g << r3) + k) + q];
+    }
+    if (e == hipSuccess) e = up(&p->d_bs_table, bs, &b);
+    for (auto &rs : p->ring_sets)
+        if (e == hipSuccess) e = up(&rs.d_rings, rs.rings, &b);
     if (p->ip.built) {
         InterpPlan &f = p->ip;
 #define UPI(d, h) \
@@ -663,8 +685,8 @@ void free_device_tables(sht_plan_s *p) {
                     p->d_ip_patch};
     for (void *q : ptrs)
         if (q) (void)hipFree(q);
-    for (auto &rc : p->classes)
-        if (rc.d_rings) (void)hipFree(rc.d_rings), rc.d_rings = nullptr;
+    for (auto &rs : p->ring_sets)
+        if (rs.d_rings) (void)hipFree(rs.d_rings), rs.d_rings = nullptr;
 
     p->d_z2_hi = p->d_z2_lo = p->d_s2 = p->d_coef_sc = p->d_coef_pole = p->d_start_d = nullptr;
     p->pole_groups = 0;

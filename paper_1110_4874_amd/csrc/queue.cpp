@@ -36,8 +36,7 @@ namespace {
 constexpr double kDdCost = 4.0;  // double-double step relative to an FP64 step
 
 struct RingGroup {
-    int lds_entries = 0;
-    bool wrap = false;
+    int threads = 0;
     size_t lds = 0;
     RingArgs *d_args = nullptr;
     int2 *d_items = nullptr;
@@ -69,7 +68,7 @@ struct sht_batch_s {
     int n = 0;
     int path = SHT_PATH_BRUTE, fp32 = 0;
     std::vector<BfGroup> bf;
-    int rings_per_lane = 2, ring_threads = 512;
+    int rings_per_lane = 2;
     std::vector<sht_request> reqs;
     LegArgs *d_passes = nullptr;
     int4 *d_items = nullptr;
@@ -398,34 +397,36 @@ int build_brute(sht_batch_s *b, const sht_batch_opts *o) {
 }
 
 int build_rings(sht_batch_s *b, const sht_batch_opts *o) {
-    // ring groups: one per (class size, wrap) over every request
-    const int T = b->ring_threads;
+    // ring groups: one per ring size class over every request
     size_t off = 0;
     for (int r = 0; r < b->n; r++) {
         const sht_request &q = b->reqs[r];
         const sht_plan_s *p = q.plan;
         const double *qbuf = reinterpret_cast<const double *>((char *)o->workspace + off);
         off += req_ws_bytes(q, b->path, b->fp32);
-        for (const auto &rc : p->classes) {
+        for (const auto &rs : p->ring_sets) {
+            if (rs.rings.empty()) continue;
             RingGroup *g = nullptr;
             for (auto &x : b->groups)
-                if (x.lds_entries == rc.lds_entries && x.wrap == rc.wrap) g = &x;
+                if (x.threads == rs.threads) g = &x;
             if (!g) {
                 b->groups.emplace_back();
                 g = &b->groups.back();
-                g->lds_entries = rc.lds_entries;
-                g->wrap = rc.wrap;
+                g->threads = rs.threads;
             }
             RingArgs a = ring_args(p, q.nmaps, qbuf, q.map);
-            a.rings = rc.d_rings;
-            a.count = (int)rc.rings.size();
-            g->lds = ring_class_shape(rc.lds_entries, rc.wrap, T, &a.fft_entries, &a.stage);
+            a.rings = rs.d_rings;
+            a.count = (int)rs.rings.size();
+            a.fft_entries = ring_group_entries(rs.max_size, rs.threads);
+            g->lds = std::max(g->lds, (size_t)a.fft_entries * 2 * sizeof(double));
             const int ai = (int)g->args.size();
             g->args.push_back(a);
             for (int it = 0; it < a.count * q.nmaps; it++) g->items.push_back(make_int2(ai, it));
         }
     }
-    hipError_t e = ring_queue_prepare(b->ring_threads);
+    hipError_t e = hipSuccess;
+    for (auto &g : b->groups)
+        if (e == hipSuccess) e = ring_queue_prepare(g.threads);
     for (auto &g : b->groups) {
         g.nitems = (long long)g.items.size();
         if (g.nitems > 0x7fffffffLL && e == hipSuccess) e = hipErrorInvalidValue;
@@ -499,7 +500,6 @@ sht_batch_t *sht_batch_create(const sht_request *reqs, int n, const sht_batch_op
     b->n = n;
     b->reqs.assign(reqs, reqs + n);
     b->rings_per_lane = o->rings_per_lane ? o->rings_per_lane : 2;
-    b->ring_threads = o->ring_threads ? o->ring_threads : 512;
     b->path = o->path;
     b->fp32 = o->path == SHT_PATH_BUTTERFLY && o->precision == SHT_PREC_FP32;
     try {
@@ -577,7 +577,7 @@ int sht_batch_run(const sht_batch_t *b, void *stream) {
     for (size_t gi = 0; gi < b->groups.size(); gi++) {
         if (e != hipSuccess) break;
         const auto &g = b->groups[gi];
-        e = launch_ring_queue(b->ring_threads, g.d_args, g.d_items, g.nitems, g.lds, b->st[gi % kMaxStreams]);
+        e = launch_ring_queue(g.threads, g.d_args, g.d_items, g.nitems, g.lds, b->st[gi % kMaxStreams]);
     }
     join(1, kr);
     if (e != hipSuccess) return fail(SHT_EDEVICE, std::string("batch launch: ") + hipGetErrorString(e));

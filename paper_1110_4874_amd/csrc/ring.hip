@@ -1,4 +1,5 @@
-// Ring stage of synthesis (Wavemoth paper, Sec. 2.3 Eqs. 8-11), for gfx950.
+// Ring stage of synthesis (Wavemoth paper, Sec. 2.3 Eqs. 8-11) and of its
+// adjoint, for gfx950.
 //
 // For ring k with J pixels at phi_j = pi (2j + s) / J:
 //   f_j = sum_{m=-L}^{L} q_m e^{i m phi_j},   q_{-m} = conj(q_m)
@@ -8,33 +9,31 @@
 // complex DFT of half length n = J/2 (even and odd pixels in the real and
 // imaginary parts) after the usual pre-twiddle.
 //
-// One workgroup handles one (ring, map).  Bin b collects the m of its two
-// residue classes m = b + jJ and m = jJ - b; all of them share the phase
-// e^{i pi b s/J} up to the sign (-1)^{js}, so each bin needs one sincospi.
-// Rings with J/2 > L (no wrap) load their q values straight into registers,
-// all loads in flight at once; so do rings with J > L, whose bins collect
-// at most two orders.  Shorter rings sum the orders of each bin straight
-// from q as well, several threads per bin when the ring has fewer bins than
-// the workgroup has threads, and reduce those partial sums through LDS in a
-// fixed order (deterministic, no atomics).  The
-// half-length DFT runs in LDS with in-place radix-8 passes (radix-4/2 for the
-// remainder): decimation in time on bit-reversed input when n is a power of
-// two.  Otherwise n = 2h (J is a multiple of 4) and the DFT is split into its
-// even- and odd-index halves, two length-h DFTs run one after the other in
-// the same buffer by Bluestein's chirp convolution with a power-of-two
-// M >= 2h-1 (forward decimation in frequency, pointwise product with the
-// plan's chirp spectrum, backward decimation in time), the first result
-// waiting in registers; z_p = A_p + w^p B_p, z_{p+h} = A_p - w^p B_p with
-// w = e^{2 pi i/n}.  This halves the LDS of the longest polar rings.  The
-// zero padding of each convolution input is implied (the first forward pass
-// reads the entries past h as zeros), so it is never stored.  LDS indices
-// are padded by one entry per 16 to spread strided accesses over the banks.
-// Global loads (q columns, chirps, chirp spectra, pixels) are issued in
-// batches before their first use, so that a thread waits for memory once per
-// batch rather than once per value.  One workgroup
-// owns one (ring, map); the maps of a ring are adjacent in the ring-major q
-// layout and their workgroups run back to back on the same XCD (dispatch is
-// round-robin over 8 XCDs), so lines read from HBM serve them all from L2.
+// Bin b collects the m of its two residue classes m = b + jJ and m = jJ - b;
+// all of them share the phase e^{i pi b s/J} up to the sign (-1)^{js}.  Rings
+// with J > L have at most two orders per bin; shorter rings sum theirs
+// straight from q, several threads per bin when the ring has fewer bins than
+// threads, reduced through LDS in a fixed order (deterministic, no atomics).
+//
+// The half-length DFT of size S = 2^lg (S = n for a power of two) keeps 16
+// points a thread in registers: a thread group of max(64, S / 16) threads, so
+// up to S = 1024 one wavefront, which needs no barrier.  Two or three
+// passes of up to four radix-2 stages each (RingShape) go through LDS between
+// them; the first reads its input in bit-reversed order, the last stores its
+// results straight to the map.  Other n are 2h (J is a multiple of 4): the
+// even and the odd half, two length-h DFTs one after the other, by Bluestein's
+// chirp convolution of size S >= 2h-1: forward decimation in frequency, whose
+// last pass meets the pointwise product with the plan's chirp spectrum and
+// the first pass of the backward decimation in time in registers.  The first
+// pass has zeros in its upper half and the last needs only its lower half, so
+// each half costs four LDS exchanges; both halves' results stay in the
+// registers of the thread that combines them, z_p = A_p + w^p B_p, z_{p+h} =
+// A_p - w^p B_p with w = e^{2 pi i/n}.  LDS indices are padded by one entry
+// per 16.  Global loads are issued in batches before their first use.
+// The maps of a ring are adjacent in the ring-major q layout; up to S = 1024
+// they share a workgroup (a wavefront each), and else run back to back on
+// one XCD (dispatch is round-robin over 8 XCDs), so lines read from HBM serve
+// them all from L2.
 #include <mutex>
 #include <set>
 #include <utility>
@@ -45,18 +44,11 @@
 
 namespace sht {
 
-constexpr int kMaxPairs = 2049;     // Hermitian bin pairs of the largest ring (n = 4096)
-constexpr int kMaxHalf = 2048;      // half length h of the largest Bluestein ring (n = 2h <= 4096)
-
+// Complex product with a fixed rounding pattern (explicit fused multiply-adds):
+// whichever way the compiler would contract the plain expression, the kernels
+// of one plan (several maps per workgroup, one, or the batch queue) agree bit
+// for bit.
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
-    return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-// Complex product with a fixed rounding pattern (explicit fused multiply-adds)
-// for the chirp products, whose loops take different shapes in different
-// kernels (batched loads or one at a time): whichever way the compiler would
-// contract the plain expression there, the ring kernels of one plan (one map
-// per workgroup, several, or the batch queue) agree bit for bit.
-__device__ __forceinline__ double2 cmul_fixed(double2 a, double2 b) {
     return make_double2(__builtin_fma(a.x, b.x, -(a.y * b.y)), __builtin_fma(a.x, b.y, a.y * b.x));
 }
 __device__ __forceinline__ double2 cconj(double2 a) { return make_double2(a.x, -a.y); }
@@ -72,173 +64,313 @@ __device__ __forceinline__ double2 i_conj(double2 y) { return make_double2(y.y, 
 __device__ __forceinline__ int ilog2_dev(int n) { return 31 - __clz(n); }
 __device__ __forceinline__ int bitrev(int k, int lg) { return lg == 0 ? 0 : (int)(__brev((unsigned)k) >> (32 - lg)); }
 __device__ __forceinline__ int pidx(int i) { return i + (i >> 4); }
+// v where on, else 0, without a branch around the load that made v
+__device__ __forceinline__ double2 keep(double2 v, bool on) {
+    const long long mask = on ? -1LL : 0LL;
+    return make_double2(__builtin_bit_cast(double, __builtin_bit_cast(long long, v.x) & mask),
+                        __builtin_bit_cast(double, __builtin_bit_cast(long long, v.y) & mask));
+}
 
 // Workgroup -> work item, grouping 8 consecutive items on one XCD.
 __device__ __forceinline__ int xcd_item(int wg) { return (wg & ~63) + ((wg & 7) << 3) + ((wg >> 3) & 7); }
 
-// x * e^{2 pi i j / 8} for j = 0..7 (exact constants)
-__device__ __forceinline__ double2 rot8(double2 x, int j) {
-    const double r = 0.70710678118654752440;
-    switch (j & 7) {
+// Orders LDS accesses between the threads of a group of T: a wavefront's LDS
+// operations complete in order, more need the workgroup's barrier.
+template <int T>
+__device__ __forceinline__ void group_sync() {
+    if constexpr (T > 64) {
+        __syncthreads();
+    } else {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// x * e^{2 pi i j / 16} (exact constants)
+__device__ __forceinline__ double2 rot16(double2 x, int j) {
+    const double r = 0.70710678118654752440, c = 0.92387953251128675613, s = 0.38268343236508977173;
+    switch (j & 15) {
         case 0: return x;
-        case 1: return make_double2(r * (x.x - x.y), r * (x.x + x.y));
-        case 2: return make_double2(-x.y, x.x);
-        case 3: return make_double2(-r * (x.x + x.y), r * (x.x - x.y));
-        case 4: return make_double2(-x.x, -x.y);
-        case 5: return make_double2(r * (x.y - x.x), -r * (x.x + x.y));
-        case 6: return make_double2(x.y, -x.x);
-        default: return make_double2(r * (x.x + x.y), r * (x.y - x.x));
+        case 1: return cmul(x, make_double2(c, s));
+        case 2: return make_double2(r * (x.x - x.y), r * (x.x + x.y));
+        case 3: return cmul(x, make_double2(s, c));
+        case 4: return make_double2(-x.y, x.x);
+        case 5: return cmul(x, make_double2(-s, c));
+        case 6: return make_double2(-r * (x.x + x.y), r * (x.x - x.y));
+        case 7: return cmul(x, make_double2(-c, s));
+        case 8: return make_double2(-x.x, -x.y);
+        case 9: return cmul(x, make_double2(-c, -s));
+        case 10: return make_double2(r * (x.y - x.x), -r * (x.x + x.y));
+        case 11: return cmul(x, make_double2(-s, -c));
+        case 12: return make_double2(x.y, -x.x);
+        case 13: return cmul(x, make_double2(s, -c));
+        case 14: return make_double2(r * (x.x + x.y), r * (x.y - x.x));
+        default: return cmul(x, make_double2(c, -s));
     }
 }
 
-// One in-place pass of 2^r radix-2 stages s .. s+r-1 (h = 2^(s-1)).
-// Decimation in time, sign +1 (backward): within each group of R = 2^r
-// elements base + k h, sub-stage u combines k and k + 2^u with the twiddle
-// e^{+2 pi i (pos + j h) / (2^(u+1) h)}, j = k mod 2^u.
-template <int r>
-__device__ __forceinline__ void dit_pass(double2 *a, int lg, int s, const double2 *__restrict__ tw,
-                                         int tw_log, int tid, int nt) {
-    constexpr int R = 1 << r;
-    const int n = 1 << lg, h = 1 << (s - 1);
-#pragma unroll 1
-    for (int gi = tid; gi < n / R; gi += nt) {
-        const int pos = gi & (h - 1);
-        const int base = (gi >> (s - 1)) * (R * h) + pos;
-        double2 x[R];
+// x[k] *= w^{bitrev(k)} (CONJ: its conjugate), k < 2^r, from w by products of
+// at most five factors.  The empty asm keeps the compiler from computing the
+// powers once and holding them across passes (60 registers).
+template <int r, bool CONJ>
+__device__ __forceinline__ void twiddle(double2 (&x)[1 << r], double2 w) {
+    asm volatile("" : "+v"(w.x), "+v"(w.y));
+    if (CONJ) w = cconj(w);
+    double2 lo[4], hi = make_double2(1.0, 0.0), w4 = hi;
+    lo[1] = w;
+    if (r > 1) {
+        lo[2] = cmul(w, w);
+        lo[3] = cmul(lo[2], w);
+        if (r > 2) w4 = cmul(lo[2], lo[2]);
+    }
 #pragma unroll
-        for (int k = 0; k < R; k++) x[k] = a[pidx(base + k * h)];
-        double2 wp[r];                             // wp[u] = e^{2 pi i pos / (2^(u+1) h)}
-        wp[r - 1] = tw[pos << (tw_log - (s - 1) - r)];
+    for (int e = 1; e < (1 << r); e++) {
+        if ((e & 3) == 0) hi = e == 4 ? w4 : e == 8 ? cmul(w4, w4) : cmul(hi, w4);
+        const double2 f = e < 4 ? lo[e] : (e & 3) ? cmul(hi, lo[e & 3]) : hi;
+        int k = 0;
 #pragma unroll
-        for (int u = r - 2; u >= 0; u--) wp[u] = cmul(wp[u + 1], wp[u + 1]);
+        for (int b = 0; b < r; b++) k |= (e >> b & 1) << (r - 1 - b);
+        x[k] = cmul(x[k], f);
+    }
+}
+
+// r radix-2 stages on R = 2^r elements base + k h, h = 2^(s-1), pos = base mod h.
+// Decimation in time, sign +1 (backward): sub-stage u combines k and k + 2^u
+// with the twiddle e^{+2 pi i (pos + j h) / (2^(u+1) h)}, j = k mod 2^u.  The
+// parts of pos gather on the inputs as wt^{bitrev(k)}, wt = e^{2 pi i pos / (R h)}
+// (TRIV: h = 1, wt = 1), which leaves constants between the sub-stages.
+// HALF: only the lower half of the results is wanted.
+template <int r, bool TRIV, bool HALF>
+__device__ __forceinline__ void dit_regs(double2 (&x)[1 << r], double2 wt) {
+    if constexpr (!TRIV) twiddle<r, false>(x, wt);
 #pragma unroll
-        for (int u = 0; u < r; u++) {
-            const int span = 1 << u;
+    for (int u = 0; u < r; u++) {
+        const int span = 1 << u;
 #pragma unroll
-            for (int k = 0; k < R; k++) {
-                if (k & span) continue;
-                const int j = k & (span - 1);
-                const double2 w = rot8(wp[u], j * (4 >> u));  // e^{2 pi i j / 2^(u+1)}
-                const double2 t = cmul(x[k + span], w);
-                x[k + span] = csub(x[k], t);
-                x[k] = cadd(x[k], t);
+        for (int k = 0; k < (1 << r); k++) {
+            if (k & span) continue;
+            const double2 t = rot16(x[k + span], (k & (span - 1)) * (8 >> u));
+            if (!(HALF && u == r - 1)) x[k + span] = csub(x[k], t);
+            x[k] = cadd(x[k], t);
+        }
+    }
+}
+
+// Decimation in frequency, sign -1 (forward): the sub-stages in reverse order,
+// conjugate twiddles after the difference.  HALF: the upper half of the input
+// is zero (and not read).
+template <int r, bool TRIV, bool HALF>
+__device__ __forceinline__ void dif_regs(double2 (&x)[1 << r], double2 wt) {
+#pragma unroll
+    for (int u = r - 1; u >= 0; u--) {
+        const int span = 1 << u;
+#pragma unroll
+        for (int k = 0; k < (1 << r); k++) {
+            if (k & span) continue;
+            double2 d = x[k];
+            if (!(HALF && u == r - 1)) {
+                d = csub(x[k], x[k + span]);
+                x[k] = cadd(x[k], x[k + span]);
+            }
+            x[k + span] = rot16(d, 16 - (k & (span - 1)) * (8 >> u));
+        }
+    }
+    if constexpr (!TRIV) twiddle<r, true>(x, wt);
+}
+
+// The transform of size S = 2^LG by T threads: passes of r1 (outermost), r2 and
+// r3 (innermost) radix-2 stages; up to S = 16 one thread does it all.
+template <int LG, int T>
+struct RingFft {
+    static constexpr int S = 1 << LG, r1 = ring_shape(LG).r1, r2 = ring_shape(LG).r2, r3 = ring_shape(LG).r3;
+    static constexpr int RO = r1 ? r1 : r3;         // stages of the pass that meets input and output
+    static constexpr int NO = 1 << RO, ST = S >> RO;  // its points per thread and their stride
+    static_assert(ST <= T && (S >> r3) <= T, "one outer and one inner group per thread");
+    int tid;
+    double2 *buf;
+    double2 w1, w2;  // top twiddles of the outer and the middle pass
+
+    __device__ __forceinline__ RingFft(int tid_, double2 *buf_, const double2 *__restrict__ tw, int tw_log)
+        : tid(tid_), buf(buf_) {
+        w1 = w2 = make_double2(1.0, 0.0);
+        if (r1) w1 = tw[min(tid, ST - 1) << (tw_log - LG)];
+        if (r2) w2 = tw[(tid & ((1 << r3) - 1)) << (tw_log - r3 - r2)];
+    }
+    __device__ __forceinline__ bool active() const { return ST == T || tid < ST; }
+    __device__ __forceinline__ bool inner() const { return (S >> r3) == T || tid < (S >> r3); }
+
+    // middle pass (its groups of one thread share pos, hence the twiddle)
+    template <bool DIT>
+    __device__ __forceinline__ void middle() {
+        if constexpr (r2 > 0) {
+            constexpr int h = 1 << r3;
+#pragma unroll
+            for (int g0 = 0; g0 < (S >> r2); g0 += T) {
+                const int gi = tid + g0;
+                if ((S >> r2) % T && gi >= (S >> r2)) break;
+                const int base = (gi >> r3) * (h << r2) + (gi & (h - 1));
+                double2 x[1 << r2];
+#pragma unroll
+                for (int k = 0; k < (1 << r2); k++) x[k] = buf[pidx(base + k * h)];
+                if (DIT) dit_regs<r2, false, false>(x, w2);
+                else dif_regs<r2, false, false>(x, w2);
+#pragma unroll
+                for (int k = 0; k < (1 << r2); k++) buf[pidx(base + k * h)] = x[k];
+            }
+            group_sync<T>();
+        }
+    }
+
+    // Backward DFT of the natural-order input in buf (complete before the
+    // call); on return x[k] of an active thread is output tid + k ST.
+    __device__ __forceinline__ void backward(double2 (&x)[NO]) {
+        if constexpr (r1 == 0) {
+            if (inner()) {
+#pragma unroll
+                for (int k = 0; k < NO; k++) x[k] = buf[pidx(bitrev(k, r3))];
+                dit_regs<r3, true, false>(x, w1);
+            }
+        } else {
+            double2 v[1 << r3];
+            if (inner()) {
+#pragma unroll
+                for (int k = 0; k < (1 << r3); k++) v[k] = buf[pidx((bitrev(k, r3) << (LG - r3)) | bitrev(tid, LG - r3))];
+                dit_regs<r3, true, false>(v, w1);
+            }
+            group_sync<T>();  // every input is in registers
+            if (inner()) {
+#pragma unroll
+                for (int k = 0; k < (1 << r3); k++) buf[pidx((tid << r3) + k)] = v[k];
+            }
+            group_sync<T>();
+            middle<true>();
+            if (active()) {
+#pragma unroll
+                for (int k = 0; k < NO; k++) x[k] = buf[pidx(tid + k * ST)];
+                dit_regs<r1, false, false>(x, w1);
             }
         }
-#pragma unroll
-        for (int k = 0; k < R; k++) a[pidx(base + k * h)] = x[k];
     }
-    __syncthreads();
-}
 
-// Decimation in frequency, sign -1 (forward): the same groups with the
-// sub-stages in reverse order and conjugate twiddles applied after the
-// difference.
-template <int r>
-__device__ __forceinline__ void dif_pass(double2 *a, int lg, int s, const double2 *__restrict__ tw,
-                                         int tw_log, int tid, int nt, int nz) {
-    constexpr int R = 1 << r;
-    const int n = 1 << lg, h = 1 << (s - 1);
+    // Circular convolution with the spectrum V (laid out [k][group] of the
+    // innermost pass): cur[k] of an active thread holds input tid + k ST, k <
+    // NO / 2 (the upper half is zero), and on return the output of that index.
+    // Writes only what the same thread read last, so calls can follow each
+    // other; the buffer's earlier contents must have been read by all.
+    // (No array lives across a pass: values merged under a condition would.)
+    __device__ __forceinline__ void convolve(double2 (&cur)[NO / 2], const double2 *__restrict__ V) {
+        if constexpr (r1 == 0) {
+            double2 x[NO];
+#pragma unroll
+            for (int k = 0; k < NO / 2; k++) x[k] = cur[k];
+            dif_regs<r3, true, true>(x, w1);
+#pragma unroll
+            for (int k = 0; k < NO; k++) x[k] = cmul(x[k], V[k]);
+            dit_regs<r3, true, true>(x, w1);
+#pragma unroll
+            for (int k = 0; k < NO / 2; k++) cur[k] = x[k];
+        } else {
+            if (active()) {
+                double2 x[NO];
+#pragma unroll
+                for (int k = 0; k < NO / 2; k++) x[k] = cur[k];
+                dif_regs<r1, false, true>(x, w1);
+#pragma unroll
+                for (int k = 0; k < NO; k++) buf[pidx(tid + k * ST)] = x[k];
+            }
+            group_sync<T>();
+            middle<false>();
+            if (inner()) {
+                constexpr int NG = S >> r3;
+                double2 v[1 << r3];
+#pragma unroll
+                for (int k = 0; k < (1 << r3); k++) v[k] = buf[pidx((tid << r3) + k)];
+                dif_regs<r3, true, false>(v, w1);
+#pragma unroll
+                for (int k0 = 0; k0 < (1 << r3); k0 += 4) {  // four loads at a time: registers
+#pragma unroll
+                    for (int k = k0; k < k0 + 4; k++) v[k] = cmul(v[k], V[k * NG + tid]);
+                    asm volatile("" ::: "memory");
+                }
+                dit_regs<r3, true, false>(v, w1);
+#pragma unroll
+                for (int k = 0; k < (1 << r3); k++) buf[pidx((tid << r3) + k)] = v[k];
+            }
+            group_sync<T>();
+            middle<true>();
+            double2 x[NO];
+#pragma unroll
+            for (int k = 0; k < NO; k++) x[k] = buf[pidx(min(tid, ST - 1) + k * ST)];
+            dit_regs<r1, false, true>(x, w1);
+#pragma unroll
+            for (int k = 0; k < NO / 2; k++) cur[k] = x[k];
+        }
+    }
+
+    // Backward DFT of size n = 2h from the chirp-weighted halves even and odd
+    // (input tid + k ST of each, zero past h), by Bluestein: for each of the
+    // thread's p = tid + k ST < h, out(p, z_p, z_{p+h}).
+    template <typename F>
+    __device__ __forceinline__ void bluestein(double2 (&even)[NO / 2], double2 (&odd)[NO / 2], int n,
+                                              const double2 *__restrict__ V, const double2 *__restrict__ W, F out) {
+        const int h = n / 2;
+        double2 A[NO / 2];
 #pragma unroll 1
-    for (int gi = tid; gi < n / R; gi += nt) {
-        const int pos = gi & (h - 1);
-        const int base = (gi >> (s - 1)) * (R * h) + pos;
-        double2 x[R];
+        for (int hh = 0; hh < 2; hh++) {
+            convolve(even, V);
+            if (hh == 0) {
 #pragma unroll
-        for (int k = 0; k < R; k++) x[k] = base + k * h < nz ? a[pidx(base + k * h)] : make_double2(0.0, 0.0);
-        double2 wp[r];
-        wp[r - 1] = tw[pos << (tw_log - (s - 1) - r)];
-#pragma unroll
-        for (int u = r - 2; u >= 0; u--) wp[u] = cmul(wp[u + 1], wp[u + 1]);
-#pragma unroll
-        for (int u = r - 1; u >= 0; u--) {
-            const int span = 1 << u;
-#pragma unroll
-            for (int k = 0; k < R; k++) {
-                if (k & span) continue;
-                const int j = k & (span - 1);
-                const double2 w = cconj(rot8(wp[u], j * (4 >> u)));
-                const double2 x0 = x[k], x1 = x[k + span];
-                x[k] = cadd(x0, x1);
-                x[k + span] = cmul(csub(x0, x1), w);
+                for (int k = 0; k < NO / 2; k++) {
+                    A[k] = even[k];
+                    even[k] = odd[k];
+                }
             }
         }
+        if (!active()) return;
+        const double2 ws = expipi(2.0 * ST / n);
+        double2 wp;
 #pragma unroll
-        for (int k = 0; k < R; k++) a[pidx(base + k * h)] = x[k];
-    }
-    __syncthreads();
-}
-
-// Backward DFT of size 2^lg, bit-reversed input, natural output, by the nt
-// threads tid = 0..nt-1 of the caller's thread group.
-__device__ void fft_dit_inv(double2 *a, int lg, const double2 *__restrict__ tw, int tw_log, int tid, int nt) {
-    int s = 1;
-    while (lg - s + 1 >= 3) {
-        dit_pass<3>(a, lg, s, tw, tw_log, tid, nt);
-        s += 3;
-    }
-    if (lg - s + 1 == 2) dit_pass<2>(a, lg, s, tw, tw_log, tid, nt);
-    else if (lg - s + 1 == 1) dit_pass<1>(a, lg, s, tw, tw_log, tid, nt);
-}
-
-// Forward DFT of size 2^lg, natural input, bit-reversed output; the inputs
-// past the first nz are zero (the first pass reads them as such, so they
-// need not be stored).
-__device__ void fft_dif_fwd(double2 *a, int lg, const double2 *__restrict__ tw, int tw_log, int tid, int nt,
-                            int nz) {
-    const int n = 1 << lg, rem = lg % 3;
-    int s = lg - 2;
-    while (s >= 1 + rem) {
-        dif_pass<3>(a, lg, s, tw, tw_log, tid, nt, s == lg - 2 ? nz : n);
-        s -= 3;
-    }
-    if (rem == 2) dif_pass<2>(a, lg, 1, tw, tw_log, tid, nt, lg == 2 ? nz : n);
-    else if (rem == 1) dif_pass<1>(a, lg, 1, tw, tw_log, tid, nt, lg == 1 ? nz : n);
-}
-
-// buf[pidx(i)] *= X[i] for the entries i = tid + j nt < cnt (j < PT) of one
-// thread, up to NB loads of X in flight before the first product (loads
-// past cnt read X[cnt - 1] and are dropped).
-template <int PT, int NB>
-__device__ __forceinline__ void lds_cmul(double2 *buf, const double2 *__restrict__ X, int cnt, int tid, int nt) {
-    constexpr int B = PT < NB ? PT : NB;
-    if (B == 1) {  // one load at a time
-        for (int i = tid; i < cnt; i += nt) buf[pidx(i)] = cmul_fixed(buf[pidx(i)], X[i]);
-        return;
-    }
+        for (int k0 = 0; k0 < NO / 2; k0 += 4) {
+            double2 w[4];
 #pragma unroll
-    for (int j0 = 0; j0 < PT; j0 += B) {
-        double2 x[B];
+            for (int k = 0; k < 4; k++) w[k] = W[min(tid + min(k0 + k, NO / 2 - 1) * ST, h - 1)];
 #pragma unroll
-        for (int j = 0; j < B; j++) x[j] = X[min(tid + (j0 + j) * nt, cnt - 1)];
-#pragma unroll
-        for (int j = 0; j < B; j++) {
-            const int i = tid + (j0 + j) * nt;
-            if (i < cnt) buf[pidx(i)] = cmul_fixed(buf[pidx(i)], x[j]);
+            for (int k = k0; k < k0 + 4 && k < NO / 2; k++) {
+                const int p = tid + k * ST;
+                wp = k == k0 ? expipi(2.0 * p / n) : cmul(wp, ws);  // e^{2 pi i p/n}, stepped by products
+                if (p < h) {
+                    const double2 Ap = cmul(A[k], w[k - k0]), t = cmul(cmul(even[k], w[k - k0]), wp);
+                    out(p, cadd(Ap, t), csub(Ap, t));
+                }
+            }
         }
     }
-}
+};
 
-// Unnormalised backward DFT of size n in LDS: z_p = sum_k Z_k e^{+2 pi i k p/n}.
-// On entry the buffer holds Z_k at pidx(bitrev(k)) (n a power of two, M = 0)
-// or the chirp-weighted u_k = Z_k W_k, W_k = e^{i pi k^2/n}, at pidx(k), k < n
-// (Bluestein: the zero padding up to M is implied, entries n..M-1 are not
-// read); on exit z_p is at pidx(p), p < n.  PT bounds M / nt (and so
-// 2n / nt); NB loads of V or W per thread are in flight at once.
-template <int PT, int NB>
-__device__ __forceinline__ void backward_dft(double2 *buf, int n, int M, const double2 *__restrict__ V,
-                                             const double2 *__restrict__ W, const double2 *__restrict__ tw,
-                                             int tw_log, int tid, int nt) {
-    if (M == 0) {
-        fft_dit_inv(buf, ilog2_dev(n), tw, tw_log, tid, nt);
-        return;
+// f(RingFft) of the transform size 2^lg; a group of T threads has the sizes
+// its class holds.
+template <int T, typename F>
+__device__ __forceinline__ void with_fft(int lg, int tid, double2 *buf, const RingArgs &a, F f) {
+#define SHT_FFT(LG) f(RingFft<LG, T>(tid, buf, a.tw, a.tw_log))
+    if constexpr (T == 64) {
+        switch (lg) {
+            case 1: SHT_FFT(1); break;
+            case 2: SHT_FFT(2); break;
+            case 3: SHT_FFT(3); break;
+            case 4: SHT_FFT(4); break;
+            case 5: SHT_FFT(5); break;
+            case 6: SHT_FFT(6); break;
+            case 7: SHT_FFT(7); break;
+            case 8: SHT_FFT(8); break;
+            case 9: SHT_FFT(9); break;
+            default: SHT_FFT(10); break;
+        }
+    } else if constexpr (T == 128) {
+        SHT_FFT(11);
+    } else {
+        SHT_FFT(12);
     }
-    const int lgM = ilog2_dev(M);
-    fft_dif_fwd(buf, lgM, tw, tw_log, tid, nt, n);
-    lds_cmul<PT, NB>(buf, V, M, tid, nt);
-    __syncthreads();
-    fft_dit_inv(buf, lgM, tw, tw_log, tid, nt);
-    lds_cmul<(PT > 1 ? PT / 2 : 1), NB>(buf, W, n, tid, nt);
-    __syncthreads();
+#undef SHT_FFT
 }
 
 // Raw wrap sums (before the common phase) of the NBIN bins bin[p] of one
@@ -310,186 +442,29 @@ __device__ __forceinline__ void bins_direct(const double2 *__restrict__ qr, size
     }
 }
 
-// Synthesis of one ring of one map (item = ring position in the class's
-// list times nmaps plus the map) by the nt threads tid = 0..nt-1 of a group
-// owning the LDS block buf.  A workgroup of T threads is one group, or T/nt
-// groups for maps of one ring (identical control flow, so the workgroup's
-// barriers match); a ring whose transform size is at most 4096 nt / T keeps
-// the per-thread counts within those sized for T.
-template <int T, int nt, int kNB>
+// Synthesis of one ring of one map (item = ring position in the class's list
+// times nmaps plus the map) by the T threads tid = 0..T-1 of a group owning
+// the LDS block buf.
+template <int T>
 __device__ __forceinline__ void ring_synth_item(const RingArgs &a, const int item, const int tid, double2 *buf) {
-    constexpr int kPairsPerThread = (kMaxPairs + T - 1) / T;
-    constexpr int kMPerThread = (2 * kMaxHalf + T - 1) / T;  // Bluestein size M <= 2 kMaxHalf
+    constexpr int CP = 4;  // bin pairs per thread and batch of loads
     const int pos = item / a.nmaps, b = item % a.nmaps;
     const int rho = a.rings[pos];
     const int J = a.ring_J[rho], s = a.ring_s[rho], M = a.ring_M[rho];
-    const int n = J / 2, lgn = ilog2_dev(n);
+    const int n = J / 2, h = n / 2;
     const bool bs = M > 0;
     const double2 *__restrict__ W = a.chirp + (bs ? a.ring_chirp_off[rho] : 0);
     const int L = a.L;
     const int npair = n / 2 + 1;
-    // ring-major q: the maps of one ring interleave in one contiguous block,
-    // and their workgroups run back to back on one XCD (shared L2 lines)
-    const size_t qstride = (size_t)a.nmaps;
+    // ring-major q: the maps of one ring interleave in one contiguous block
+    const size_t qs = (size_t)a.nmaps;
     const double2 *qr = a.q + (size_t)rho * (L + 1) * a.nmaps + b;
 
-    // raw bin sums for the pairs (k, n-k) owned by this thread
-    double2 xa[kPairsPerThread], xb[kPairsPerThread];
-#pragma unroll
-    for (int j = 0; j < kPairsPerThread; j++) xa[j] = xb[j] = make_double2(0.0, 0.0);
-
-    const bool wrap = n <= L;
-    int G = 1;
-    if (!wrap) {
-        // every bin b <= L holds exactly q_b; issue all loads first
-#pragma unroll
-        for (int j = 0; j < kPairsPerThread; j++) {
-            const int k = tid + j * nt;
-            if (k < npair) {
-                if (k <= L) xa[j] = qr[(size_t)k * qstride];
-                if (k == 0) xa[j].y = 0.0;
-                if (k != 0 && n - k <= L) xb[j] = qr[(size_t)(n - k) * qstride];
-            }
-        }
-    } else if (2 * n > L) {
-        // J > L: bin b <= n collects m = b and, when J - b <= L, m = J - b
-        // (conjugated, sign (-1)^s); bin n (pair k = 0) collects m = n
-        // (j = 0) and m = J - n = n (j = 1, conjugated).  Direct loads, no
-        // staging: the four loads of every pair of a chunk of kCH pairs are
-        // issued (at valid orders) before any is used, and the optional
-        // terms enter by selection
-        const double sg = (s & 1) ? -1.0 : 1.0;
-        const int J2 = 2 * n;
-        constexpr int kCH = kPairsPerThread < 3 ? kPairsPerThread : 3;
-#pragma unroll
-        for (int j0 = 0; j0 < kPairsPerThread; j0 += kCH) {
-            double2 v[kCH][4];
-#pragma unroll
-            for (int c = 0; c < kCH; c++) {
-                const int k = tid + (j0 + c) * nt;
-                const int kc = j0 + c < kPairsPerThread && k < npair ? k : 0;
-                const int b = kc == 0 ? n : n - kc;  // second bin, 0 < b <= n
-                v[c][0] = qr[(size_t)kc * qstride];  // kc <= n <= L
-                v[c][1] = qr[(size_t)(J2 - kc <= L ? J2 - kc : 0) * qstride];
-                v[c][2] = qr[(size_t)b * qstride];
-                v[c][3] = qr[(size_t)(kc == 0 ? n : (J2 - b <= L ? J2 - b : 0)) * qstride];
-            }
-#pragma unroll
-            for (int c = 0; c < kCH; c++) {
-                const int j = j0 + c, k = tid + j * nt;
-                if (j < kPairsPerThread && k < npair) {
-                    const int b = k == 0 ? n : n - k;
-                    double2 x = v[c][0];
-                    if (k == 0) x.y = 0.0;
-                    const double2 xw = make_double2(x.x + sg * v[c][1].x, x.y - sg * v[c][1].y);
-                    xa[j] = J2 - k <= L ? xw : x;
-                    const double2 u = v[c][2];
-                    const double2 uw = make_double2(u.x + sg * v[c][3].x, u.y - sg * v[c][3].y);
-                    xb[j] = k == 0 || J2 - b <= L ? uw : u;
-                }
-            }
-            asm volatile("" ::: "memory");  // keep the next chunk's loads after this one's uses
-        }
-    } else {
-        // J <= L: every bin collects several orders; each thread sums the
-        // orders of its bins (terms j = g mod G) straight from q, in a fixed
-        // order: pair k owns bins k and n - k (bin n for k = 0, none for
-        // 2k = n)
-        G = npair >= nt ? 1 : nt / npair;
-        if (npair <= nt) {
-            // one pair per thread (G groups of npair threads), four terms
-            // of each bin per round of loads
-            const int g = tid / npair, k = tid % npair;
-            const int bn[2] = {k, k == 0 ? n : n - k};
-            const bool on[2] = {g < G, g < G && 2 * k != n};
-            double2 acc[2];
-            bins_direct<2, 4>(qr, qstride, L, J, s, bn, on, g, G, acc);
-            xa[0] = acc[0];
-            xb[0] = acc[1];
-        } else {
-            // several pairs per thread (G = 1): rounds of one term of each
-            // of up to 2 kCP bins
-            constexpr int kCP = kPairsPerThread < 3 ? kPairsPerThread : 3;
-#pragma unroll
-            for (int j0 = 0; j0 < kPairsPerThread; j0 += kCP) {
-                int bn[2 * kCP];
-                bool on[2 * kCP];
-#pragma unroll
-                for (int c = 0; c < kCP; c++) {
-                    const int k = tid + (j0 + c) * nt;
-                    bn[2 * c] = k;
-                    bn[2 * c + 1] = k == 0 ? n : n - k;
-                    on[2 * c] = j0 + c < kPairsPerThread && k < npair;
-                    on[2 * c + 1] = on[2 * c] && 2 * k != n;
-                }
-                double2 acc[2 * kCP];
-                bins_direct<2 * kCP, 1>(qr, qstride, L, J, s, bn, on, 0, 1, acc);
-#pragma unroll
-                for (int c = 0; c < kCP; c++)
-                    if (j0 + c < kPairsPerThread) {
-                        xa[j0 + c] = acc[2 * c];
-                        xb[j0 + c] = acc[2 * c + 1];
-                    }
-            }
-        }
-        if (G > 1) {
-            // reduce the group partials in a fixed order, through the start
-            // of the group's LDS block (at least 2 nt entries), before the
-            // DFT uses it
-            double2 *red = buf;
-            if (tid < G * npair) {
-                red[2 * tid] = xa[0];
-                red[2 * tid + 1] = xb[0];
-            }
-            __syncthreads();
-            if (tid < npair) {
-                double2 s0 = make_double2(0.0, 0.0), s1 = make_double2(0.0, 0.0);
-                for (int g = 0; g < G; g++) {
-                    s0 = cadd(s0, red[2 * (g * npair + tid)]);
-                    s1 = cadd(s1, red[2 * (g * npair + tid) + 1]);
-                }
-                xa[0] = s0;
-                xb[0] = s1;
-            }
-            __syncthreads();
-        }
-    }
-
-    // phase shift, Hermitian pre-twiddle, store into the DFT input: natural
-    // bit-reversed order for power-of-two n; for split Bluestein rings even k
-    // at k/2 and odd k at h + (k-1)/2 (n = 2h), weighted by the chirp
-    const int h = n / 2;
-    // e^{i pi k/J} and e^{i pi k/n} for k = tid + j nt by products with the
-    // step e^{i pi nt/J} (resp. n): two sincospi per thread instead of three
-    // per pair (the rounding grows by about an ulp per step)
-    double2 pJ = make_double2(1.0, 0.0), sJ = pJ;
-    if (s) {
-        pJ = expipi((double)tid / J);
-        sJ = expipi((double)nt / J);
-    }
-    double2 pn = expipi((double)tid / n);
-    const double2 sn = expipi((double)nt / n);
-    // Bluestein chirp weights W[kp], W[kq] of a chunk of kCW pairs loaded
-    // (at clamped, valid indices) before the chunk's first use
-    constexpr int kCW = kPairsPerThread < 3 ? kPairsPerThread : 3;
-#pragma unroll
-    for (int j0 = 0; j0 < kPairsPerThread; j0 += kCW) {
-    double2 wv[kCW][2];
-    if (bs) {
-#pragma unroll
-        for (int c = 0; c < kCW; c++) {
-            const int k = tid + (j0 + c) * nt, odd = k & 1;
-            wv[c][0] = W[max(0, min((k - odd) / 2, h - 1))];
-            wv[c][1] = W[max(0, min((n - k - odd) / 2, h - 1))];
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < kCW; c++) {
-        const int j = j0 + c;
-        if (j >= kPairsPerThread) break;
-        const int k = tid + j * nt;
-        if (k < npair && !(G > 1 && j > 0)) {
-        double2 Xk = xa[j], Xnk = xb[j];
+    // the raw sums Xk, Xnk of the pair of bins (k, n - k) (bin n for k = 0),
+    // phase shifted, pre-twiddled and stored in the DFT's input: natural order,
+    // or (Bluestein) even k at k/2 and odd k at h + (k-1)/2, chirp-weighted
+    const double2 sJ = s ? expipi((double)T / J) : make_double2(1.0, 0.0), sn = expipi((double)T / n);
+    auto put = [&](int k, double2 Xk, double2 Xnk, double2 pJ, double2 pn, double2 wk, double2 wnk) {
         if (s) {
             Xk = cmul(Xk, pJ);
             Xnk = cmul(Xnk, i_conj(pJ));  // e^{i pi (n - k)/J}, n = J/2
@@ -497,90 +472,180 @@ __device__ __forceinline__ void ring_synth_item(const RingArgs &a, const int ite
         double2 Zk, Znk = make_double2(0.0, 0.0);
         const bool two = (k != 0) && (2 * k != n);
         if (k == 0) {
-            double2 e = cadd(Xk, cconj(Xnk)), o = csub(Xk, cconj(Xnk));
+            const double2 e = cadd(Xk, cconj(Xnk)), o = csub(Xk, cconj(Xnk));
             Zk = make_double2(e.x - o.y, e.y + o.x);
         } else if (2 * k == n) {
             Zk = make_double2(2.0 * Xk.x, -2.0 * Xk.y);
         } else {
-            double2 e = cadd(Xk, cconj(Xnk));
-            double2 o = cmul(csub(Xk, cconj(Xnk)), pn);
+            const double2 e = cadd(Xk, cconj(Xnk));
+            const double2 o = cmul(csub(Xk, cconj(Xnk)), pn);
             Zk = make_double2(e.x - o.y, e.y + o.x);
             Znk = make_double2(e.x + o.y, -e.y + o.x);  // conj(e) + i conj(o)
         }
         if (!bs) {
-            buf[pidx(bitrev(k, lgn))] = Zk;
-            if (two) buf[pidx(bitrev(n - k, lgn))] = Znk;
+            buf[pidx(k)] = Zk;
+            if (two) buf[pidx(n - k)] = Znk;
         } else {
-            const int odd = k & 1, kp = (k - odd) / 2;
-            buf[pidx(kp + odd * h)] = cmul(Zk, wv[c][0]);
-            if (two) {
-                const int kq = (n - k - odd) / 2;
-                buf[pidx(kq + odd * h)] = cmul(Znk, wv[c][1]);
+            const int odd = k & 1;
+            buf[pidx((k - odd) / 2 + odd * h)] = cmul(Zk, wk);
+            if (two) buf[pidx((n - k - odd) / 2 + odd * h)] = cmul(Znk, wnk);
+        }
+    };
+    auto chirp = [&](int k) { return W[max(0, min((k - (k & 1)) / 2, h - 1))]; };
+    const double2 one = make_double2(1.0, 0.0);
+
+    if (J <= L && npair <= T) {
+        // few bins, several orders each: G groups of npair threads sum the
+        // terms j = g mod G of their bins, then reduce
+        const int G = T / npair, g = tid / npair, k = tid % npair;
+        const int bn[2] = {k, k == 0 ? n : n - k};
+        const bool on[2] = {g < G, g < G && 2 * k != n};
+        double2 acc[2];
+        bins_direct<2, 4>(qr, qs, L, J, s, bn, on, g, G, acc);
+        if (G > 1) {
+            if (g < G) {
+                buf[2 * tid] = acc[0];
+                buf[2 * tid + 1] = acc[1];
+            }
+            group_sync<T>();
+            if (tid < npair) {
+                acc[0] = acc[1] = make_double2(0.0, 0.0);
+                for (int gg = 0; gg < G; gg++) {
+                    acc[0] = cadd(acc[0], buf[2 * (gg * npair + tid)]);
+                    acc[1] = cadd(acc[1], buf[2 * (gg * npair + tid) + 1]);
+                }
+            }
+            group_sync<T>();
+        }
+        if (tid < npair)
+            put(k, acc[0], acc[1], s ? expipi((double)k / J) : one, expipi((double)k / n), bs ? chirp(k) : one,
+                bs ? chirp(n - k) : one);
+    } else {
+#pragma unroll 1
+        for (int k0 = tid; k0 < npair; k0 += T * CP) {
+            double2 xa[CP], xb[CP];
+            if (J > L) {
+                // bin b <= n collects m = b and, when J - b <= L, m = J - b
+                // (conjugated, sign (-1)^s); bin n of pair 0 collects m = n
+                // twice.  All loads go first, at valid orders.
+                const double sg = (s & 1) ? -1.0 : 1.0;
+                double2 v[CP][2];
+#pragma unroll
+                for (int c = 0; c < CP; c++) {
+                    const int k = min(k0 + c * T, npair - 1), nk = n - k;
+                    xa[c] = qr[(size_t)min(k, L) * qs];
+                    xb[c] = qr[(size_t)min(nk, L) * qs];
+                }
+                if (n <= L) {
+#pragma unroll
+                    for (int c = 0; c < CP; c++) {
+                        const int k = min(k0 + c * T, npair - 1), nk = n - k;
+                        v[c][0] = qr[(size_t)(J - k <= L ? J - k : 0) * qs];
+                        v[c][1] = qr[(size_t)(J - nk <= L ? J - nk : 0) * qs];
+                    }
+#pragma unroll
+                    for (int c = 0; c < CP; c++) {
+                        const int k = min(k0 + c * T, npair - 1), nk = n - k;
+                        const double2 wa = keep(v[c][0], k != 0 && J - k <= L), wb = keep(v[c][1], J - nk <= L);
+                        xa[c] = make_double2(xa[c].x + sg * wa.x, xa[c].y - sg * wa.y);
+                        xb[c] = make_double2(xb[c].x + sg * wb.x, xb[c].y - sg * wb.y);
+                        if (k == 0) xa[c].y = 0.0;
+                    }
+                } else {
+#pragma unroll
+                    for (int c = 0; c < CP; c++) {
+                        const int k = min(k0 + c * T, npair - 1), nk = n - k;
+                        xa[c] = keep(xa[c], k <= L);
+                        xb[c] = keep(xb[c], nk <= L);
+                        if (k == 0) xa[c].y = 0.0;
+                    }
+                }
+            } else {
+                // several pairs per thread: rounds of one term of each bin
+                int bn[2 * CP];
+                bool on[2 * CP];
+#pragma unroll
+                for (int c = 0; c < CP; c++) {
+                    const int k = k0 + c * T;
+                    bn[2 * c] = k;
+                    bn[2 * c + 1] = k == 0 ? n : n - k;
+                    on[2 * c] = k < npair;
+                    on[2 * c + 1] = on[2 * c] && 2 * k != n;
+                }
+                double2 acc[2 * CP];
+                bins_direct<2 * CP, 1>(qr, qs, L, J, s, bn, on, 0, 1, acc);
+#pragma unroll
+                for (int c = 0; c < CP; c++) {
+                    xa[c] = acc[2 * c];
+                    xb[c] = acc[2 * c + 1];
+                }
+            }
+            double2 wv[CP][2];
+            if (bs) {
+#pragma unroll
+                for (int c = 0; c < CP; c++) {
+                    const int k = k0 + c * T;
+                    wv[c][0] = chirp(k);
+                    wv[c][1] = chirp(n - k);
+                }
+            }
+            // e^{i pi k/J} and e^{i pi k/n}, exact at the batch's first k and
+            // stepped by products (about an ulp per step)
+            double2 pJ = s ? expipi((double)k0 / J) : one, pn = expipi((double)k0 / n);
+#pragma unroll
+            for (int c = 0; c < CP; c++) {
+                const int k = k0 + c * T;
+                if (k < npair) put(k, xa[c], xb[c], pJ, pn, wv[c][0], wv[c][1]);
+                pJ = cmul(pJ, sJ);
+                pn = cmul(pn, sn);
             }
         }
-        }
-        pJ = cmul(pJ, sJ);
-        pn = cmul(pn, sn);
     }
-    }
-    __syncthreads();
+    group_sync<T>();
     // pixel 2p = Re z_p, pixel 2p+1 = Im z_p
     double2 *out = reinterpret_cast<double2 *>(a.map + (size_t)b * a.npix + a.ring_off[rho]);
     if (!bs) {
-        backward_dft<kMPerThread, kNB>(buf, n, 0, nullptr, nullptr, a.tw, a.tw_log, tid, nt);
-        for (int p = tid; p < n; p += nt) out[p] = buf[pidx(p)];
-        return;
-    }
-
-    // split Bluestein: the odd half waits in registers while the even half
-    // (A) is transformed, then A waits while the odd half (B) is
-    constexpr int kHalfPerThread = (kMaxHalf + T - 1) / T;
-    const double2 *__restrict__ V = a.bs_table + a.ring_bs_off[rho];
-    double2 R[kHalfPerThread];
+        with_fft<T>(ilog2_dev(n), tid, buf, a, [&](auto fft) {
+            using F = decltype(fft);
+            double2 x[F::NO];
+            fft.backward(x);
+            if (fft.active()) {
 #pragma unroll
-    for (int jj = 0; jj < kHalfPerThread; jj++) {
-        const int p = tid + jj * nt;
-        if (p < h) R[jj] = buf[pidx(h + p)];
-    }
-    __syncthreads();
-    backward_dft<kMPerThread, kNB>(buf, h, M, V, W, a.tw, a.tw_log, tid, nt);
+                for (int k = 0; k < F::NO; k++) out[tid + k * F::ST] = x[k];
+            }
+        });
+    } else {
+        const double2 *__restrict__ V = a.bs_table + a.ring_bs_off[rho];
+        with_fft<T>(ilog2_dev(M), tid, buf, a, [&](auto fft) {
+            using F = decltype(fft);
+            if constexpr (F::r3 >= 3) {  // a Bluestein transform has h >= 3
+                double2 even[F::NO / 2], odd[F::NO / 2];
 #pragma unroll
-    for (int jj = 0; jj < kHalfPerThread; jj++) {
-        const int p = tid + jj * nt;
-        if (p < h) {
-            const double2 odd_in = R[jj];
-            R[jj] = buf[pidx(p)];  // A_p
-            buf[pidx(p)] = odd_in;
-        }
-    }
-    __syncthreads();
-    backward_dft<kMPerThread, kNB>(buf, h, M, V, W, a.tw, a.tw_log, tid, nt);
-    double2 wp = expipi(2.0 * tid / n);  // e^{2 pi i p/n}, stepped as above
-    const double2 ws = expipi(2.0 * nt / n);
-#pragma unroll
-    for (int jj = 0; jj < kHalfPerThread; jj++) {
-        const int p = tid + jj * nt;
-        if (p < h) {
-            const double2 t = cmul(buf[pidx(p)], wp);
-            out[p] = cadd(R[jj], t);
-            out[p + h] = csub(R[jj], t);
-        }
-        wp = cmul(wp, ws);
+                for (int k = 0; k < F::NO / 2; k++) {
+                    const int p = tid + k * F::ST, pc = min(p, h - 1);
+                    even[k] = keep(buf[pidx(pc)], p < h);
+                    odd[k] = keep(buf[pidx(h + pc)], p < h);
+                }
+                group_sync<T>();
+                fft.bluestein(even, odd, n, V, W, [&](int p, double2 z0, double2 z1) {
+                    out[p] = z0;
+                    out[p + h] = z1;
+                });
+            }
+        });
     }
 }
 
-// Workgroup w runs the items w G .. w G + G - 1 (G = a.mpw maps of one
-// ring, G | nmaps), one group of T/G threads and one LDS block each.
+// Groups of T threads; up to T = 64 a workgroup runs G maps of one ring (G
+// divides nmaps), a wavefront and an LDS block each.
 template <int T, int G>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 4 : 1))) void k_ring_synth(RingArgs a) {
+__global__ __launch_bounds__(T * G, 2) void k_ring_synth(RingArgs a) {
     extern __shared__ double2 sm[];
-    constexpr int nt = T / G;
-    const int sub = G == 1 ? 0 : (int)threadIdx.x / nt;
-    const int item0 = xcd_item(blockIdx.x) * G;
-    if (item0 >= a.count * a.nmaps) return;
-    // (one group: the plain thread index and LDS base keep 26 fewer VGPRs)
-    if (G == 1) ring_synth_item<T, nt, (T >= 512 ? 8 : 1)>(a, item0, threadIdx.x, sm);
-    else ring_synth_item<T, nt, 1>(a, item0 + sub, threadIdx.x - sub * nt, sm + (size_t)sub * (a.fft_entries + a.stage));
+    static_assert(G == 1 || T == 64, "wavefronts are independent, larger groups are not");
+    const int sub = G == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / T);
+    const int item = xcd_item(blockIdx.x) * G + sub;
+    if (item >= a.count * a.nmaps) return;
+    ring_synth_item<T>(a, item, (int)threadIdx.x - sub * T, sm + (size_t)sub * a.fft_entries);
 }
 
 // Ring queue of a batch of requests: one launch per ring size class for all
@@ -588,158 +653,14 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 4 
 // items are ordered request by request, ring by ring, map by map, so that
 // the maps of one ring stay on one XCD as in k_ring_synth.
 template <int T>
-__global__ __launch_bounds__(T) void k_ring_synth_queue(const RingArgs *__restrict__ args, const int2 *__restrict__ items,
+__global__ __launch_bounds__(T, 2) void k_ring_synth_queue(const RingArgs *__restrict__ args, const int2 *__restrict__ items,
                                                         int nitems) {
     const int j = xcd_item(blockIdx.x);
     if (j >= nitems) return;
     const int2 it = items[j];
     extern __shared__ double2 sm[];
     const RingArgs a = args[__builtin_amdgcn_readfirstlane(it.x)];
-    ring_synth_item<T, T, 1>(a, __builtin_amdgcn_readfirstlane(it.y), threadIdx.x, sm);
-}
-
-// Raises a kernel's dynamic LDS limit to `bytes`, once per (kernel, device):
-// the attribute belongs to the device current at the call.
-hipError_t allow_dynamic_lds(const void *fn, int bytes) {
-    static std::mutex mu;
-    static std::set<std::pair<const void *, int>> done;
-    int dev = -1;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lk(mu);
-    if (done.count({fn, dev})) return hipSuccess;
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    if (e == hipSuccess) done.insert({fn, dev});
-    return e;
-}
-
-// FFT buffer entries, extra entries and dynamic LDS bytes of the workgroups
-// of one ring class (FFT buffer of lds_entries complex values) at T threads:
-// wrapped rings reduce up to 2 T partial bin sums through the start of the
-// block, so the block holds at least 2 T entries.
-size_t ring_class_shape(int lds_entries, bool wrap, int T, int *fft_entries, int *stage) {
-    *fft_entries = lds_entries + lds_entries / 16;
-    *stage = wrap ? std::max(0, 2 * T - *fft_entries) : 0;
-    return (size_t)(*fft_entries + *stage) * sizeof(double2);
-}
-
-// Maps of one ring per workgroup for a class of transform size S: as many
-// as fill the workgroup's threads with the groups a 4096-entry transform
-// would use (at most 4), dividing nmaps.
-int ring_maps_per_wg(int lds_entries, int nmaps) {
-    int g = 1;
-    while (g < 4 && (g * 2) * lds_entries <= 4096 && nmaps % (g * 2) == 0) g *= 2;
-    return g;
-}
-
-template <int T>
-static hipError_t launch_classes(const sht_plan_s *p, RingArgs a, int nmaps, hipStream_t stream) {
-    const void *fn[3] = {(const void *)k_ring_synth<T, 1>, (const void *)k_ring_synth<T, 2>,
-                         (const void *)k_ring_synth<T, 4>};
-    for (const void *f : fn) {
-        hipError_t ea = allow_dynamic_lds(f, 160 * 1024);
-        if (ea != hipSuccess) return ea;
-    }
-    for (const auto &rc : p->classes) {
-        a.rings = rc.d_rings;
-        a.count = (int)rc.rings.size();
-        a.mpw = ring_maps_per_wg(rc.lds_entries, nmaps);
-        const size_t lds = a.mpw * ring_class_shape(rc.lds_entries, rc.wrap, T / a.mpw, &a.fft_entries, &a.stage);
-        long long grid = ((long long)a.count * nmaps / a.mpw + 63) / 64 * 64;
-        switch (a.mpw) {
-            case 1: hipLaunchKernelGGL((k_ring_synth<T, 1>), dim3((unsigned)grid), dim3(T), lds, stream, a); break;
-            case 2: hipLaunchKernelGGL((k_ring_synth<T, 2>), dim3((unsigned)grid), dim3(T), lds, stream, a); break;
-            default: hipLaunchKernelGGL((k_ring_synth<T, 4>), dim3((unsigned)grid), dim3(T), lds, stream, a); break;
-        }
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-template <int T>
-static hipError_t launch_ring_queue_t(const RingArgs *args, const int2 *items, long long nitems, size_t lds,
-                                      hipStream_t st) {
-    hipError_t e = allow_dynamic_lds((const void *)k_ring_synth_queue<T>, 160 * 1024);
-    if (e != hipSuccess) return e;
-    const long long grid = (nitems + 63) / 64 * 64;
-    if (grid > 0) hipLaunchKernelGGL(k_ring_synth_queue<T>, dim3((unsigned)grid), dim3(T), lds, st, args, items, (int)nitems);
-    return hipGetLastError();
-}
-
-// Raises the ring queue kernel's LDS limit on the current device (done at
-// batch creation, so that runs make no runtime calls besides launches).
-hipError_t ring_queue_prepare(int T) {
-    switch (T) {
-        case 256: return allow_dynamic_lds((const void *)k_ring_synth_queue<256>, 160 * 1024);
-        case 512: return allow_dynamic_lds((const void *)k_ring_synth_queue<512>, 160 * 1024);
-        default: return allow_dynamic_lds((const void *)k_ring_synth_queue<1024>, 160 * 1024);
-    }
-}
-
-hipError_t launch_ring_queue(int T, const RingArgs *args, const int2 *items, long long nitems, size_t lds,
-                             hipStream_t st) {
-    if (nitems < 0 || nitems > 0x7fffffffLL) return hipErrorInvalidValue;
-    switch (T) {
-        case 256: return launch_ring_queue_t<256>(args, items, nitems, lds, st);
-        case 512: return launch_ring_queue_t<512>(args, items, nitems, lds, st);
-        default: return launch_ring_queue_t<1024>(args, items, nitems, lds, st);
-    }
-}
-
-// Plan-wide fields of the ring argument block (synthesis direction); the
-// caller sets the class fields (rings, count, fft_entries, stage).
-RingArgs ring_args(const sht_plan_s *p, int nmaps, const double *q, double *map) {
-    RingArgs a;
-    std::memset(&a, 0, sizeof(a));
-    a.ring_J = p->d_ring_J;
-    a.ring_s = p->d_ring_s;
-    a.ring_M = p->d_ring_M;
-    a.ring_off = p->d_ring_off;
-    a.ring_bs_off = p->d_ring_bs_off;
-    a.tw = reinterpret_cast<const double2 *>(p->d_tw);
-    a.tw_log = p->tw_log;
-    a.bs_table = reinterpret_cast<const double2 *>(p->d_bs_table);
-    a.chirp = reinterpret_cast<const double2 *>(p->d_chirp);
-    a.ring_chirp_off = p->d_ring_chirp_off;
-    a.q = reinterpret_cast<const double2 *>(q);
-    a.map = map;
-    a.L = p->L;
-    a.nrings = p->nrings;
-    a.nmaps = nmaps;
-    a.npix = 12LL * p->nside * p->nside;
-    a.mpw = 1;
-    return a;
-}
-
-hipError_t launch_ring_synthesis(const sht_plan_s *p, int nmaps, const double *q, double *map,
-                                 hipStream_t stream) {
-    RingArgs a;
-    a.ring_J = p->d_ring_J;
-    a.ring_s = p->d_ring_s;
-    a.ring_M = p->d_ring_M;
-    a.ring_off = p->d_ring_off;
-    a.ring_bs_off = p->d_ring_bs_off;
-    a.tw = reinterpret_cast<const double2 *>(p->d_tw);
-    a.tw_log = p->tw_log;
-    a.bs_table = reinterpret_cast<const double2 *>(p->d_bs_table);
-    a.chirp = reinterpret_cast<const double2 *>(p->d_chirp);
-    a.ring_chirp_off = p->d_ring_chirp_off;
-    a.q = reinterpret_cast<const double2 *>(q);
-    a.map = map;
-    a.map_in = nullptr;
-    a.ybar = nullptr;
-    a.wpos = 0.0;
-    a.L = p->L;
-    a.nrings = p->nrings;
-    a.nmaps = nmaps;
-    a.npix = 12LL * p->nside * p->nside;
-    switch (p->ring_threads) {
-        case 256: return launch_classes<256>(p, a, nmaps, stream);
-        case 512: return launch_classes<512>(p, a, nmaps, stream);
-        default: return launch_classes<1024>(p, a, nmaps, stream);
-    }
-    return hipSuccess;
+    ring_synth_item<T>(a, __builtin_amdgcn_readfirstlane(it.y), threadIdx.x, sm);
 }
 
 // Ring stage of the adjoint (the transpose of the above).  For ring k:
@@ -751,117 +672,103 @@ hipError_t launch_ring_synthesis(const sht_plan_s *p, int nmaps, const double *q
 // every m of bin b's two residue classes is written from G_b =
 // e^{-i pi b s/J} F_b:  ybar_{b+jJ} = w (-1)^{js} G_b,
 // ybar_{jJ-b} = w (-1)^{js} conj(G_b).
-// Workgroups of a.mpw maps of one ring, one group of T/a.mpw threads and one
-// LDS block each, as in k_ring_synth.
 template <int T, int G>
-__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 4 : 1))) void k_ring_analysis(RingArgs a) {
+__global__ __launch_bounds__(T * G, 2) void k_ring_analysis(RingArgs a) {
     extern __shared__ double2 sm[];
-    constexpr int nt = T / G;
-    const int sub = G == 1 ? 0 : (int)threadIdx.x / nt;
-    const int item0 = xcd_item(blockIdx.x) * G;
-    if (item0 >= a.count * a.nmaps) return;
-    const int item = item0 + sub;
+    static_assert(G == 1 || T == 64, "wavefronts are independent, larger groups are not");
+    const int sub = G == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / T);
+    const int item = xcd_item(blockIdx.x) * G + sub;
+    if (item >= a.count * a.nmaps) return;
+    double2 *buf = sm + (size_t)sub * a.fft_entries;
+    const int tid = (int)threadIdx.x - sub * T;
     const int pos = item / a.nmaps, b = item % a.nmaps;
     const int rho = a.rings[pos];
     const int J = a.ring_J[rho], s = a.ring_s[rho], M = a.ring_M[rho];
-    const int n = J / 2, lgn = ilog2_dev(n);
+    const int n = J / 2, h = n / 2;
     const bool bs = M > 0;
     const double2 *__restrict__ W = a.chirp + (bs ? a.ring_chirp_off[rho] : 0);
-    double2 *buf = G == 1 ? sm : sm + (size_t)sub * a.fft_entries;
-    const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x - sub * nt;
     const int L = a.L;
     const size_t qstride = (size_t)a.nmaps;
     double2 *yr = a.ybar + (size_t)rho * (L + 1) * a.nmaps + b;
 
     const double2 *pix = reinterpret_cast<const double2 *>(a.map_in + (size_t)b * a.npix + a.ring_off[rho]);
-    constexpr int kMPerThread = (2 * kMaxHalf + T - 1) / T;  // n / nt, or M / nt for Bluestein rings
-    constexpr int kLdMax = G == 1 && T >= 512 ? 8 : 1;  // input loads in flight per thread (registers permitting)
-    constexpr int kLd = kMPerThread < kLdMax ? kMPerThread : kLdMax;
-    constexpr int kNB = G == 1 && T >= 512 ? 8 : 1;  // chirp loads in flight (registers permitting)
     if (!bs) {
-        if (kLd == 1) {
-            for (int p = tid; p < n; p += nt) buf[pidx(bitrev(p, lgn))] = cconj(pix[p]);
-        } else {
+        constexpr int LD = 8;  // loads in flight per thread
+#pragma unroll 1
+        for (int p0 = tid; p0 < n; p0 += LD * T) {
+            double2 x[LD];
 #pragma unroll
-            for (int j0 = 0; j0 < kMPerThread; j0 += kLd) {
-                double2 x[kLd];
+            for (int j = 0; j < LD; j++) x[j] = pix[min(p0 + j * T, n - 1)];
 #pragma unroll
-                for (int j = 0; j < kLd; j++) x[j] = pix[min(tid + (j0 + j) * nt, n - 1)];
-#pragma unroll
-                for (int j = 0; j < kLd; j++) {
-                    const int p = tid + (j0 + j) * nt;
-                    if (p < n) buf[pidx(bitrev(p, lgn))] = cconj(x[j]);
-                }
-            }
+            for (int j = 0; j < LD; j++)
+                if (p0 + j * T < n) buf[pidx(p0 + j * T)] = cconj(x[j]);
         }
-        __syncthreads();
-        backward_dft<kMPerThread, kNB>(buf, n, 0, nullptr, nullptr, a.tw, a.tw_log, tid, nt);
+        group_sync<T>();
+        with_fft<T>(ilog2_dev(n), tid, buf, a, [&](auto fft) {
+            using F = decltype(fft);
+            double2 x[F::NO];
+            fft.backward(x);
+            if (fft.active()) {  // where this thread read its last pass
+#pragma unroll
+                for (int k = 0; k < F::NO; k++) buf[pidx(tid + k * F::ST)] = x[k];
+            }
+        });
     } else {
-        // split Bluestein: even inputs (hh = 0), then odd inputs (hh = 1)
-        constexpr int kHalfPerThread = (kMaxHalf + T - 1) / T;
-        constexpr int kLdH = kHalfPerThread < kLdMax ? kHalfPerThread : kLdMax;
-        const int h = n / 2;
         const double2 *__restrict__ V = a.bs_table + a.ring_bs_off[rho];
-        double2 A[kHalfPerThread];
-        for (int hh = 0; hh < 2; hh++) {
-            if (kLdH == 1) {
-                for (int p = tid; p < h; p += nt) buf[pidx(p)] = cmul(cconj(pix[2 * p + hh]), W[p]);
-            } else {
+        with_fft<T>(ilog2_dev(M), tid, buf, a, [&](auto fft) {
+            using F = decltype(fft);
+            if constexpr (F::r3 >= 3) {
+                double2 even[F::NO / 2], odd[F::NO / 2];
 #pragma unroll
-                for (int j0 = 0; j0 < kHalfPerThread; j0 += kLdH) {
-                    double2 x[kLdH], w[kLdH];
+                for (int k0 = 0; k0 < F::NO / 2; k0 += 4) {
+                    double2 x[4][2], w[4];
 #pragma unroll
-                    for (int j = 0; j < kLdH; j++) {
-                        const int pc = min(tid + (j0 + j) * nt, h - 1);
-                        x[j] = pix[2 * pc + hh];
-                        w[j] = W[pc];
+                    for (int k = 0; k < 4; k++) {
+                        const int pc = min(tid + min(k0 + k, F::NO / 2 - 1) * F::ST, h - 1);
+                        x[k][0] = pix[2 * pc];
+                        x[k][1] = pix[2 * pc + 1];
+                        w[k] = W[pc];
                     }
 #pragma unroll
-                    for (int j = 0; j < kLdH; j++) {
-                        const int p = tid + (j0 + j) * nt;
-                        if (p < h) buf[pidx(p)] = cmul(cconj(x[j]), w[j]);
+                    for (int k = k0; k < k0 + 4 && k < F::NO / 2; k++) {
+                        const bool in = tid + k * F::ST < h;
+                        even[k] = keep(cmul(cconj(x[k - k0][0]), w[k - k0]), in);
+                        odd[k] = keep(cmul(cconj(x[k - k0][1]), w[k - k0]), in);
+                    }
+                }
+                double2 z0[F::NO / 2], z1[F::NO / 2];
+                fft.bluestein(even, odd, n, V, W, [&](int p, double2 zp, double2 zph) {
+                    z0[(p - tid) / F::ST] = zp;
+                    z1[(p - tid) / F::ST] = zph;
+                });
+                group_sync<T>();  // the last pass has been read
+#pragma unroll
+                for (int k = 0; k < F::NO / 2; k++) {
+                    const int p = tid + k * F::ST;
+                    if (fft.active() && p < h) {
+                        buf[pidx(p)] = z0[k];
+                        buf[pidx(p + h)] = z1[k];
                     }
                 }
             }
-            __syncthreads();
-            backward_dft<kMPerThread, kNB>(buf, h, M, V, W, a.tw, a.tw_log, tid, nt);
-            if (hh == 0) {
-#pragma unroll
-                for (int jj = 0; jj < kHalfPerThread; jj++) {
-                    const int p = tid + jj * nt;
-                    if (p < h) A[jj] = buf[pidx(p)];
-                }
-                __syncthreads();
-            }
-        }
-        // Z_p = A_p + w^p B_p and Z_{p+h} = A_p - w^p B_p in place (each
-        // thread reads B_p before writing p and p + h, which no other thread
-        // reads)
-        double2 wp = expipi(2.0 * tid / n);  // e^{2 pi i p/n}, stepped by products
-        const double2 ws = expipi(2.0 * nt / n);
-#pragma unroll
-        for (int jj = 0; jj < kHalfPerThread; jj++) {
-            const int p = tid + jj * nt;
-            if (p < h) {
-                const double2 t = cmul(buf[pidx(p)], wp);
-                buf[pidx(p)] = cadd(A[jj], t);
-                buf[pidx(p + h)] = csub(A[jj], t);
-            }
-            wp = cmul(wp, ws);
-        }
-        __syncthreads();
+        });
     }
+    group_sync<T>();
 
     // bins b = 0..n, split over NG groups of the residue classes for small rings
     const int nb = n + 1;
-    const int NG = nb >= nt ? 1 : nt / nb;
-    // e^{-i pi bin/n} and e^{-i pi bin/J}: with NG = 1 a thread's bins are
-    // tid + j nt, stepped by products; with NG > 1 each thread has one bin
-    const int bin0 = tid % nb;
-    double2 qn = expipi(-(double)bin0 / n), qJ = s ? expipi(-(double)bin0 / J) : make_double2(1.0, 0.0);
-    const double2 sn = expipi(-(double)nt / n), sJ = s ? expipi(-(double)nt / J) : make_double2(1.0, 0.0);
-    for (int u = tid; u < NG * nb; u += nt) {
+    const int NG = nb >= T ? 1 : T / nb;
+    // e^{-i pi bin/n} and e^{-i pi bin/J}: exact every fourth bin of a thread,
+    // stepped by products between (with NG > 1 a thread has one bin)
+    const double2 sn = expipi(-(double)T / n), sJ = s ? expipi(-(double)T / J) : make_double2(1.0, 0.0);
+    double2 qn, qJ;
+    int turn = 0;
+    for (int u = tid; u < NG * nb; u += T, turn++) {
         const int g = u / nb, bin = u % nb;
+        if ((turn & 3) == 0) {
+            qn = expipi(-(double)bin / n);
+            qJ = s ? expipi(-(double)bin / J) : make_double2(1.0, 0.0);
+        }
         const double2 Zb = cconj(buf[pidx(bin == n ? 0 : bin)]);
         const double2 Znb = cconj(buf[pidx(bin == 0 ? 0 : n - bin)]);
         // F_b = (Z_b + conj Z_{n-b})/2 - (i/2) e^{-2 pi i b/J} (Z_b - conj Z_{n-b})
@@ -893,35 +800,86 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(T == 512 ? 4 
     }
 }
 
-template <int T>
-static hipError_t launch_analysis_classes(const sht_plan_s *p, RingArgs a, int nmaps, hipStream_t stream) {
-    const void *fn[3] = {(const void *)k_ring_analysis<T, 1>, (const void *)k_ring_analysis<T, 2>,
-                         (const void *)k_ring_analysis<T, 4>};
-    for (const void *f : fn) {
-        hipError_t ea = allow_dynamic_lds(f, 160 * 1024);
-        if (ea != hipSuccess) return ea;
-    }
-    for (const auto &rc : p->classes) {
-        a.rings = rc.d_rings;
-        a.count = (int)rc.rings.size();
-        a.fft_entries = rc.lds_entries + rc.lds_entries / 16;
-        a.mpw = ring_maps_per_wg(rc.lds_entries, nmaps);
-        long long grid = ((long long)a.count * nmaps / a.mpw + 63) / 64 * 64;
-        size_t lds = (size_t)a.mpw * a.fft_entries * sizeof(double2);
-        switch (a.mpw) {
-            case 1: hipLaunchKernelGGL((k_ring_analysis<T, 1>), dim3((unsigned)grid), dim3(T), lds, stream, a); break;
-            case 2: hipLaunchKernelGGL((k_ring_analysis<T, 2>), dim3((unsigned)grid), dim3(T), lds, stream, a); break;
-            default: hipLaunchKernelGGL((k_ring_analysis<T, 4>), dim3((unsigned)grid), dim3(T), lds, stream, a); break;
+// Raises a kernel's dynamic LDS limit to `bytes`, once per (kernel, device):
+// the attribute belongs to the device current at the call.
+hipError_t allow_dynamic_lds(const void *fn, int bytes) {
+    static std::mutex mu;
+    static std::set<std::pair<const void *, int>> done;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lk(mu);
+    if (done.count({fn, dev})) return hipSuccess;
+    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+    if (e == hipSuccess) done.insert({fn, dev});
+    return e;
+}
+
+// LDS entries of a thread group of T for transforms of up to S points: the
+// padded points, at least the 2 T partial bin sums of a short ring.
+int ring_group_entries(int S, int T) { return std::max(S + S / 16, 2 * T); }
+
+template <int T, int G>
+static hipError_t launch_set(bool adj, const RingArgs &a, hipStream_t st) {
+    const void *fn = adj ? (const void *)k_ring_analysis<T, G> : (const void *)k_ring_synth<T, G>;
+    hipError_t e = allow_dynamic_lds(fn, 160 * 1024);
+    if (e != hipSuccess) return e;
+    const size_t lds = (size_t)G * a.fft_entries * sizeof(double2);
+    const long long grid = ((long long)a.count * a.nmaps / G + 63) / 64 * 64;
+    if (adj) hipLaunchKernelGGL((k_ring_analysis<T, G>), dim3((unsigned)grid), dim3(T * G), lds, st, a);
+    else hipLaunchKernelGGL((k_ring_synth<T, G>), dim3((unsigned)grid), dim3(T * G), lds, st, a);
+    return hipGetLastError();
+}
+
+// One launch per ring size class.
+static hipError_t launch_sets(const sht_plan_s *p, bool adj, RingArgs a, hipStream_t st) {
+    for (const auto &rs : p->ring_sets) {
+        if (rs.rings.empty()) continue;
+        a.rings = rs.d_rings;
+        a.count = (int)rs.rings.size();
+        a.fft_entries = ring_group_entries(rs.max_size, rs.threads);
+        hipError_t e;
+        switch (rs.threads) {
+            case 64:
+                e = a.nmaps % 4 == 0 ? launch_set<64, 4>(adj, a, st)
+                                     : a.nmaps % 2 == 0 ? launch_set<64, 2>(adj, a, st) : launch_set<64, 1>(adj, a, st);
+                break;
+            case 128: e = launch_set<128, 1>(adj, a, st); break;
+            default: e = launch_set<256, 1>(adj, a, st); break;
         }
-        hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-hipError_t launch_ring_analysis(const sht_plan_s *p, int nmaps, const double *map, double *ybar,
-                                double wpos, hipStream_t stream) {
+static const void *ring_queue_kernel(int T) {
+    return T == 64 ? (const void *)k_ring_synth_queue<64>
+                   : T == 128 ? (const void *)k_ring_synth_queue<128> : (const void *)k_ring_synth_queue<256>;
+}
+
+// Raises the ring queue kernel's LDS limit on the current device (done at
+// batch creation, so that runs make no runtime calls besides launches).
+hipError_t ring_queue_prepare(int T) { return allow_dynamic_lds(ring_queue_kernel(T), 160 * 1024); }
+
+hipError_t launch_ring_queue(int T, const RingArgs *args, const int2 *items, long long nitems, size_t lds,
+                             hipStream_t st) {
+    if (nitems < 0 || nitems > 0x7fffffffLL) return hipErrorInvalidValue;
+    hipError_t e = ring_queue_prepare(T);
+    if (e != hipSuccess || nitems == 0) return e;
+    const dim3 grid((unsigned)((nitems + 63) / 64 * 64));
+    switch (T) {
+        case 64: hipLaunchKernelGGL(k_ring_synth_queue<64>, grid, dim3(T), lds, st, args, items, (int)nitems); break;
+        case 128: hipLaunchKernelGGL(k_ring_synth_queue<128>, grid, dim3(T), lds, st, args, items, (int)nitems); break;
+        default: hipLaunchKernelGGL(k_ring_synth_queue<256>, grid, dim3(T), lds, st, args, items, (int)nitems); break;
+    }
+    return hipGetLastError();
+}
+
+// Plan-wide fields of the ring argument block (synthesis direction); the
+// caller sets the class fields (rings, count, fft_entries).
+RingArgs ring_args(const sht_plan_s *p, int nmaps, const double *q, double *map) {
     RingArgs a;
+    std::memset(&a, 0, sizeof(a));
     a.ring_J = p->d_ring_J;
     a.ring_s = p->d_ring_s;
     a.ring_M = p->d_ring_M;
@@ -932,21 +890,27 @@ hipError_t launch_ring_analysis(const sht_plan_s *p, int nmaps, const double *ma
     a.bs_table = reinterpret_cast<const double2 *>(p->d_bs_table);
     a.chirp = reinterpret_cast<const double2 *>(p->d_chirp);
     a.ring_chirp_off = p->d_ring_chirp_off;
-    a.q = nullptr;
-    a.map = nullptr;
-    a.map_in = map;
-    a.ybar = reinterpret_cast<double2 *>(ybar);
-    a.wpos = wpos;
+    a.q = reinterpret_cast<const double2 *>(q);
+    a.map = map;
     a.L = p->L;
     a.nrings = p->nrings;
     a.nmaps = nmaps;
     a.npix = 12LL * p->nside * p->nside;
-    a.stage = 0;
-    switch (p->ring_threads) {
-        case 256: return launch_analysis_classes<256>(p, a, nmaps, stream);
-        case 512: return launch_analysis_classes<512>(p, a, nmaps, stream);
-        default: return launch_analysis_classes<1024>(p, a, nmaps, stream);
-    }
+    return a;
+}
+
+hipError_t launch_ring_synthesis(const sht_plan_s *p, int nmaps, const double *q, double *map,
+                                 hipStream_t stream) {
+    return launch_sets(p, false, ring_args(p, nmaps, q, map), stream);
+}
+
+hipError_t launch_ring_analysis(const sht_plan_s *p, int nmaps, const double *map, double *ybar,
+                                double wpos, hipStream_t stream) {
+    RingArgs a = ring_args(p, nmaps, nullptr, nullptr);
+    a.map_in = map;
+    a.ybar = reinterpret_cast<double2 *>(ybar);
+    a.wpos = wpos;
+    return launch_sets(p, true, a, stream);
 }
 
 }  // namespace sht
