@@ -25,12 +25,19 @@
 // evaluated directly instead: the Wigner-d three-term recurrence in l,
 //   _s lambda_{l+1} = A_l (c + m s/(l(l+1))) _s lambda_l - (A_l / A_{l-1}) _s lambda_{l-1},
 //   A_l = sqrt((2l+3)(2l+1)(l+1)^2 / (((l+1)^2 - m^2)((l+1)^2 - s^2))),
-// in double-double arithmetic (the z-based recurrence loses ~l eps / s in
-// FP64) from Goldberg's closed form at l0 = max(m, 2), with the plan's
-// per-(m, s) start factors; one wave per (m, 64 polar rings), both
-// hemispheres from one recurrence (_s lambda(pi - theta) =
-// (-1)^(l+m) _{-s} lambda(theta)).
+// from Goldberg's closed form at l0 = max(m, 2), with the plan's per-(m, s)
+// start factors.  Evaluated as written it loses ~l eps / s in FP64, so it runs
+// split about its solution at the pole, as the scalar one does there
+// (legendre.hip): with r_l the ratio of _s lambda_{l+1} to _s lambda_l at
+// theta -> 0 and v = 1 - c = 2 sin^2(theta/2),
+//   _s lambda_{l+1} = r_l _s lambda_l + d_l,
+//   d_l = A_l / (A_{l-1} r_{l-1}) d_{l-1} - A_l v _s lambda_l,
+//   r_l^2 = (2l+3)/(2l+1) (l+1+M)(l+1-M') / ((l+1-M)(l+1+M')),
+// {M, M'} = {m, -s}, the larger first.  One workgroup per (m, 64 polar rings),
+// one wave per s; both hemispheres from one recurrence
+// (_s lambda(pi - theta) = (-1)^(l+m) _{-s} lambda(theta)).
 #include "ddmath.h"
+#include "dpp.h"
 #include "internal.h"
 
 namespace sht {
@@ -121,13 +128,6 @@ struct PolArgs {
     int L, nrings, pol_n, ng, ngp, n, map0;  // ng: the plan's 64-ring groups, ngp: polar groups
 };
 
-__device__ __forceinline__ double rdl(double x, int j) {  // lane j's x (j wave-uniform)
-    const long long v = __double_as_longlong(x);
-    const int lo = __builtin_amdgcn_readlane((int)(v & 0xffffffffLL), j);
-    const int hi = __builtin_amdgcn_readlane((int)(v >> 32), j);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
 // mant * base^p with exponent tracking (mant kept in [0.5, 1) by powers of 2)
 __device__ __forceinline__ void dd_pow_acc(dd &mant, int &e, dd base, int p) {
     int eb;
@@ -150,27 +150,49 @@ __device__ __forceinline__ void dd_pow_acc(dd &mant, int &e, dd base, int p) {
     }
 }
 
+// A_l and r_l of the file's head
+__device__ __forceinline__ dd pol_A(double l, double mm) {
+    const double q = l + 1.0;
+    return dd_sqrt(dd_div(dd{(2.0 * l + 3.0) * (2.0 * l + 1.0) * q * q, 0.0}, dd{(q * q - mm) * (q * q - 4.0), 0.0}));
+}
+__device__ __forceinline__ dd pol_r(double l, double M, double M1) {
+    const double q = l + 1.0;
+    return dd_sqrt(dd_div(dd{(2.0 * l + 3.0) * (q + M) * (q - M1), 0.0}, dd{(2.0 * l + 1.0) * (q - M) * (q + M1), 0.0}));
+}
+
+// Rows of 64 degrees at a time are staged in the wave's LDS: E and B of NB
+// maps (4 NB values) and the three coefficients, read by DPP row broadcasts.
+// Values are held as p 2^(300 S), S <= 0, checked every 8 steps (a step grows
+// them by less than 2^13); those with S < 0 are below 2^-180 and left out of
+// the sums.  The recurrence is a serial chain of Lp - l0 steps of about four
+// dependent operations; in double-double arithmetic (one wave for both s) it
+// took 530 us at L = 1023 for one map.
+constexpr int kPolRows = 64;
+
 template <int NB>
-__global__ __launch_bounds__(64) void k_pol_polar(PolArgs a) {
+__global__ __launch_bounds__(128) void k_pol_polar(PolArgs a) {
+    constexpr int NV = 4 * NB, CW = 16;
+    static_assert(NV + 3 <= CW, "a row holds the values of NB maps and the coefficients");
+    __shared__ __attribute__((aligned(16))) double lds[2][kPolRows * CW];
     const int m = blockIdx.x / a.ngp, g = blockIdx.x % a.ngp;
-    const int L = a.L, Lp = L - 1, lane = threadIdx.x;
-    if (m > Lp) return;
-    const int n0 = (L - m) / 2 + 1;
+    const int L = a.L, Lp = L - 1;
+    const int si = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int lo = a.grp_lo[(size_t)m * a.ng + g];
-    if (lo >= n0) return;  // every chain of this group stays below the cutoff: the combination wrote 0
+    if (lo >= (L - m) / 2 + 1) return;  // every chain of this group stays below the cutoff: the combination wrote 0
     const int k = g * 64 + lane;
     const bool act = k < a.pol_n;
     const int kk = act ? k : a.pol_n - 1;
-    const dd z = {a.ring[6 * kk], a.ring[6 * kk + 1]};
     const dd sh = {a.ring[6 * kk + 2], a.ring[6 * kk + 3]};
     const dd chh = {a.ring[6 * kk + 4], a.ring[6 * kk + 5]};
+    const double v = 2.0 * dd_mul(sh, sh).h;
     const int l0 = m > 2 ? m : 2;
-    // start values and exponents of s = +2 (index 0) and s = -2 (index 1)
-    dd p0[2], p1[2];  // lambda_{l-1}, lambda_l (scaled by 2^-E)
-    int Ex[2];
-#pragma unroll
-    for (int si = 0; si < 2; si++) {
-        const int s = si == 0 ? 2 : -2;
+    const int s = si == 0 ? 2 : -2;
+    double *rows = lds[si];
+
+    // start value and its power of two
+    double P0;
+    int S;
+    {
         const int r = m - s > 0 ? m - s : 0;
         const int pc = 2 * r + s - m, ps = 2 * l0 - pc;
         const double *Kp = a.K + ((size_t)m * 2 + si) * 4;
@@ -178,97 +200,106 @@ __global__ __launch_bounds__(64) void k_pol_polar(PolArgs a) {
         int e = (int)Kp[2];
         dd_pow_acc(mant, e, chh, pc);
         dd_pow_acc(mant, e, sh, ps);
-        p0[si] = {0.0, 0.0};
-        p1[si] = mant;
-        Ex[si] = e;
+        S = e >= 0 ? 0 : -(-e / 300);
+        P0 = ldexp(mant.h, e - 300 * S);
     }
-    // accumulators per map: [parity of l - m][E F1, B F2, B F1, E F2] complex
-    double acc[NB][2][4][2];
+    const double mm = (double)m * m, M = m > -s ? m : -s, M1 = m > -s ? -s : m;
+    double P1 = -(pol_A((double)l0, mm).h * v) * P0;  // d at l0
+    double live = S == 0 ? 1.0 : 0.0;
+    bool dead = __any(S < 0);
+
+    double acc[2][NV];  // by parity of l - l0: sums of E and B (re, im) of each map
 #pragma unroll
-    for (int b = 0; b < NB; b++)
-#pragma unroll
-        for (int pp = 0; pp < 2; pp++)
-#pragma unroll
-            for (int q = 0; q < 4; q++) acc[b][pp][q][0] = acc[b][pp][q][1] = 0.0;
+    for (int q = 0; q < NV; q++) acc[0][q] = acc[1][q] = 0.0;
     const size_t offi = (size_t)m * (2 * Lp + 3 - m) / 2;
-    const double mm = (double)m * m;
-    for (int lb = l0; lb <= Lp; lb += 64) {
-        // recurrence coefficients of steps l -> l + 1, l = lb + lane
-        const int l = lb + lane;
-        const double lp = l + 1.0;
-        auto Asq = [&](double ll) {  // A_{ll}^2 as an exact ratio, ll = l
-            const double q = ll + 1.0;
-            return dd_div(dd{(2.0 * ll + 3.0) * (2.0 * ll + 1.0) * q * q, 0.0},
-                          dd{(q * q - mm) * (q * q - 4.0), 0.0});
-        };
-        const dd A = dd_sqrt(Asq((double)l));
-        const dd Bc = (l == l0) ? dd{0.0, 0.0} : dd_div(A, dd_sqrt(Asq((double)l - 1.0)));
-        const dd C = dd_div(dd{2.0 * m, 0.0}, dd{(double)l * lp, 0.0});  // m s / (l(l+1)), s = +2
-        const double Ah = A.h, Al = A.l, Bh = Bc.h, Bl = Bc.l, Ch = C.h, Cl = C.l;
-        const int steps = min(64, Lp - lb + 1);
-        for (int j = 0; j < steps; j++) {
-            const int lc = lb + j;
-            const int par = (lc - m) & 1;
-            // accumulate l = lc
-            const double fp = ldexp(p1[0].h, max(Ex[0], -4000)), fm = ldexp(p1[1].h, max(Ex[1], -4000));
-            const double F1 = 0.5 * (fp + fm), F2 = 0.5 * (fp - fm);
-            const double *Er = a.E + 2 * ((offi + lc - m) * a.n + a.map0);
-            const double *Br = a.B + 2 * ((offi + lc - m) * a.n + a.map0);
+    double2 pe[NB], pb[NB];
+    auto fetch = [&](int lb) {  // rows lb .. lb + 63, clamped to Lp (rows past it are staged as zeros)
+        const size_t at = (offi + min(lb + lane, Lp) - m) * a.n + a.map0;
 #pragma unroll
-            for (int b = 0; b < NB; b++) {
-                const double er = Er[2 * b], ei = m ? Er[2 * b + 1] : 0.0;
-                const double br = Br[2 * b], bi = m ? Br[2 * b + 1] : 0.0;
-                acc[b][par][0][0] = __builtin_fma(er, F1, acc[b][par][0][0]);
-                acc[b][par][0][1] = __builtin_fma(ei, F1, acc[b][par][0][1]);
-                acc[b][par][1][0] = __builtin_fma(br, F2, acc[b][par][1][0]);
-                acc[b][par][1][1] = __builtin_fma(bi, F2, acc[b][par][1][1]);
-                acc[b][par][2][0] = __builtin_fma(br, F1, acc[b][par][2][0]);
-                acc[b][par][2][1] = __builtin_fma(bi, F1, acc[b][par][2][1]);
-                acc[b][par][3][0] = __builtin_fma(er, F2, acc[b][par][3][0]);
-                acc[b][par][3][1] = __builtin_fma(ei, F2, acc[b][par][3][1]);
+        for (int b = 0; b < NB; b++) {
+            pe[b] = reinterpret_cast<const double2 *>(a.E)[at + b];
+            pb[b] = reinterpret_cast<const double2 *>(a.B)[at + b];
+        }
+    };
+    fetch(l0);
+    for (int lb = l0; lb <= Lp; lb += kPolRows) {
+        double2 *row = reinterpret_cast<double2 *>(rows + lane * CW);
+#pragma unroll
+        for (int b = 0; b < NB; b++) {
+            row[2 * b] = pe[b];
+            row[2 * b + 1] = pb[b];
+        }
+        if (lb + lane > Lp) {
+#pragma unroll
+            for (int q = 0; q < NV / 2; q++) row[q] = make_double2(0.0, 0.0);
+        }
+        {
+            // step l: lambda_{l+1} = r_l lambda_l + d_l, then d_{l+1}
+            const double l = lb + lane;
+            const dd A = pol_A(l, mm), A1 = pol_A(l + 1.0, mm), r = pol_r(l, M, M1);
+            double *c = rows + lane * CW + NV;
+            c[0] = dd_div(A1, dd_mul(A, r)).h;
+            c[1] = -A1.h;
+            c[2] = r.h;
+        }
+        fetch(lb + kPolRows);
+        const int steps = min(kPolRows, Lp - lb + 1);
+        for (int j = 0; j < steps; j += 8) {
+            double rv[8];
+#pragma unroll
+            for (int u = 0; u < 8; u++) rv[u] = rows[(j + u) * CW + (lane & 15)];
+#pragma unroll
+            for (int u = 0; u < 8; u++) {
+                const double h = row_bcast<NV>(rv[u]), nA = row_bcast<NV + 1>(rv[u]), r = row_bcast<NV + 2>(rv[u]);
+                fmac_row_bcast<NV>(acc[u & 1], rv[u], dead ? P0 * live : P0);
+                const double nx = __builtin_fma(r, P0, P1);
+                P1 = __builtin_fma(h, P1, (nA * v) * nx);
+                P0 = nx;
             }
-            if (lc == Lp) break;
-            // advance to lc + 1
-            const dd Aj = {rdl(Ah, j), rdl(Al, j)}, Bj = {rdl(Bh, j), rdl(Bl, j)}, Cj = {rdl(Ch, j), rdl(Cl, j)};
-#pragma unroll
-            for (int si = 0; si < 2; si++) {
-                const dd w = dd_mul(Aj, dd_add(z, si == 0 ? Cj : dd_neg(Cj)));
-                const dd nx = dd_sub(dd_mul(w, p1[si]), dd_mul(Bj, p0[si]));
-                p0[si] = p1[si];
-                p1[si] = nx;
-                if (fabs(nx.h) > 0x1p300) {
-                    p0[si] = {ldexp(p0[si].h, -300), ldexp(p0[si].l, -300)};
-                    p1[si] = {ldexp(p1[si].h, -300), ldexp(p1[si].l, -300)};
-                    Ex[si] += 300;
+            if (dead) {
+                if (S < 0 && fabs(P0) > 1.0) {
+                    P0 = ldexp(P0, -300);
+                    P1 = ldexp(P1, -300);
+                    S++;
                 }
+                live = S == 0 ? 1.0 : 0.0;
+                dead = __any(S < 0);
             }
         }
     }
+    // Even and odd l - m: the north sum of this s, and the south sum of -s.
+    // Wave 0 writes the north ring, wave 1 its mirror.
+    const bool odd0 = (l0 - m) & 1;
+    double north[NV], south[NV];
+#pragma unroll
+    for (int q = 0; q < NV; q++) {
+        north[q] = acc[0][q] + acc[1][q];
+        south[q] = odd0 ? acc[1][q] - acc[0][q] : acc[0][q] - acc[1][q];
+        rows[q * 64 + lane] = si == 0 ? south[q] : north[q];
+    }
+    __syncthreads();
     if (!act) return;
-    const int ks = a.nrings - 1 - k;
+    // sums over s = +2 (p) and -2 (q) at this wave's ring: F1 = (p + q)/2, F2 = (p - q)/2
+    const double *other = lds[1 - si];
+    const int ring = si == 0 ? k : a.nrings - 1 - k;
+    double2 *o = reinterpret_cast<double2 *>(a.q2) + ((size_t)ring * (L + 1) + m) * 2 * a.n + a.map0;
 #pragma unroll
     for (int b = 0; b < NB; b++) {
-        // north: parity sums added; south: F1 -> (-1)^(l+m) F1, F2 -> -(-1)^(l+m) F2
-        double s[2][4][2];
+        double F1[4], F2[4];  // E re, im, B re, im
 #pragma unroll
-        for (int q = 0; q < 4; q++)
-#pragma unroll
-            for (int c = 0; c < 2; c++) {
-                s[0][q][c] = acc[b][0][q][c] + acc[b][1][q][c];
-                const double d = acc[b][0][q][c] - acc[b][1][q][c];
-                s[1][q][c] = (q == 0 || q == 2) ? d : -d;
-            }
-#pragma unroll
-        for (int h = 0; h < 2; h++) {
-            // Q = -(sum E F1 + i sum B F2), U = -(sum B F1 - i sum E F2)
-            double2 Q = make_double2(-s[h][0][0] + s[h][1][1], -s[h][0][1] - s[h][1][0]);
-            double2 U = make_double2(-s[h][2][0] - s[h][3][1], -s[h][2][1] + s[h][3][0]);
-            if (m == 0) Q.y = U.y = 0.0;
-            const int ring = h == 0 ? k : ks;
-            double2 *o = reinterpret_cast<double2 *>(a.q2) + ((size_t)ring * (L + 1) + m) * 2 * a.n;
-            o[a.map0 + b] = Q;
-            o[a.n + a.map0 + b] = U;
+        for (int c = 0; c < 4; c++) {
+            // north: own is s = +2; south: own (s = -2's sums) stands for +2
+            const double p = si == 0 ? north[4 * b + c] : south[4 * b + c], q = other[(4 * b + c) * 64 + lane];
+            F1[c] = 0.5 * (p + q);
+            F2[c] = 0.5 * (p - q);
+            if (m == 0 && (c & 1)) F1[c] = F2[c] = 0.0;  // real fields
         }
+        // Q = -(sum E F1 + i sum B F2), U = -(sum B F1 - i sum E F2)
+        double2 Q = make_double2(-F1[0] + F2[3], -F1[1] - F2[2]);
+        double2 U = make_double2(-F1[2] - F2[1], -F1[3] + F2[0]);
+        if (m == 0) Q.y = U.y = 0.0;
+        o[b] = Q;
+        o[a.n + b] = U;
     }
 }
 
@@ -307,13 +338,15 @@ hipError_t launch_pol_polar(const sht_plan_s *p, int nmaps, const double *E, con
     a.ngp = (p->pol_n + 63) / 64;
     hipError_t e = hipSuccess;
     for (int b = 0; b < nmaps && e == hipSuccess;) {
-        const int nb = nmaps - b >= 2 ? 2 : 1;
+        const int nb = nmaps - b == 4 ? 2 : std::min(nmaps - b, 3);
         a.map0 = b;
         const dim3 grid((unsigned)(p->L * a.ngp));  // orders 0 .. L-1 x polar groups
-        if (nb == 2)
-            hipLaunchKernelGGL(k_pol_polar<2>, grid, dim3(64), 0, st, a);
+        if (nb == 3)
+            hipLaunchKernelGGL(k_pol_polar<3>, grid, dim3(128), 0, st, a);
+        else if (nb == 2)
+            hipLaunchKernelGGL(k_pol_polar<2>, grid, dim3(128), 0, st, a);
         else
-            hipLaunchKernelGGL(k_pol_polar<1>, grid, dim3(64), 0, st, a);
+            hipLaunchKernelGGL(k_pol_polar<1>, grid, dim3(128), 0, st, a);
         e = hipGetLastError();
         b += nb;
     }
