@@ -369,15 +369,6 @@ constexpr int adj_wave_lds(int NS, int R) {
 }
 constexpr int adj_sums(int NS) { return 4 * kAdjSteps * NS; }
 
-// x + the value of the lane N to the right, cyclic within each row of 16
-template <int N>
-__device__ __forceinline__ double row_ror_add(double x) {
-    const long long v = __builtin_bit_cast(long long, x);
-    const int lo = __builtin_amdgcn_mov_dpp((int)v, 0x120 + N, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), 0x120 + N, 0xF, 0xF, false);
-    return x + __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
-}
-
 // One wave's share of the kAdjSteps steps from c on: the recurrence of its R
 // ring groups, the products with their phases Y, and the sums of its rings.
 template <int NS, int R, bool POLE>

@@ -142,16 +142,23 @@ __device__ __forceinline__ void id_block(const BfArgs<S> &a, int node, int ch, i
 
 // One residual piece on one wave: R rings per lane (lane j: rings j + 64 r,
 // lane records from lbase), rows [imin, iend) of one parity, outputs at
-// entries outb + ring.  The a_lm rows and recurrence coefficients of each
-// aligned chunk of kChunk rows are fetched one chunk ahead with coalesced
-// vector loads and staged in the wave's own LDS slot (stg: two chunks) as
-// rows of 16 (NC <= 13) or 32 values: a_lm components, then B, AB and G.
-// Lane k of every 16-lane row reads value k of a row, and the products take
-// the values from there by DPP broadcasts; LDS operations of one wave
-// complete in order, so no barrier is needed.
+// entries outb + ring.  The scaled recurrence of legendre.hip (two FP64
+// operations a step, f_l in the staged a_lm).  The a_lm rows and recurrence
+// coefficients of each aligned chunk of kChunk rows are fetched one chunk
+// ahead with coalesced vector loads and staged in the wave's own LDS slot
+// (stg: two chunks) as rows of 16 (NC <= 14) or 32 values: a_lm components,
+// then the two coefficients.  Lane k of every 16-lane row reads value k of a
+// row, and the products take the values from there by DPP broadcasts; LDS
+// operations of one wave complete in order, so no barrier is needed.  The
+// loads are unconditional, of rows clamped into [imin, iend), and rows outside
+// are overwritten with zeros in LDS: a select on a load would become a branch
+// that waits for memory, twice a chunk.  Residual launch at L = 2047, before
+// and now: 4 maps 781 and 793 us, with FP32 results 808 and 696 us; 8 maps 1455
+// and 1425 us.  FP64 issue bounds it (one wavefront or four a workgroup: the
+// same within 2%).
 template <int NB>
 constexpr int bf_res_row_doubles() {
-    return 2 * NB + 3 <= 16 ? 16 : 32;
+    return 2 * NB + 2 <= 16 ? 16 : 32;
 }
 template <int NB>
 constexpr int bf_res_stage_doubles() {
@@ -161,13 +168,14 @@ constexpr int bf_res_stage_doubles() {
 template <int NB, int R, typename S>
 __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict__ slot, long long lbase, int lane,
                                               int t, int imin, int iend, int nl, int outb,
-                                              const double *__restrict__ ap, const double *__restrict__ cfs,
+                                              const double *__restrict__ ap, const double4 *__restrict__ sc,
                                               int astride, double *stg, int col0) {
     constexpr int NC = 2 * NB;
     constexpr int CW = bf_res_row_doubles<NB>();  // staged values per row
     constexpr int CS = kChunk * CW;                // doubles per staged chunk
     constexpr int E = CS / 64;                     // staged doubles per lane
-    constexpr int CO = NC < 16 ? NC : 0;           // lane of B within its 16-lane group
+    constexpr int CO = NC % 16;                    // lane of b within its 16-lane row
+    static_assert(NC + 2 <= 16 || NC == 16, "the coefficients share one 16-lane row");
     int i0[R];
     double z2[R], v0[R], v1[R], P0[R], P1[R], acc[R][NC];
 #pragma unroll
@@ -183,46 +191,52 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
 #pragma unroll
         for (int c = 0; c < NC; c++) acc[r][c] = 0.0;
     }
-    // Chunk loads without branches: every lane loads from a row clamped into
-    // [imin, iend) and keeps zero where the row or the component lies outside,
-    // so that a chunk's whole update is one basic block the compiler cannot
-    // reorder around branches.
-    double pre[E];
-    auto fetch = [&](int c0) {
-#pragma unroll
-        for (int e = 0; e < E; e++) {
-            const int idx = lane + 64 * e, ir = c0 + idx / CW, comp = idx % CW;
-            const int i = min(ir, iend - 1);
-            const double *p = comp < NC ? ap + (size_t)i * astride + comp
-                                        : cfs + 4 * (t + 2 * i + 2) + min(comp - NC, 2);
-            const double v = *p;
-            pre[e] = (ir < iend && comp < NC + 3) ? v : 0.0;
-        }
-    };
-    auto stage = [&](int sl) {
-#pragma unroll
-        for (int e = 0; e < E; e++) stg[sl * CS + lane + 64 * e] = pre[e];
-    };
     auto step_v = [&](double rv, double rc) {
-        const double eb = row_bcast<CO>(rc), eab = row_bcast<CO + 1>(rc), eg = row_bcast<CO + 2>(rc);
+        const double eb = row_bcast<CO>(rc), ea = row_bcast<CO + 1>(rc);
 #pragma unroll
         for (int r = 0; r < R; r++) {
             fmac_row_bcast<NC>(acc[r], rv, P0[r]);
-            const double P2 = __builtin_fma(__builtin_fma(z2[r], eb, eab), P1[r], eg * P0[r]);
+            const double P2 = __builtin_fma(__builtin_fma(z2[r], eb, ea), P1[r], -P0[r]);
             P0[r] = P1[r];
             P1[r] = P2;
         }
     };
-    auto step = [&](const double *row) {
-        const double rv = row[lane & 15];
-        step_v(rv, CW == 16 ? rv : row[16 + (lane & 15)]);
-    };
     // a piece without rows (a parity with no l <= L) writes zeros and loads
     // nothing: its clamped row iend - 1 would lie outside the order's rows
     if (imin < iend) {
+        const int comp = lane % CW;
+        const bool is_a = comp < NC;
+        const double *base = is_a ? ap + comp : reinterpret_cast<const double *>(sc + t + 2) + min(comp - NC, 1);
+        const unsigned stride = is_a ? (unsigned)astride : 8u;
+        const double *fb = reinterpret_cast<const double *>(sc + t) + 2;
+        const double f1 = is_a ? 1.0 : 0.0, f0 = 1.0 - f1;  // factor of a staged value: f_l, or 1
+        double pre[E], fac[E];
+        auto fetch = [&](int c0) {
+#pragma unroll
+            for (int e = 0; e < E; e++) {
+                const unsigned i = (unsigned)min(c0 + (lane + 64 * e) / CW, iend - 1);
+                pre[e] = base[(size_t)i * stride];
+                fac[e] = fb[8 * (size_t)i];
+            }
+        };
+        auto stage = [&](int sl, int c0) {
+#pragma unroll
+            for (int e = 0; e < E; e++) stg[sl * CS + lane + 64 * e] = pre[e] * __builtin_fma(fac[e], f1, f0);
+            if (c0 + kChunk > iend) {
+#pragma unroll
+                for (int e = 0; e < E; e++)
+                    if (c0 + (lane + 64 * e) / CW >= iend) stg[sl * CS + lane + 64 * e] = 0.0;
+            }
+        };
         int c0 = imin & ~(kChunk - 1), sl = 0;
         fetch(c0);
-        stage(0);
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int i = i0[r] < iend ? i0[r] : imin;
+            v0[r] *= sc[t + 2 * i].w;
+            v1[r] *= sc[t + 2 * i + 2].w;
+        }
+        stage(0, c0);
         fetch(c0 + kChunk);
         // The rings that start at imin; a first chunk that begins before imin
         // runs row by row, every later chunk as eight unrolled steps (rows past
@@ -235,8 +249,12 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
             }
         if (c0 != imin) {
             const int ce = min(iend, c0 + kChunk);
-            for (int i = imin; i < ce; i++) step(stg + (i - c0) * CW);
-            stage(1);
+            for (int i = imin; i < ce; i++) {
+                const double *row = stg + (i - c0) * CW + (lane & 15);
+                const double rv = row[0];
+                step_v(rv, CW == 16 ? rv : row[16]);
+            }
+            stage(1, c0 + kChunk);
             fetch(c0 + 2 * kChunk);
             c0 += kChunk;
             sl = 1;
@@ -248,18 +266,21 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
                 P0[r] = st ? v0[r] : P0[r];
                 P1[r] = st ? v1[r] : P1[r];
             }
-            // the chunk's rows are read at once (one or two values per lane
-            // and row), so that their LDS latency is paid once per chunk
+            // four rows are read at once (one or two values per lane and row),
+            // so that their LDS latency is paid twice per chunk
             const double *cur = stg + sl * CS + (lane & 15);
-            double rv[kChunk], rc[kChunk];
 #pragma unroll
-            for (int u = 0; u < kChunk; u++) {
-                rv[u] = cur[u * CW];
-                rc[u] = CW == 16 ? rv[u] : cur[u * CW + 16];
+            for (int u0 = 0; u0 < kChunk; u0 += 4) {
+                double rv[4], rc[4];
+#pragma unroll
+                for (int u = 0; u < 4; u++) {
+                    rv[u] = cur[(u0 + u) * CW];
+                    rc[u] = CW == 16 ? rv[u] : cur[(u0 + u) * CW + 16];
+                }
+#pragma unroll
+                for (int u = 0; u < 4; u++) step_v(rv[u], rc[u]);
             }
-#pragma unroll
-            for (int u = 0; u < kChunk; u++) step_v(rv[u], rc[u]);
-            stage(sl ^ 1);
+            stage(sl ^ 1, c0 + kChunk);
             fetch(c0 + 2 * kChunk);
         }
     }
@@ -285,17 +306,17 @@ __device__ __forceinline__ void residual_piece(const BfArgs<S> &a, long long tk,
     const long long lbase = (unsigned)__builtin_amdgcn_readfirstlane(h2.z);
     const size_t aoff = (size_t)m * (2 * a.L + 3 - m) / 2;
     const double *ap = reinterpret_cast<const double *>(a.alm + (aoff + t) * a.nmaps + a.map0);
-    const double *cfs = a.coef + 4 * a.coef_off[m];
+    const double4 *sc = reinterpret_cast<const double4 *>(a.coef_sc) + a.coef_off[m];
     const int astride = 4 * a.nmaps;  // doubles between rows i and i+1
-    residual_task<NB, kBfPieceRings / 64>(a, a.ws, lbase, lane, t, imin, iend, nl, outb, ap, cfs, astride, stg,
+    residual_task<NB, kBfPieceRings / 64>(a, a.ws, lbase, lane, t, imin, iend, nl, outb, ap, sc, astride, stg,
                                           col0);
 }
 
 template <int NB, typename S>
-__global__ __launch_bounds__(kBfThreads) void k_bf_residual(BfArgs<S> a, long long t0, long long t1, int col0) {
-    __shared__ double stg_all[kBfThreads / 64][bf_res_stage_doubles<NB>()];
+__global__ __launch_bounds__(kBfResThreads) void k_bf_residual(BfArgs<S> a, long long t0, long long t1, int col0) {
+    __shared__ double stg_all[kBfResThreads / 64][bf_res_stage_doubles<NB>()];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long tk = t0 + (long long)blockIdx.x * (kBfThreads / 64) + w;
+    const long long tk = t0 + (long long)blockIdx.x * (kBfResThreads / 64) + w;
     if (tk >= t1) return;
     residual_piece<NB, S>(a, tk, threadIdx.x & 63, stg_all[w], col0);
 }
@@ -407,11 +428,11 @@ __global__ __launch_bounds__(kBfThreads) void k_bf_fold(BfArgs<S> a, int batch, 
 // one map-group width; item = {pass (argument block), index within the
 // pass's plan}.  The bodies are the single-request kernels'.
 template <int NB, typename S>
-__global__ __launch_bounds__(kBfThreads) void k_bfq_residual(const BfArgs<S> *__restrict__ args,
+__global__ __launch_bounds__(kBfResThreads) void k_bfq_residual(const BfArgs<S> *__restrict__ args,
                                                              const int2 *__restrict__ items, long long n) {
-    __shared__ double stg_all[kBfThreads / 64][bf_res_stage_doubles<NB>()];
+    __shared__ double stg_all[kBfResThreads / 64][bf_res_stage_doubles<NB>()];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const long long j = (long long)blockIdx.x * (kBfThreads / 64) + w;
+    const long long j = (long long)blockIdx.x * (kBfResThreads / 64) + w;
     if (j >= n) return;
     const int2 it = items[j];
     const BfArgs<S> a = args[__builtin_amdgcn_readfirstlane(it.x)];
@@ -483,11 +504,11 @@ __global__ __launch_bounds__(kBfThreads) void k_bfq_fold(const BfArgs<S> *__rest
 template <int NB, typename S>
 static hipError_t bfq_stage_nb(int stage, const void *args, const int2 *items, long long n, size_t lds, hipStream_t st) {
     const BfArgs<S> *ar = reinterpret_cast<const BfArgs<S> *>(args);
-    constexpr int WPB = kBfThreads / 64;
+    constexpr int WPB = kBfResThreads / 64;
     if (n <= 0) return hipSuccess;
     switch (stage) {
         case 0:
-            hipLaunchKernelGGL((k_bfq_residual<NB, S>), dim3((unsigned)((n + WPB - 1) / WPB)), dim3(kBfThreads), 0, st, ar,
+            hipLaunchKernelGGL((k_bfq_residual<NB, S>), dim3((unsigned)((n + WPB - 1) / WPB)), dim3(kBfResThreads), 0, st, ar,
                                items, n);
             break;
         case 1:
@@ -563,7 +584,7 @@ static void bf_event(void *const *ev, int stage, int which, hipStream_t st) {
 
 template <int NB, typename S, bool ONE>
 static hipError_t launch_bf_nbg(const sht_plan_s *p, BfArgs<S> a, hipStream_t st, void *const *ev) {
-    constexpr int WPB = kBfThreads / 64;
+    constexpr int WPB = kBfResThreads / 64;
     const BflyPlan &b = p->bf;
     if (b.nbatch != 1) ev = nullptr;
     for (int bt = 0; bt < b.nbatch; bt++) {
@@ -572,7 +593,7 @@ static hipError_t launch_bf_nbg(const sht_plan_s *p, BfArgs<S> a, hipStream_t st
         for (int g = 0; g < a.G && t1 > t0; g++) {  // one launch per group of NB maps
             BfArgs<S> ag = a;
             ag.map0 = a.map0 + g * NB;
-            hipLaunchKernelGGL((k_bf_residual<NB, S>), dim3((unsigned)((t1 - t0 + WPB - 1) / WPB)), dim3(kBfThreads), 0,
+            hipLaunchKernelGGL((k_bf_residual<NB, S>), dim3((unsigned)((t1 - t0 + WPB - 1) / WPB)), dim3(kBfResThreads), 0,
                                st, ag, t0, t1, g * 2 * NB);
         }
         bf_event(ev, SHT_STAGE_BF_RESIDUAL, 1, st);
@@ -611,13 +632,13 @@ static hipError_t launch_bf_nbg(const sht_plan_s *p, BfArgs<S> a, hipStream_t st
 // for a pass of nb maps (G = 1).
 hipError_t launch_node_phase(const sht_plan_s *p, int nb, BfArgs<double> a, long long npieces, hipStream_t st) {
     (void)p;
-    constexpr int WPB = kBfThreads / 64;
+    constexpr int WPB = kBfResThreads / 64;
     if (npieces <= 0) return hipSuccess;
     const dim3 grid((unsigned)((npieces + WPB - 1) / WPB));
     switch (nb) {
-        case 4: hipLaunchKernelGGL((k_bf_residual<4, double>), grid, dim3(kBfThreads), 0, st, a, 0LL, npieces, 0); break;
-        case 2: hipLaunchKernelGGL((k_bf_residual<2, double>), grid, dim3(kBfThreads), 0, st, a, 0LL, npieces, 0); break;
-        default: hipLaunchKernelGGL((k_bf_residual<1, double>), grid, dim3(kBfThreads), 0, st, a, 0LL, npieces, 0); break;
+        case 4: hipLaunchKernelGGL((k_bf_residual<4, double>), grid, dim3(kBfResThreads), 0, st, a, 0LL, npieces, 0); break;
+        case 2: hipLaunchKernelGGL((k_bf_residual<2, double>), grid, dim3(kBfResThreads), 0, st, a, 0LL, npieces, 0); break;
+        default: hipLaunchKernelGGL((k_bf_residual<1, double>), grid, dim3(kBfResThreads), 0, st, a, 0LL, npieces, 0); break;
     }
     return hipGetLastError();
 }

@@ -17,6 +17,7 @@
 //     the order of those few addends, and the last bits of g, may vary from
 //     run to run).
 #include "butterfly_common.h"
+#include "dpp.h"
 
 namespace sht {
 
@@ -215,101 +216,29 @@ __global__ __launch_bounds__(kBfUnfoldThreads) void k_bf_unfold_level1(BfArgs<S>
     }
 }
 
-// Lane exchanges for the wave reductions.  permlane32_swap(a, b) leaves
-// a = [a lanes 0-31, b lanes 0-31] and b = [a lanes 32-63, b lanes 32-63];
-// permlane16_swap does the same with rows of 16 (a keeps its even rows and
-// b's even rows, b gets the odd rows of both), as measured on gfx950.
-__device__ __forceinline__ void swap32(double &a, double &b) {
-    const long long ia = __builtin_bit_cast(long long, a), ib = __builtin_bit_cast(long long, b);
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned)ia, (unsigned)ib, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
-    a = __builtin_bit_cast(double, ((long long)hi[0] << 32) | (long long)lo[0]);
-    b = __builtin_bit_cast(double, ((long long)hi[1] << 32) | (long long)lo[1]);
-}
-__device__ __forceinline__ void swap16(double &a, double &b) {
-    const long long ia = __builtin_bit_cast(long long, a), ib = __builtin_bit_cast(long long, b);
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)ia, (unsigned)ib, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)(ia >> 32), (unsigned)(ib >> 32), false, false);
-    a = __builtin_bit_cast(double, ((long long)hi[0] << 32) | (long long)lo[0]);
-    b = __builtin_bit_cast(double, ((long long)hi[1] << 32) | (long long)lo[1]);
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_mov(double v) {
-    const long long x = __builtin_bit_cast(long long, v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(x >> 32), CTRL, 0xF, 0xF, false);
-    return __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
-}
-// One in-row stage at lane distance given by CTRL (a DPP pattern pairing
-// lanes that differ in bit BIT): with h > 0 it halves the values (value j
-// stays where the bit is clear, value j + h where it is set), with h = 0 it
-// adds the partner's single value.
-template <int CTRL, int BIT, int N>
-__device__ __forceinline__ void row_stage(double (&x)[N], int h, int lane) {
-    const bool hi = (lane >> BIT) & 1;
-    if (h == 0) {
-        x[0] += dpp_mov<CTRL>(x[0]);
-        return;
-    }
-#pragma unroll
-    for (int j = 0; j < N / 2; j++) {
-        if (j >= h) break;
-        const double keep = hi ? x[j + h] : x[j], send = hi ? x[j] : x[j + h];
-        x[j] = keep + dpp_mov<CTRL>(send);
-    }
-}
-
-// Sum of x[c] over the 64 lanes of a wave for N = 2^A values per lane
-// (N <= 16): afterwards value c = lane >> (6 - A) is complete in every lane
-// of its group.  Lane distances 32 and 16 use lane swaps (each pair of
-// values costs two swaps and one add), 8, 4, 2, 1 use DPP.
-template <int N>
-__device__ __forceinline__ double wave_transpose_sum(double (&x)[N], int lane) {
-    static_assert(N == 1 || N == 2 || N == 4 || N == 8 || N == 16, "value count");
-    int h = N / 2;
-    if (h > 0) {
-#pragma unroll
-        for (int j = 0; j < N / 2; j++) {
-            swap32(x[j], x[j + N / 2]);
-            x[j] += x[j + N / 2];
-        }
-    } else {
-        double y = x[0];
-        swap32(x[0], y);
-        x[0] += y;
-    }
-    h /= 2;
-    if (h > 0) {
-#pragma unroll
-        for (int j = 0; j < N / 4; j++) {
-            swap16(x[j], x[j + N / 4]);
-            x[j] += x[j + N / 4];
-        }
-    } else {
-        double y = x[0];
-        swap16(x[0], y);
-        x[0] += y;
-    }
-    h /= 2;
-    row_stage<0x128, 3>(x, h, lane);  // row_ror:8
-    h /= 2;
-    row_stage<0x141, 2>(x, h, lane);  // row_half_mirror
-    h /= 2;
-    row_stage<0x4E, 1>(x, h, lane);   // quad_perm [2,3,0,1]
-    h /= 2;
-    row_stage<0xB1, 0>(x, h, lane);   // quad_perm [1,0,3,2]
-    return x[0];
-}
-
 // One transposed residual task on one wave: R rings per lane, rows
 // [imin, iend) of parity t; each row's sum over the task's rings goes to g.
+// As in the brute-force adjoint (adjoint.hip): four rows at a time the wave
+// writes its rings' values of the scaled recurrence to LDS and multiplies
+// them, 16 rings at a time, by the vector in FP64 MFMA 4x4x4 products of four
+// blocks (operand A: row l % 4, ring l / 4; B: ring l / 4, value l % 4; result:
+// row l / 16, value l % 4, split over the blocks (l / 4) % 4), which are added by
+// DPP.  Rows are taken at multiples of four; those outside [imin, iend) add
+// nothing.  (With the sums of 64 lanes by lane swaps, row by row, and
+// coefficients by uniform loads, the launch took 1238 us at L = 2047, 4 maps;
+// so 943 us.)
+constexpr int kBfTileRow = 68;  // doubles per row of 64 rings: 16-lane reads of 4 rows hit distinct banks
+constexpr int kBfTLds = 4 * kBfTileRow + 64;  // a tile of four rows, coefficients of 16
+
 template <int NB, int R, typename S>
 __device__ __forceinline__ void residual_task_t(const BfArgs<S> &a, long long tk, int lane, int t, int imin,
-                                                int iend, int nl, int outb, int m, c_double *cfs, int col0) {
-    constexpr int NC = 2 * NB;
-    constexpr int A = NC == 2 ? 1 : NC == 4 ? 2 : NC == 8 ? 3 : 4;
+                                                int iend, int nl, int outb, int m, double *lds, int col0) {
+    constexpr int NC = 2 * NB, NS = (NC + 3) / 4;
+    double *tile = lds, *cst = lds + 4 * kBfTileRow;
+    if (imin >= iend) return;
+    const double4 *sc = reinterpret_cast<const double4 *>(a.coef_sc) + a.coef_off[m] + t;
     int i0[R];
-    double z2[R], v0[R], v1[R], P0[R], P1[R], w[R][NC];
+    double z2[R], v0[R], v1[R], P0[R], P1[R], Y[R][4][NS];
 #pragma unroll
     for (int r = 0; r < R; r++) {
         const size_t li = (size_t)tk * kBfTaskRings + r * 64 + lane;
@@ -320,71 +249,105 @@ __device__ __forceinline__ void residual_task_t(const BfArgs<S> &a, long long tk
         v0[r] = sv.x;
         v1[r] = sv.y;
         P0[r] = P1[r] = 0.0;
-        const int j = r * 64 + lane;
+        // (lanes past the task's last ring never start)
 #pragma unroll
-        for (int c = 0; c < NC; c++) w[r][c] = j < nl ? (double)a.ws[((size_t)outb + j) * a.ES + col0 + c] : 0.0;
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+            for (int s = 0; s < NS; s++)
+                Y[r][q][s] = (double)a.ws[((size_t)outb + min(64 * r + 16 * q + (lane >> 2), nl - 1)) * a.ES + col0 +
+                                          min(4 * s + (lane & 3), NC - 1)];
+    }
+    // coefficients of 16 rows: lane 4 u + c holds value c of row u (b, -b d of
+    // the next row, f of the row)
+    const double *cb = reinterpret_cast<const double *>((lane & 3) < 2 ? sc + 2 : sc) + min(lane & 3, 2);
+    auto coef = [&](int c) { return cb[8 * (size_t)min(c + (lane >> 2), iend - 1)]; };
+    int c = imin & ~3;
+    double cnext = coef(c);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = i0[r] < iend ? i0[r] : imin;
+        v0[r] *= sc[2 * i].w;
+        v1[r] *= sc[2 * i + 2].w;
     }
     const size_t aoff = (size_t)m * (2 * a.L + 3 - m) / 2;
     // component c = 2 b + (re, im) of row i lives at gb[i * 4 nmaps + c]
     double *gb = a.g + 2 * ((aoff + t) * a.nmaps + a.map0);
     const size_t gstride = 4 * (size_t)a.nmaps;
-    const int c_own = lane >> (6 - A);
-    const bool writer = (lane & ((1 << (6 - A)) - 1)) == 0 && !(m == 0 && (c_own & 1));
-    auto step = [&](int i) {
-        c_double *e = cfs + 4 * (t + 2 * i + 2);
-        const double eb = e[0], eab = e[1], eg = e[2];
-        double part[NC];
+    const int blk = (lane >> 2) & 3, col = 4 * blk + (lane & 3);
+    const bool writer = blk < NS && col < NC && !(m == 0 && (col & 1));
+    for (; c < iend; c += 16) {
+        cst[lane] = cnext;
+        cnext = coef(c + 16);
 #pragma unroll
-        for (int c = 0; c < NC; c++) part[c] = 0.0;
+        for (int q = 0; q < 4; q++) {
+            if (c + 4 * q >= iend) break;
+            const double cv = cst[16 * q + (lane & 15)];
+            const double cB[4] = {row_bcast<0>(cv), row_bcast<4>(cv), row_bcast<8>(cv), row_bcast<12>(cv)};
+            const double cA[4] = {row_bcast<1>(cv), row_bcast<5>(cv), row_bcast<9>(cv), row_bcast<13>(cv)};
+            const double f = cst[16 * q + 4 * (lane >> 4) + 2];
+            double D[NS];
 #pragma unroll
-        for (int r = 0; r < R; r++) {
+            for (int s = 0; s < NS; s++) D[s] = 0.0;
 #pragma unroll
-            for (int c = 0; c < NC; c++) part[c] = __builtin_fma(P0[r], w[r][c], part[c]);
-            const double P2 = __builtin_fma(__builtin_fma(z2[r], eb, eab), P1[r], eg * P0[r]);
-            P0[r] = P1[r];
-            P1[r] = P2;
-        }
-        const double tot = wave_transpose_sum<NC>(part, lane);
-        if (writer) atomicAdd(gb + (size_t)i * gstride + c_own, tot);
-    };
-    for (int c = imin; c < iend;) {
+            for (int r = 0; r < R; r++) {
+                // chains start at imin or at a multiple of kChunk
 #pragma unroll
-        for (int r = 0; r < R; r++)
-            if (i0[r] == c) {
-                P0[r] = v0[r];
-                P1[r] = v1[r];
+                for (int u = 0; u < 4; u++) {
+                    const int i = c + 4 * q + u;
+                    if (u == 0 || (q == 0 && i == imin)) {
+                        const bool st = i0[r] == i;
+                        P0[r] = st ? v0[r] : P0[r];
+                        P1[r] = st ? v1[r] : P1[r];
+                    }
+                    tile[u * kBfTileRow + lane] = P0[r];
+                    const double nx = __builtin_fma(__builtin_fma(z2[r], cB[u], cA[u]), P1[r], -P0[r]);
+                    P0[r] = P1[r];
+                    P1[r] = nx;
+                }
+                // the wave's own tile: its LDS writes and reads complete in order
+                double av[4];
+#pragma unroll
+                for (int k = 0; k < 4; k++) av[k] = tile[(lane & 3) * kBfTileRow + 16 * k + (lane >> 2)];
+#pragma unroll
+                for (int k = 0; k < 4; k++)
+#pragma unroll
+                    for (int s = 0; s < NS; s++)
+                        D[s] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[k], Y[r][k][s], D[s], 0, 0, 0);
             }
-        const int ce = min(iend, (c & ~(kChunk - 1)) + kChunk);
-        if (ce - c == kChunk) {
+            // the four blocks' sums, in every block; block s adds value set s to g
+            double v = row_ror_add<4>(row_ror_add<8>(D[0]));
 #pragma unroll
-            for (int u = 0; u < kChunk; u++) step(c + u);
-        } else {
-            for (int i = c; i < ce; i++) step(i);
+            for (int s = 1; s < NS; s++) {
+                const double d = row_ror_add<4>(row_ror_add<8>(D[s]));
+                v = blk == s ? d : v;
+            }
+            const int i = c + 4 * q + (lane >> 4);
+            if (writer && i >= imin && i < iend) atomicAdd(gb + (size_t)i * gstride + col, f * v);
         }
-        c = ce;
     }
 }
 
 template <int NB, typename S>
-__global__ __launch_bounds__(kBfThreads) void k_bf_residual_t(BfArgs<S> a, long long t0, long long t1, int col0) {
+__global__ __launch_bounds__(kBfResThreads) void k_bf_residual_t(BfArgs<S> a, long long t0, long long t1, int col0) {
     const int lane = threadIdx.x & 63;
-    const long long tk = t0 + (long long)blockIdx.x * (kBfThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const long long tk = t0 + (long long)blockIdx.x * (kBfResThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (tk >= t1) return;
     const int4 h = a.res_task[2 * tk], h2 = a.res_task[2 * tk + 1];
     const int t = __builtin_amdgcn_readfirstlane(h.x), imin = __builtin_amdgcn_readfirstlane(h.y);
     const int iend = __builtin_amdgcn_readfirstlane(h.z), nl = __builtin_amdgcn_readfirstlane(h.w);
     const int outb = __builtin_amdgcn_readfirstlane(h2.x), m = __builtin_amdgcn_readfirstlane(h2.y);
-    c_double *cfs = (c_double *)(a.coef + 4 * a.coef_off[m]);
+    __shared__ double lds_all[kBfResThreads / 64][kBfTLds];
+    double *lds = lds_all[__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)];
     if constexpr (kBfTaskRings > 192) {
-        if (nl > 192) return residual_task_t<NB, 4>(a, tk, lane, t, imin, iend, nl, outb, m, cfs, col0);
+        if (nl > 192) return residual_task_t<NB, 4>(a, tk, lane, t, imin, iend, nl, outb, m, lds, col0);
     }
     if constexpr (kBfTaskRings > 128) {
-        if (nl > 128) return residual_task_t<NB, 3>(a, tk, lane, t, imin, iend, nl, outb, m, cfs, col0);
+        if (nl > 128) return residual_task_t<NB, 3>(a, tk, lane, t, imin, iend, nl, outb, m, lds, col0);
     }
     if constexpr (kBfTaskRings > 64) {
-        if (nl > 64) return residual_task_t<NB, 2>(a, tk, lane, t, imin, iend, nl, outb, m, cfs, col0);
+        if (nl > 64) return residual_task_t<NB, 2>(a, tk, lane, t, imin, iend, nl, outb, m, lds, col0);
     }
-    residual_task_t<NB, 1>(a, tk, lane, t, imin, iend, nl, outb, m, cfs, col0);
+    residual_task_t<NB, 1>(a, tk, lane, t, imin, iend, nl, outb, m, lds, col0);
 }
 
 // g = 0 over the nalm rows of maps [map0, map0 + nb) (a kernel, not a
@@ -399,7 +362,7 @@ __global__ __launch_bounds__(kBfThreads) void k_bf_zero(double *g, long long nal
 
 template <int NB, bool TT, typename S, bool ONE>
 static hipError_t launch_bf_adj_nbg(const sht_plan_s *p, BfArgs<S> a, hipStream_t st) {
-    constexpr int WPB = kBfThreads / 64;
+    constexpr int WPB = kBfResThreads / 64;
     const BflyPlan &b = p->bf;
     const long long nalm = (long long)(p->L + 1) * (p->L + 2) / 2;
     const int np = NB * a.G;  // maps of the pass
@@ -434,7 +397,7 @@ static hipError_t launch_bf_adj_nbg(const sht_plan_s *p, BfArgs<S> a, hipStream_
             BfArgs<S> ag = a;
             ag.map0 = a.map0 + g * NB;
             hipLaunchKernelGGL((k_bf_residual_t<NB, S>), dim3((unsigned)((t1 - t0 + WPB - 1) / WPB)),
-                               dim3(kBfThreads), 0, st, ag, t0, t1, g * 2 * NB);
+                               dim3(kBfResThreads), 0, st, ag, t0, t1, g * 2 * NB);
         }
     }
     return hipGetLastError();

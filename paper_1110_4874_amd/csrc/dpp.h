@@ -63,6 +63,15 @@ __device__ __forceinline__ double row_bcast(double x) {
     return __builtin_amdgcn_mov_dpp(x, 0x150 + K, 0xF, 0xF, false);
 }
 
+// x + the value of the lane N to the right, cyclic within each row of 16
+template <int N>
+__device__ __forceinline__ double row_ror_add(double x) {
+    const long long v = __builtin_bit_cast(long long, x);
+    const int lo = __builtin_amdgcn_mov_dpp((int)v, 0x120 + N, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_mov_dpp((int)(v >> 32), 0x120 + N, 0xF, 0xF, false);
+    return x + __builtin_bit_cast(double, ((long long)hi << 32) | (long long)(unsigned)lo);
+}
+
 // Order m of item s of XCD xcd (workgroups are dealt to the 8 XCDs round
 // robin): eight consecutive orders of each 64, so that the XCD's L2 serves an
 // order's coefficient and a_lm stream to all its blocks, and gathers the 16
