@@ -152,17 +152,19 @@ __device__ __forceinline__ void id_block(const BfArgs<S> &a, int node, int ch, i
 // operations of one wave complete in order, so no barrier is needed.  The
 // loads are unconditional, of rows clamped into [imin, iend), and rows outside
 // are overwritten with zeros in LDS: a select on a load would become a branch
-// that waits for memory, twice a chunk.  Residual launch at L = 2047, before
-// and now: 4 maps 781 and 793 us, with FP32 results 808 and 696 us; 8 maps 1455
-// and 1425 us.  FP64 issue bounds it (one wavefront or four a workgroup: the
-// same within 2%).
+// that waits for memory, twice a chunk.  Start values wait in LDS, where they
+// cost no registers.  Residual launch at L = 2047: 4 maps 735 us (781 with
+// selected loads and 16-byte stores into 64 entries at once), with FP32 results
+// 680 us (808); 8 maps 1210 us (1455; 1386 with those stores alone), FP32 1175.
+// FP64 issue bounds it: its products alone take 842 us for 8 maps, and 18% of
+// its instructions stage operands.
 template <int NB>
 constexpr int bf_res_row_doubles() {
     return 2 * NB + 2 <= 16 ? 16 : 32;
 }
 template <int NB>
 constexpr int bf_res_stage_doubles() {
-    return 2 * kChunk * bf_res_row_doubles<NB>();
+    return 2 * kChunk * bf_res_row_doubles<NB>() + 2 * kBfPieceRings;
 }
 
 template <int NB, int R, typename S>
@@ -177,16 +179,15 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
     constexpr int CO = NC % 16;                    // lane of b within its 16-lane row
     static_assert(NC + 2 <= 16 || NC == 16, "the coefficients share one 16-lane row");
     int i0[R];
-    double z2[R], v0[R], v1[R], P0[R], P1[R], acc[R][NC];
+    double z2[R], P0[R], P1[R], acc[R][NC];
+    double2 *st = reinterpret_cast<double2 *>(stg + 2 * CS);  // the rings' start values
 #pragma unroll
     for (int r = 0; r < R; r++) {
         const size_t li = (size_t)lbase + r * 64 + lane;
         const int2 ln = a.res_lane[li];
-        const double2 sv = a.res_val[li];
+        st[r * 64 + lane] = a.res_val[li];
         i0[r] = ln.y;
         z2[r] = a.z2[ln.x];
-        v0[r] = sv.x;
-        v1[r] = sv.y;
         P0[r] = P1[r] = 0.0;
 #pragma unroll
         for (int c = 0; c < NC; c++) acc[r][c] = 0.0;
@@ -233,8 +234,10 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
 #pragma unroll
         for (int r = 0; r < R; r++) {
             const int i = i0[r] < iend ? i0[r] : imin;
-            v0[r] *= sc[t + 2 * i].w;
-            v1[r] *= sc[t + 2 * i + 2].w;
+            double2 v = st[r * 64 + lane];
+            v.x *= sc[t + 2 * i].w;
+            v.y *= sc[t + 2 * i + 2].w;
+            st[r * 64 + lane] = v;
         }
         stage(0, c0);
         fetch(c0 + kChunk);
@@ -244,8 +247,9 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
 #pragma unroll
         for (int r = 0; r < R; r++)
             if (i0[r] == imin) {
-                P0[r] = v0[r];
-                P1[r] = v1[r];
+                const double2 v = st[r * 64 + lane];
+                P0[r] = v.x;
+                P1[r] = v.y;
             }
         if (c0 != imin) {
             const int ce = min(iend, c0 + kChunk);
@@ -261,11 +265,12 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
         }
         for (; c0 < iend; c0 += kChunk, sl ^= 1) {
 #pragma unroll
-            for (int r = 0; r < R; r++) {
-                const bool st = i0[r] == c0;
-                P0[r] = st ? v0[r] : P0[r];
-                P1[r] = st ? v1[r] : P1[r];
-            }
+            for (int r = 0; r < R; r++)
+                if (i0[r] == c0) {
+                    const double2 v = st[r * 64 + lane];
+                    P0[r] = v.x;
+                    P1[r] = v.y;
+                }
             // four rows are read at once (one or two values per lane and row),
             // so that their LDS latency is paid twice per chunk
             const double *cur = stg + sl * CS + (lane & 15);
@@ -284,13 +289,42 @@ __device__ __forceinline__ void residual_task(const BfArgs<S> &a, S *__restrict_
             fetch(c0 + 2 * kChunk);
         }
     }
+    // The results leave as whole entries: through LDS, 16-byte units swizzled by
+    // the ring, so that a store instruction covers 64 consecutive units and not
+    // 16 bytes of each of 64 entries.
+    constexpr int V = 16 / sizeof(S), U = NC / V;  // values per unit, units per ring
+    S *out = slot + (size_t)outb * a.ES + col0;
+    if constexpr (U > 1) {
+        typedef S unit_t __attribute__((ext_vector_type(V), aligned(sizeof(S))));
+        typedef S lds_t __attribute__((ext_vector_type(V)));
+        lds_t *tile = reinterpret_cast<lds_t *>(stg);
+        static_assert(64 * U * 16 <= sizeof(double) * bf_res_stage_doubles<NB>(), "a tile of 64 rings");
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-        const int j = r * 64 + lane;
-        if (j < nl) {
-            S *dst = slot + ((size_t)outb + j) * a.ES + col0;
+        for (int r = 0; r < R; r++) {
+            __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int c = 0; c < NC; c++) dst[c] = (S)acc[r][c];
+            for (int u = 0; u < U; u++) {
+                lds_t x;
+#pragma unroll
+                for (int v = 0; v < V; v++) x[v] = (S)acc[r][u * V + v];
+                tile[lane * U + (u ^ (lane & (U - 1)))] = x;
+            }
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int j = (64 * u + lane) / U, c = lane & (U - 1);
+                if (r * 64 + j < nl)
+                    *reinterpret_cast<unit_t *>(out + (size_t)(r * 64 + j) * a.ES + c * V) = tile[j * U + (c ^ (j & (U - 1)))];
+            }
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+            const int j = r * 64 + lane;
+            if (j < nl) {
+#pragma unroll
+                for (int c = 0; c < NC; c++) out[(size_t)j * a.ES + c] = (S)acc[r][c];
+            }
         }
     }
 }
@@ -314,7 +348,7 @@ __device__ __forceinline__ void residual_piece(const BfArgs<S> &a, long long tk,
 
 template <int NB, typename S>
 __global__ __launch_bounds__(kBfResThreads) void k_bf_residual(BfArgs<S> a, long long t0, long long t1, int col0) {
-    __shared__ double stg_all[kBfResThreads / 64][bf_res_stage_doubles<NB>()];
+    __shared__ __align__(16) double stg_all[kBfResThreads / 64][bf_res_stage_doubles<NB>()];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long long tk = t0 + (long long)blockIdx.x * (kBfResThreads / 64) + w;
     if (tk >= t1) return;
@@ -430,7 +464,7 @@ __global__ __launch_bounds__(kBfThreads) void k_bf_fold(BfArgs<S> a, int batch, 
 template <int NB, typename S>
 __global__ __launch_bounds__(kBfResThreads) void k_bfq_residual(const BfArgs<S> *__restrict__ args,
                                                              const int2 *__restrict__ items, long long n) {
-    __shared__ double stg_all[kBfResThreads / 64][bf_res_stage_doubles<NB>()];
+    __shared__ __align__(16) double stg_all[kBfResThreads / 64][bf_res_stage_doubles<NB>()];
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const long long j = (long long)blockIdx.x * (kBfResThreads / 64) + w;
     if (j >= n) return;
