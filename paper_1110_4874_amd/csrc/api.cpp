@@ -426,8 +426,7 @@ int sht_pol_synthesis(const sht_plan_t *p, const sht_exec_opts *x, const double 
     stage_event(x, SHT_STAGE_LEGENDRE, 0);
     if ((rc = hip_status(launch_pol_prep(p, n, E, B, alm6, st), "polarization coefficient launch"))) return rc;
     if ((rc = legendre_stage(p, 6 * n, x->path, x->precision, alm6, sws, st, nullptr))) return rc;
-    if ((rc = hip_status(launch_pol_combine(p, n, q6, q2, st), "spin-2 combination launch"))) return rc;
-    if ((rc = hip_status(launch_pol_polar(p, n, E, B, q2, st), "polar spin-2 launch"))) return rc;
+    if ((rc = hip_status(launch_pol_finish(p, n, E, B, q6, q2, st), "spin-2 combination launch"))) return rc;
     stage_event(x, SHT_STAGE_LEGENDRE, 1);
     stage_event(x, SHT_STAGE_RING, 0);
     rc = hip_status(launch_ring_synthesis(p, 2 * n, q2, QU, st), "ring kernel launch");

@@ -299,9 +299,8 @@ int pol_column_host(const sht_plan_s *p, int m, int s, int k, double *out);
 size_t pol_alm_bytes(const sht_plan_s *p, int nmaps);
 hipError_t launch_pol_prep(const sht_plan_s *p, int nmaps, const double *E, const double *B, double *alm6,
                            hipStream_t st);
-hipError_t launch_pol_combine(const sht_plan_s *p, int nmaps, const double *q6, double *q2, hipStream_t st);
-hipError_t launch_pol_polar(const sht_plan_s *p, int nmaps, const double *E, const double *B, double *q2,
-                            hipStream_t st);
+hipError_t launch_pol_finish(const sht_plan_s *p, int nmaps, const double *E, const double *B, const double *q6,
+                             double *q2, hipStream_t st);
 int interp_apply_host(const sht_plan_s *p, int m, int t, const double *x, double *y);
 int butterfly_apply_host(const sht_plan_s *p, int m, int t, const double *x, double *y);
 int upload_tables(sht_plan_s *p);

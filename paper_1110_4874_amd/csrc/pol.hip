@@ -49,57 +49,99 @@ __device__ __forceinline__ double2 ld2(const double *p) { return *reinterpret_ca
 }  // namespace
 
 // ---- coefficient sets -------------------------------------------------------
-// One workgroup per order m; E, B: [nalm(L-1)][n] complex; out: [nalm(L)][6n]
-// complex, map 6b + {0, 1, 2} = S0, S1, S2 of E_b, 6b + {3, 4, 5} of B_b.
-__global__ __launch_bounds__(256) void k_pol_prep(const double *__restrict__ E, const double *__restrict__ B,
-                                                  double *__restrict__ out, int L, int n) {
-    const int m = blockIdx.x;
+// E, B: [nalm(L-1)][n] complex; out: [nalm(L)][6n] complex, map 6b + {0, 1, 2}
+// = S0, S1, S2 of E_b, 6b + {3, 4, 5} of B_b.  One thread per entry of an
+// order (workgroup L + 1 apart: the next 256), the six loads unconditional, of
+// degrees clamped to the order's (one workgroup per order and loads under their
+// conditions, one after the other: 30 us at L = 1023, one map; so 25 us).
+constexpr int kPolPrep = 256;
+__global__ __launch_bounds__(kPolPrep) void k_pol_prep(const double *__restrict__ E, const double *__restrict__ B,
+                                                       double *__restrict__ out, int L, int n) {
+    const int m = blockIdx.x % (L + 1);
     const int Lp = L - 1;
     const size_t offo = (size_t)m * (2 * L + 3 - m) / 2;
     const size_t offi = (size_t)m * (2 * Lp + 3 - m) / 2;  // valid for m <= Lp
-    auto coef = [&](const double *A, int l, int b) -> double2 {
+    const int e = blockIdx.x / (L + 1) * kPolPrep + threadIdx.x;
+    if (e >= (L - m + 1) * n) return;
+    const int l = m + e / n, b = e % n;
+    double2 *o = reinterpret_cast<double2 *>(out) + (offo + l - m) * 6 * n + 6 * b;
+    if (m > Lp) {  // the order L has no input
+        for (int c = 0; c < 6; c++) o[c] = make_double2(0.0, 0.0);
+        return;
+    }
+    double2 a[2][3];  // a_lm of E and B at l - 1, l, l + 1
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+        const size_t at = (offi + (min(max(l - 1 + d, m), Lp) - m)) * n + b;
+        a[0][d] = ld2(E + 2 * at);
+        a[1][d] = ld2(B + 2 * at);
+    }
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
         // N_l a_lm for 2 <= l <= Lp, l >= m; Im a_l0 ignored
-        if (l < 2 || l < m || l > Lp) return make_double2(0.0, 0.0);
-        const double2 a = ld2(A + 2 * ((offi + l - m) * n + b));
-        const double nl = 1.0 / sqrt((double)(l - 1) * l * (double)(l + 1) * (l + 2));
-        return make_double2(a.x * nl, m == 0 ? 0.0 : a.y * nl);
-    };
+        const int ll = l - 1 + d;
+        const bool none = ll < 2 || ll < m || ll > Lp;
+        const double nl = 1.0 / sqrt((double)(ll - 1) * ll * (double)(ll + 1) * (ll + 2));
+#pragma unroll
+        for (int mode = 0; mode < 2; mode++) {
+            double2 &x = a[mode][d];
+            x.x = none ? 0.0 : x.x * nl;
+            x.y = none || m == 0 ? 0.0 : x.y * nl;
+        }
+    }
     auto eps = [&](int l) -> double {
         return l > m ? sqrt(((double)l * l - (double)m * m) / (4.0 * l * l - 1.0)) : 0.0;
     };
-    const int cnt = (L - m + 1) * n;
-    for (int e = threadIdx.x; e < cnt; e += blockDim.x) {
-        const int l = m + e / n, b = e % n;
-        const double el = eps(l), el1 = eps(l + 1);
-        double2 *o = reinterpret_cast<double2 *>(out) + (offo + l - m) * 6 * n + 6 * b;
-        for (int mode = 0; mode < 2; mode++) {
-            const double *A = mode ? B : E;
-            const double2 c = coef(A, l, b), cm1 = coef(A, l - 1, b), cp1 = coef(A, l + 1, b);
-            const double w = (double)l * (l + 1);
-            o[3 * mode + 0] = c;
-            o[3 * mode + 1] = make_double2(w * c.x, w * c.y);
-            const double f0 = (double)(l - 1) * el, f1 = (double)(l + 2) * el1;
-            o[3 * mode + 2] = make_double2(f0 * cm1.x - f1 * cp1.x, f0 * cm1.y - f1 * cp1.y);
-        }
+    const double w = (double)l * (l + 1);
+    const double f0 = (double)(l - 1) * eps(l), f1 = (double)(l + 2) * eps(l + 1);
+#pragma unroll
+    for (int mode = 0; mode < 2; mode++) {
+        const double2 cm1 = a[mode][0], c = a[mode][1], cp1 = a[mode][2];
+        o[3 * mode + 0] = c;
+        o[3 * mode + 1] = make_double2(w * c.x, w * c.y);
+        o[3 * mode + 2] = make_double2(f0 * cm1.x - f1 * cp1.x, f0 * cm1.y - f1 * cp1.y);
     }
 }
 
+struct PolArgs {
+    const double *__restrict__ E;
+    const double *__restrict__ B;
+    const double *__restrict__ ring;  // [pol_n][6] z, sin(theta/2), cos(theta/2) (hi, lo)
+    const double *__restrict__ K;     // [(L+1)*2][4]
+    const int *__restrict__ grp_lo;   // scalar chain starts per (m, 64-ring group)
+    double *__restrict__ q2;
+    int L, nrings, pol_n, ng, ngp, n, map0;  // ng: the plan's 64-ring groups, ngp: polar groups
+};
+
 // ---- spin-2 combination -----------------------------------------------------
 // One thread per (ring, m, polarized map): q6 [rings][L+1][6n] -> q2
-// [rings][L+1][2n] (Q of map b at b, U at n + b).
-__global__ __launch_bounds__(256) void k_pol_combine(const double *__restrict__ q6, double *__restrict__ q2,
-                                                     const double *__restrict__ z2_hi,
-                                                     const double *__restrict__ z2_lo, int L, int nrings,
-                                                     int n_north, int n, long long total) {
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= total) return;
+// [rings][L+1][2n] (Q of map b at b, U at n + b), but for what the polar
+// workgroups of the same launch write.
+constexpr int kPolThreads = 128;
+struct CombineArgs {
+    const double *__restrict__ q6;
+    const double *__restrict__ z2_hi;
+    const double *__restrict__ z2_lo;
+    int n_north;
+    long long total;
+};
+
+__device__ __forceinline__ bool pol_dead(const PolArgs &a, int m, int g) {
+    return a.grp_lo[(size_t)m * a.ng + g] >= (a.L - m) / 2 + 1;  // every chain stays below the cutoff
+}
+
+__device__ __forceinline__ void pol_combine(const CombineArgs &f, const PolArgs &a, long long t) {
+    if (t >= f.total) return;
+    const int L = a.L, n = a.n;
     const int b = (int)(t % n);
     const long long rm = t / n;
     const int m = (int)(rm % (L + 1)), r = (int)(rm / (L + 1));
-    const int k = r < n_north ? r : nrings - 1 - r;
-    const double zz = z2_hi[k];
-    const double c = r < n_north ? sqrt(zz) : -sqrt(zz);
-    const double s2 = (1.0 - zz) - z2_lo[k];
+    const int k = r < f.n_north ? r : a.nrings - 1 - r;
+    if (k < a.pol_n && m < L && !pol_dead(a, m, k / 64)) return;
+    const double *q6 = f.q6;
+    const double zz = f.z2_hi[k];
+    const double c = r < f.n_north ? sqrt(zz) : -sqrt(zz);
+    const double s2 = (1.0 - zz) - f.z2_lo[k];
     const double2 *S = reinterpret_cast<const double2 *>(q6) + (size_t)rm * 6 * n + 6 * b;
     const double mm = (double)m * m, inv = 1.0 / s2;
     double2 F1[2], F2[2];
@@ -112,22 +154,12 @@ __global__ __launch_bounds__(256) void k_pol_combine(const double *__restrict__ 
     double2 Q = make_double2(-F1[0].x + F2[1].y, -F1[0].y - F2[1].x);
     double2 U = make_double2(-F1[1].x - F2[0].y, -F1[1].y + F2[0].x);
     if (m == 0) Q.y = U.y = 0.0;  // real fields
-    double2 *o = reinterpret_cast<double2 *>(q2) + (size_t)rm * 2 * n;
+    double2 *o = reinterpret_cast<double2 *>(a.q2) + (size_t)rm * 2 * n;
     o[b] = Q;
     o[n + b] = U;
 }
 
 // ---- polar caps: the spin-2 recurrence itself -------------------------------
-struct PolArgs {
-    const double *__restrict__ E;
-    const double *__restrict__ B;
-    const double *__restrict__ ring;  // [pol_n][6] z, sin(theta/2), cos(theta/2) (hi, lo)
-    const double *__restrict__ K;     // [(L+1)*2][4]
-    const int *__restrict__ grp_lo;   // scalar chain starts per (m, 64-ring group)
-    double *__restrict__ q2;
-    int L, nrings, pol_n, ng, ngp, n, map0;  // ng: the plan's 64-ring groups, ngp: polar groups
-};
-
 // mant * base^p with exponent tracking (mant kept in [0.5, 1) by powers of 2)
 __device__ __forceinline__ void dd_pow_acc(dd &mant, int &e, dd base, int p) {
     int eb;
@@ -170,15 +202,12 @@ __device__ __forceinline__ dd pol_r(double l, double M, double M1) {
 constexpr int kPolRows = 64;
 
 template <int NB>
-__global__ __launch_bounds__(128) void k_pol_polar(PolArgs a) {
+__device__ __forceinline__ void pol_polar(const PolArgs &a, int m, int g, double (&lds)[2][kPolRows * 16]) {
     constexpr int NV = 4 * NB, CW = 16;
     static_assert(NV + 3 <= CW, "a row holds the values of NB maps and the coefficients");
-    __shared__ __attribute__((aligned(16))) double lds[2][kPolRows * CW];
-    const int m = blockIdx.x / a.ngp, g = blockIdx.x % a.ngp;
     const int L = a.L, Lp = L - 1;
     const int si = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int lo = a.grp_lo[(size_t)m * a.ng + g];
-    if (lo >= (L - m) / 2 + 1) return;  // every chain of this group stays below the cutoff: the combination wrote 0
+    if (pol_dead(a, m, g)) return;  // the combination writes 0
     const int k = g * 64 + lane;
     const bool act = k < a.pol_n;
     const int kk = act ? k : a.pol_n - 1;
@@ -303,26 +332,33 @@ __global__ __launch_bounds__(128) void k_pol_polar(PolArgs a) {
     }
 }
 
+// The polar workgroups first: each is a long serial chain, which the
+// combination's streaming fills (L = 1023, one map: 81 + 48 us as two launches,
+// 84 us as one).
+template <int NB>
+__global__ __launch_bounds__(kPolThreads) void k_pol_finish(PolArgs a, CombineArgs f, int polar) {
+    __shared__ __attribute__((aligned(16))) double lds[2][kPolRows * 16];
+    if ((int)blockIdx.x < polar)
+        pol_polar<NB>(a, blockIdx.x / a.ngp, blockIdx.x % a.ngp, lds);
+    else
+        pol_combine(f, a, ((long long)blockIdx.x - polar) * kPolThreads + threadIdx.x);
+}
+
 size_t pol_alm_bytes(const sht_plan_s *p, int nmaps) {
     return ((size_t)(p->L + 1) * (p->L + 2) / 2 * 6 * nmaps * 16 + 255) / 256 * 256;
 }
 
 hipError_t launch_pol_prep(const sht_plan_s *p, int nmaps, const double *E, const double *B, double *alm6,
                            hipStream_t st) {
-    hipLaunchKernelGGL(k_pol_prep, dim3((unsigned)(p->L + 1)), dim3(256), 0, st, E, B, alm6, p->L, nmaps);
+    const long long per = ((long long)(p->L + 1) * nmaps + kPolPrep - 1) / kPolPrep;
+    const dim3 grid((unsigned)((p->L + 1) * per));
+    hipLaunchKernelGGL(k_pol_prep, grid, dim3(kPolPrep), 0, st, E, B, alm6, p->L, nmaps);
     return hipGetLastError();
 }
 
-hipError_t launch_pol_combine(const sht_plan_s *p, int nmaps, const double *q6, double *q2, hipStream_t st) {
-    const long long total = (long long)p->nrings * (p->L + 1) * nmaps;
-    hipLaunchKernelGGL(k_pol_combine, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, q6, q2, p->d_z2_hi,
-                       p->d_z2_lo, p->L, p->nrings, p->n_north, nmaps, total);
-    return hipGetLastError();
-}
-
-hipError_t launch_pol_polar(const sht_plan_s *p, int nmaps, const double *E, const double *B, double *q2,
-                            hipStream_t st) {
-    if (p->pol_n == 0 || p->L < 3) return hipSuccess;
+hipError_t launch_pol_finish(const sht_plan_s *p, int nmaps, const double *E, const double *B, const double *q6,
+                             double *q2, hipStream_t st) {
+    const bool caps = p->pol_n > 0 && p->L >= 3;
     PolArgs a;
     a.E = E;
     a.B = B;
@@ -332,23 +368,32 @@ hipError_t launch_pol_polar(const sht_plan_s *p, int nmaps, const double *E, con
     a.q2 = q2;
     a.L = p->L;
     a.nrings = p->nrings;
-    a.pol_n = p->pol_n;
+    a.pol_n = caps ? p->pol_n : 0;
     a.n = nmaps;
     a.ng = p->n_north_pad / kLanes;
-    a.ngp = (p->pol_n + 63) / 64;
+    a.ngp = caps ? (p->pol_n + 63) / 64 : 1;
+    const int polar = caps ? p->L * a.ngp : 0;  // orders 0 .. L-1 x polar groups
+    CombineArgs f;
+    f.q6 = q6;
+    f.z2_hi = p->d_z2_hi;
+    f.z2_lo = p->d_z2_lo;
+    f.n_north = p->n_north;
+    f.total = (long long)p->nrings * (p->L + 1) * nmaps;  // in the first launch
     hipError_t e = hipSuccess;
     for (int b = 0; b < nmaps && e == hipSuccess;) {
         const int nb = nmaps - b == 4 ? 2 : std::min(nmaps - b, 3);
         a.map0 = b;
-        const dim3 grid((unsigned)(p->L * a.ngp));  // orders 0 .. L-1 x polar groups
+        const dim3 grid((unsigned)(polar + (f.total + kPolThreads - 1) / kPolThreads));
         if (nb == 3)
-            hipLaunchKernelGGL(k_pol_polar<3>, grid, dim3(128), 0, st, a);
+            hipLaunchKernelGGL(k_pol_finish<3>, grid, dim3(kPolThreads), 0, st, a, f, polar);
         else if (nb == 2)
-            hipLaunchKernelGGL(k_pol_polar<2>, grid, dim3(128), 0, st, a);
+            hipLaunchKernelGGL(k_pol_finish<2>, grid, dim3(kPolThreads), 0, st, a, f, polar);
         else
-            hipLaunchKernelGGL(k_pol_polar<1>, grid, dim3(128), 0, st, a);
+            hipLaunchKernelGGL(k_pol_finish<1>, grid, dim3(kPolThreads), 0, st, a, f, polar);
         e = hipGetLastError();
         b += nb;
+        f.total = 0;
+        if (!caps) break;
     }
     return e;
 }
