@@ -26,6 +26,11 @@ __device__ __forceinline__ void fmac_row_bcast(double *acc, double rv, double p)
             asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3)
                 : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
                 : [rv] "v"(rv), [p] "v"(p));
+        else if constexpr (N == 6)
+            asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3) SHT_FMAC_BC(12, 4)
+                    SHT_FMAC_BC(13, 5)
+                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5])
+                : [rv] "v"(rv), [p] "v"(p));
         else if constexpr (N == 8)
             asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3) SHT_FMAC_BC(12, 4)
                     SHT_FMAC_BC(13, 5) SHT_FMAC_BC(14, 6) SHT_FMAC_BC(15, 7)

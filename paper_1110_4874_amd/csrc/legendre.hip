@@ -40,6 +40,8 @@
 // L = 4095 for sin(theta) <= 0.1 (double-double arithmetic, which these rings
 // ran before at about 45 operations a step and chain, made one wave's serial
 // chain the length of the whole launch below L ~ 2000).
+#include <type_traits>
+
 #include "ddmath.h"
 #include "dpp.h"
 #include "internal.h"
@@ -47,11 +49,14 @@
 namespace sht {
 
 // Staged row of a chain step: a_lm of NB maps (2 NB values), then the two
-// (split recurrence: three) coefficients, in rows of 16 doubles, or of 32
-// where they do not fit.
+// (split recurrence: three) coefficients, in rows of 8, 16 or 32 doubles.  Two
+// rows of 8 share one 16-lane read, and half as many values are fetched and
+// staged (Legendre phase with rows of 16 and of 8: L = 1023, 1 map 121 and 113
+// us, 3 maps 176 and 165; L = 2047, 1 map 780 and 750, 2 maps 961 and 919).
 template <int NB, bool POLE>
 constexpr int leg_row() {
-    return 2 * NB + (POLE ? 3 : 2) <= 16 ? 16 : 32;
+    constexpr int v = 2 * NB + (POLE ? 3 : 2);
+    return v <= 8 ? 8 : v <= 16 ? 16 : 32;
 }
 // LDS doubles of one wave: two staged chunks, and the chains' start values
 // (R rings) whose room holds one ring group's sums at the fold.
@@ -70,6 +75,7 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
     constexpr int CO = NC % 16;           // lane of the first coefficient within its 16-lane row
     static_assert(NC + (POLE ? 3 : 2) <= 16 || NC == 16, "the coefficients share one 16-lane row");
     constexpr int KU = 4;                 // rows read from LDS at once
+    constexpr int PK = CW < 16 ? 16 / CW : 1;  // rows within one 16-lane read
     const int t = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int L = a.L;
     const int n = L - m - t >= 0 ? (L - m - t) / 2 + 1 : 0;  // chain length
@@ -134,12 +140,13 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
                     if (c + (lane + 64 * e) / CW >= n) stg[sl * CS + lane + 64 * e] = 0.0;
             }
         };
-        auto step = [&](double rv, double rc) {
-            const double c0 = row_bcast<CO>(rc), c1 = row_bcast<CO + 1>(rc);
-            const double c2 = POLE ? row_bcast<(CO + 2) % 16>(rc) : 0.0;
+        auto step = [&](auto first, double rv, double rc) {  // first: the row's first lane
+            constexpr int C0 = decltype(first)::value;
+            const double c0 = row_bcast<C0 + CO>(rc), c1 = row_bcast<C0 + CO + 1>(rc);
+            const double c2 = POLE ? row_bcast<(C0 + CO + 2) % 16>(rc) : 0.0;
 #pragma unroll
             for (int r = 0; r < R; r++) {
-                fmac_row_bcast<NC>(acc[r], rv, P0[r]);
+                fmac_row_bcast<NC, C0>(acc[r], rv, P0[r]);
                 if constexpr (POLE) {  // c0 = h, c1 = -b (both of the next l), c2 = r
                     const double nx = __builtin_fma(c2, P0[r], P1[r]);
                     P1[r] = __builtin_fma(c0, P1[r], (c1 * x[r]) * nx);
@@ -175,14 +182,17 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             const double *cur = stg + sl * CS + (lane & 15);
 #pragma unroll
             for (int u0 = 0; u0 < kChunk; u0 += KU) {
-                double rv[KU], rc[KU];
+                double rv[KU / PK], rc[KU / PK];
 #pragma unroll
-                for (int u = 0; u < KU; u++) {
-                    rv[u] = cur[(u0 + u) * CW];
-                    rc[u] = CW == 16 ? rv[u] : cur[(u0 + u) * CW + 16];
+                for (int u = 0; u < KU / PK; u++) {
+                    rv[u] = cur[(u0 + PK * u) * CW];
+                    rc[u] = CW <= 16 ? rv[u] : cur[(u0 + PK * u) * CW + 16];
                 }
 #pragma unroll
-                for (int u = 0; u < KU; u++) step(rv[u], rc[u]);
+                for (int u = 0; u < KU / PK; u++) {
+                    step(std::integral_constant<int, 0>{}, rv[u], rc[u]);
+                    if constexpr (PK == 2) step(std::integral_constant<int, 8>{}, rv[u], rc[u]);
+                }
             }
             stage(sl ^ 1, c + kChunk);
             fetch(c + 2 * kChunk);
