@@ -403,15 +403,16 @@ int sht_batch_execute(const sht_request *reqs, int n, const sht_batch_opts *o);
  * small number of launches, for serving loops and graph capture
  * (many-transform regime of Sec. 3.4).  sht_batch_create splits the
  * brute-force Legendre phase of every request into work items (pass of up
- * to 4 maps, order m, block of ring groups), sorts them longest first by
+ * to 8 maps, order m, block of ring groups), sorts them longest first by
  * their chain steps and uploads them with their argument blocks; it
  * allocates those tables (freed by sht_batch_free) and fixes every address
  * it was given.  sht_batch_run enqueues on `stream` (hipStream_t, NULL =
- * default) one persistent Legendre launch whose waves take items from a
- * device counter until none are left, then one ring-FFT launch per ring
- * size class covering every request (sht_batch_stats reports the item and
- * launch counts and the waves of the persistent launch); it allocates nothing and waits for nothing, so a run can
- * be captured into a HIP graph and replayed.  Results equal
+ * default) one persistent Legendre launch per item shape, whose workgroups
+ * take items from a device counter until none are left, then at most three
+ * ring-FFT launches covering every request (sht_batch_stats reports the item
+ * and launch counts and the waves of the persistent launches); it allocates
+ * nothing and waits for nothing, so a run can be captured into a HIP graph
+ * and replayed.  Results equal
  * sht_synthesis_ex of each request on the brute-force path bit for bit.
  * o->path must be SHT_PATH_BRUTE (others: SHT_EUNSUPPORTED); o->workspace
  * must hold sht_queue_workspace_bytes() (every request's Legendre phase),

@@ -325,8 +325,8 @@ __global__ __launch_bounds__(128, (R == 4 ? 4 : 1)) void k_legendre(LegArgs a) {
 // the earliest of their chains.  Measured at 1, 2 and 4 rings, four maps:
 // L = 255 (2048 wavefronts) 12.0, 14.6, 22.4 us; L = 511 (8192) 41, 39, 69 us;
 // L = 767 (18432) 106, 97, 122 us; L = 1023 (32768) 223, 193, 220 us; L = 2047
-// (131072) -, 1329, 1352 us; one map: L = 1023 140, 115, 122 us, L = 2047 -, 797,
-// 733 us.  Above two maps the state of four rings leaves too few wavefronts.
+// (131072) -, 1329, 1352 us; one map: L = 1023 132, 113, 124 us, L = 2047 -, 764,
+// 750 us.  Above two maps the state of four rings leaves too few wavefronts.
 static int leg_rings(const sht_plan_s *p, int nb) {
     int R = p->opts.rings_per_lane;
     if (R != 1 && R != 2 && R != 4) {

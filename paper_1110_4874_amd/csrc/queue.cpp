@@ -11,12 +11,12 @@
 // one per XCD, longest first, cuts each list into chunks that shrink along
 // it (guided self-scheduling), and uploads them with one argument block per
 // pass.  sht_batch_run then enqueues
-//   1. one persistent Legendre launch: its waves take chunks of items from
-//      a device counter, their own XCD's list first, then the others' (so
-//      small requests fill in behind the long chains of large ones, with no
-//      per-request launch and one atomic per chunk), and
-//   2. one ring-FFT launch per ring size class, each covering that class's
-//      rings of every request,
+//   1. one persistent Legendre launch per item shape: its workgroups take
+//      chunks of items from a device counter, their own XCD's list first,
+//      then the others' (so small requests fill in behind the long chains of
+//      large ones, with no per-request launch and one atomic per chunk), and
+//   2. one ring-FFT launch per set of rings of one workgroup size, each
+//      covering those rings of every request,
 // all on the caller's stream, with no allocation and no host
 // synchronisation, so a run can be captured into a HIP graph and replayed.
 #include <algorithm>
@@ -587,7 +587,7 @@ int sht_batch_run(const sht_batch_t *b, void *stream) {
 int sht_batch_stats(const sht_batch_t *b, long long *items, int *launches, int *waves) {
     if (!b || !items || !launches || !waves) return fail(SHT_EINVAL, "NULL argument");
     *items = b->nitems;
-    // counter reset, one Legendre launch per wave shape present, one per ring class
+    // counter reset, one Legendre launch per item shape present, one per ring workgroup size
     *launches = 1 + (int)b->groups.size();
     *waves = 0;
     for (int v = 0; v < kQueueShapes; v++) {
