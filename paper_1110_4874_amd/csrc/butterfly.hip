@@ -24,6 +24,7 @@
 //
 // The adjoint runs the same factorization backwards in butterfly_adjoint.hip.
 #include <cstring>
+#include <type_traits>
 
 #include "butterfly_common.h"
 #include "dpp.h"
@@ -47,36 +48,12 @@ namespace sht {
 constexpr int kBfKSteps = 4;    // K-steps (4 rows of T each) per batch of loads
 constexpr int kBfIdUnroll = 4;  // identity entries per lane in flight
 
-// NT 16-row tiles of dense rows gw .. gw + 16 NT - 1 of one ID block:
-// uc[perm (k + d)] = sum_s T[s][d] v[s] (32-bit element offsets from
-// wave-uniform bases; the tile count is a template parameter so that the
-// products run back to back, without branches between them).
-template <int NT, int NB, typename S>
-__device__ __forceinline__ void dense_tiles(const S *__restrict__ v, int ES, const S *__restrict__ Tb,
-                                            const int16_t *__restrict__ pm, int kk, int nd, int gw, int lane,
-                                            S *uc) {
+// The results of NT tiles to their positions in C.
+template <int NT, int NB, typename S, int N>
+__device__ __forceinline__ void store_tiles(const typename Acc<S>::type (&acc)[N], const int16_t *__restrict__ pm, int kk,
+                                            int nd, int gw, int lane, S *uc) {
     constexpr int NC = 2 * NB;
-    constexpr int KS = kBfKSteps;
-    typedef typename Acc<S>::type acc_t;
     const int i16 = lane & 15, k4 = lane >> 4;
-    const int ic = min(i16, NC - 1);
-    acc_t acc[NT];
-#pragma unroll
-    for (int tt = 0; tt < NT; tt++) acc[tt] = acc_t{0, 0, 0, 0};
-    for (int s0 = 0; s0 < kk; s0 += 4 * KS) {
-        S av[KS][NT], bv[KS];
-#pragma unroll
-        for (int j = 0; j < KS; j++) {
-            const int s = s0 + 4 * j + k4, sc = min(s, kk - 1);
-            bv[j] = ld32(v, sc * ES + ic) * (S)(s < kk);
-#pragma unroll
-            for (int tt = 0; tt < NT; tt++) av[j][tt] = ld32(Tb, sc * nd + min(gw + 16 * tt + i16, nd - 1));
-        }
-#pragma unroll
-        for (int j = 0; j < KS; j++)
-#pragma unroll
-            for (int tt = 0; tt < NT; tt++) acc[tt] = mfma_16x16x4(av[j][tt], bv[j], acc[tt]);
-    }
     // the output rows' positions in C, all loads issued before the first
     // store (the empty asm keeps the compiler from moving each load into
     // its store's branch, which would wait on them one by one)
@@ -95,12 +72,60 @@ __device__ __forceinline__ void dense_tiles(const S *__restrict__ v, int ES, con
         }
 }
 
-template <int NB, typename S, bool ONE>
-__device__ __forceinline__ void id_block(const BfArgs<S> &a, int node, int ch, int half, int lane, S *uc, int col) {
+// NT 16-row tiles of dense rows gw .. gw + 16 NT - 1 of one ID block:
+// uc[perm (k + d)] = sum_s T[s][d] v[s] (32-bit element offsets from
+// wave-uniform bases; the tile count is a template parameter so that the
+// products run back to back, without branches between them).
+// TWO: the products of the next group of maps as well, left in `next`.
+template <int NT, bool TWO, int NB, typename S>
+__device__ __forceinline__ void dense_tiles(const S *__restrict__ v, int ES, const S *__restrict__ Tb,
+                                            const int16_t *__restrict__ pm, int kk, int nd, int gw, int lane,
+                                            S *uc, typename Acc<S>::type (&next)[4]) {
+    constexpr int NC = 2 * NB;
+    constexpr int KS = TWO ? kBfKSteps / 2 : kBfKSteps;
+    typedef typename Acc<S>::type acc_t;
+    const int i16 = lane & 15, k4 = lane >> 4;
+    const int ic = min(i16, NC - 1);
+    acc_t acc[NT];
+#pragma unroll
+    for (int tt = 0; tt < NT; tt++) {
+        acc[tt] = acc_t{0, 0, 0, 0};
+        if (TWO) next[tt] = acc_t{0, 0, 0, 0};
+    }
+    for (int s0 = 0; s0 < kk; s0 += 4 * KS) {
+        S av[KS][NT], bv[KS], bn[KS];
+#pragma unroll
+        for (int j = 0; j < KS; j++) {
+            const int s = s0 + 4 * j + k4, sc = min(s, kk - 1);
+            bv[j] = ld32(v, sc * ES + ic) * (S)(s < kk);
+            if (TWO) bn[j] = ld32(v, sc * ES + NC + ic) * (S)(s < kk);
+#pragma unroll
+            for (int tt = 0; tt < NT; tt++) av[j][tt] = ld32(Tb, sc * nd + min(gw + 16 * tt + i16, nd - 1));
+        }
+#pragma unroll
+        for (int j = 0; j < KS; j++)
+#pragma unroll
+            for (int tt = 0; tt < NT; tt++) {
+                acc[tt] = mfma_16x16x4(av[j][tt], bv[j], acc[tt]);
+                if (TWO) next[tt] = mfma_16x16x4(av[j][tt], bn[j], next[tt]);
+            }
+    }
+    store_tiles<NT, NB, S, NT>(acc, pm, kk, nd, gw, lane, uc);
+}
+
+// A pass of several groups streams T once for two of them (the second read of
+// a block missed the L2): AHEAD computes the products of the next group with
+// this one's and leaves them in `next`, in registers (blocks of up to 64 dense
+// rows; others run each group by itself), DONE takes them from there.  Half
+// the K-steps a batch and three wavefronts a SIMD keep it from spilling.  L =
+// 2047, 16 maps: level launch 693 -> 607 us, fused level 1 the same 1136 us;
+// FP32 492 -> 440 and 1019 -> 964 us (with whole batches 678 and 1173 us).
+enum class Pair { NONE, AHEAD, DONE };
+template <int NB, typename S, bool ONE, Pair PAIR = Pair::NONE>
+__device__ __forceinline__ void id_block(const BfArgs<S> &a, int node, int ch, int half, int lane, S *uc, int col,
+                                         typename Acc<S>::type (&next)[4]) {
     constexpr int NC = 2 * NB;
     constexpr int TPW = 4 / kBfHalves;  // tiles per wave
-    constexpr int KS = kBfKSteps;
-    typedef typename Acc<S>::type acc_t;
     const int *ni = a.node_i + (size_t)node * kBfNodeInts;
     const int n = ni[2] + ni[4];
     const int kk = ni[2 + ch], nd = ni[4 + ch];
@@ -127,17 +152,35 @@ __device__ __forceinline__ void id_block(const BfArgs<S> &a, int node, int ch, i
         }
     }
     // dense rows, in groups of 64
-    for (int g0 = 0; g0 < nd; g0 += 64) {
-        const int ntile = min(TPW, min(4, (nd - g0 + 15) >> 4) - half * TPW);  // tiles of this wave
-        const int gw = g0 + 16 * TPW * half;
+    auto tiles = [&](auto two, int ntile, int gw) {
+        constexpr bool TWO = decltype(two)::value;
         switch (ntile) {
-            case 1: dense_tiles<1, NB, S>(v, ES, Tb, pm, kk, nd, gw, lane, uc); break;
-            case 2: dense_tiles<2, NB, S>(v, ES, Tb, pm, kk, nd, gw, lane, uc); break;
-            case 3: dense_tiles<3, NB, S>(v, ES, Tb, pm, kk, nd, gw, lane, uc); break;
-            case 4: dense_tiles<4, NB, S>(v, ES, Tb, pm, kk, nd, gw, lane, uc); break;
+            case 1: dense_tiles<1, TWO, NB>(v, ES, Tb, pm, kk, nd, gw, lane, uc, next); break;
+            case 2: dense_tiles<2, TWO, NB>(v, ES, Tb, pm, kk, nd, gw, lane, uc, next); break;
+            case 3: dense_tiles<3, TWO, NB>(v, ES, Tb, pm, kk, nd, gw, lane, uc, next); break;
+            case 4: dense_tiles<4, TWO, NB>(v, ES, Tb, pm, kk, nd, gw, lane, uc, next); break;
             default: break;
         }
+    };
+    if constexpr (PAIR != Pair::NONE) {
+        if (nd <= 64) {
+            const int ntile = min(TPW, (nd + 15) / 16 - half * TPW), gw = 16 * TPW * half;
+            if constexpr (PAIR == Pair::AHEAD) {
+                tiles(std::true_type{}, ntile, gw);
+            } else {
+                switch (ntile) {
+                    case 1: store_tiles<1, NB, S>(next, pm, kk, nd, gw, lane, uc); break;
+                    case 2: store_tiles<2, NB, S>(next, pm, kk, nd, gw, lane, uc); break;
+                    case 3: store_tiles<3, NB, S>(next, pm, kk, nd, gw, lane, uc); break;
+                    case 4: store_tiles<4, NB, S>(next, pm, kk, nd, gw, lane, uc); break;
+                    default: break;
+                }
+            }
+            return;
+        }
     }
+    for (int g0 = 0; g0 < nd; g0 += 64)
+        tiles(std::false_type{}, min(TPW, min(4, (nd - g0 + 15) >> 4) - half * TPW), g0 + 16 * TPW * half);
 }
 
 // One residual piece on one wave: R rings per lane (lane j: rings j + 64 r,
@@ -355,6 +398,22 @@ __global__ __launch_bounds__(kBfResThreads) void k_bf_residual(BfArgs<S> a, long
     residual_piece<NB, S>(a, tk, threadIdx.x & 63, stg_all[w], col0);
 }
 
+// The groups of a pass, two at a time where there are two.
+template <bool ONE, typename F>
+__device__ __forceinline__ void for_groups(int G, F &&group) {
+    typedef std::integral_constant<Pair, Pair::NONE> none_t;
+    if constexpr (ONE) {
+        group(none_t{}, 0);
+    } else {
+        int g = 0;
+        for (; g + 1 < G; g += 2) {
+            group(std::integral_constant<Pair, Pair::AHEAD>{}, g);
+            group(std::integral_constant<Pair, Pair::DONE>{}, g + 1);
+        }
+        if (g < G) group(none_t{}, g);
+    }
+}
+
 // One workgroup of 2 kBfHalves waves per pair node (wave w: child w % 2,
 // half w / 2): per group of NB maps, each child writes its share of u into
 // its own LDS copy, and the two copies are summed into the next level's
@@ -371,9 +430,11 @@ __device__ __forceinline__ void level_node_g(const BfArgs<S> &a, int node) {
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int ES = ONE ? NC : a.ES, G = ONE ? 1 : a.G;
     S *__restrict__ out = a.ws + (size_t)ni[6] * ES;
-    for (int g = 0; g < G; g++) {
+    typename Acc<S>::type next[4];
+    auto group = [&](auto pair, int g) {
         if (g) __syncthreads();  // the previous group's sums have been read out of LDS
-        id_block<NB, S, ONE>(a, node, w & 1, w >> 1, threadIdx.x & 63, (w & 1) ? u1 : u0, g * NC);
+        id_block<NB, S, ONE, decltype(pair)::value>(a, node, w & 1, w >> 1, threadIdx.x & 63, (w & 1) ? u1 : u0, g * NC,
+                                                    next);
         __syncthreads();
         if (ONE) {
             for (int e = threadIdx.x; e < n * NC; e += kBfLevelThreads) out[e] = u0[e] + u1[e];
@@ -381,14 +442,14 @@ __device__ __forceinline__ void level_node_g(const BfArgs<S> &a, int node) {
             for (int e = threadIdx.x; e < n * NC; e += kBfLevelThreads)
                 out[(size_t)(e / NC) * ES + g * NC + e % NC] = u0[e] + u1[e];
         }
-    }
+    };
+    for_groups<ONE>(G, group);
 }
-
 
 // ONE: the pass has a single group of maps (separate instantiations, so the
 // common case keeps its constant strides and its register count).
 template <int NB, typename S, bool ONE>
-__global__ __launch_bounds__(kBfLevelThreads) void k_bf_level(BfArgs<S> a, long long n0) {
+__global__ __launch_bounds__(kBfLevelThreads, ONE ? 1 : 3) void k_bf_level(BfArgs<S> a, long long n0) {
     level_node_g<NB, S, ONE>(a, (int)(n0 + blockIdx.x));
 }
 
@@ -406,7 +467,7 @@ __global__ __launch_bounds__(kBfLevelThreads) void k_bf_level_list(BfArgs<S> a, 
 constexpr int kBfFoldThreads = 2 * kBfLevelThreads;
 
 template <int NB, typename S, bool ONE>
-__global__ __launch_bounds__(kBfFoldThreads) void k_bf_level1_fold(BfArgs<S> a, const int4 *__restrict__ units,
+__global__ __launch_bounds__(kBfFoldThreads, ONE ? 1 : 3) void k_bf_level1_fold(BfArgs<S> a, const int4 *__restrict__ units,
                                                                    long long u0, int batch, int nbatch) {
     constexpr int NC = 2 * NB;
     extern __shared__ char lds_raw[];
@@ -418,10 +479,11 @@ __global__ __launch_bounds__(kBfFoldThreads) void k_bf_level1_fold(BfArgs<S> a, 
     const int par = w / (2 * kBfHalves), wc = w % (2 * kBfHalves);
     const int m = batch + un.w * nbatch, k0 = un.z;
     const int G = ONE ? 1 : a.G;
-    for (int g = 0; g < G; g++) {
+    typename Acc<S>::type next[4];
+    auto group = [&](auto pair, int g) {
         if (g) __syncthreads();  // the previous group's fold has read LDS
-        id_block<NB, S, ONE>(a, par ? un.y : un.x, wc & 1, wc >> 1, threadIdx.x & 63,
-                             uE + (size_t)(2 * par + (wc & 1)) * n * NC, g * NC);
+        id_block<NB, S, ONE, decltype(pair)::value>(a, par ? un.y : un.x, wc & 1, wc >> 1, threadIdx.x & 63,
+                                                    uE + (size_t)(2 * par + (wc & 1)) * n * NC, g * NC, next);
         __syncthreads();
         const int mb = a.map0 + g * NB;
         for (int e = threadIdx.x; e < n * NB; e += kBfFoldThreads) {
@@ -435,7 +497,8 @@ __global__ __launch_bounds__(kBfFoldThreads) void k_bf_level1_fold(BfArgs<S> a, 
             a.q[((size_t)k * (a.L + 1) + m) * a.nmaps + mb + b] = make_double2(er + orr, ei + oi);
             if (ks != k) a.q[((size_t)ks * (a.L + 1) + m) * a.nmaps + mb + b] = make_double2(er - orr, ei - oi);
         }
-    }
+    };
+    for_groups<ONE>(G, group);
 }
 
 // Fold of the listed slots of one batch: slot j holds order m = batch + j nbatch.
@@ -497,8 +560,9 @@ __global__ __launch_bounds__(kBfFoldThreads) void k_bfq_level1_fold(const BfArgs
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int par = w / (2 * kBfHalves), wc = w % (2 * kBfHalves);
     const int m = un.w, k0 = un.z;  // one order batch: slot j holds order j
+    typename Acc<S>::type next[4];
     id_block<NB, S, true>(a, par ? un.y : un.x, wc & 1, wc >> 1, threadIdx.x & 63,
-                          uE + (size_t)(2 * par + (wc & 1)) * n * NC, 0);
+                          uE + (size_t)(2 * par + (wc & 1)) * n * NC, 0, next);
     __syncthreads();
     for (int e = threadIdx.x; e < n * NB; e += kBfFoldThreads) {
         const int c = e / NB, b = e % NB;

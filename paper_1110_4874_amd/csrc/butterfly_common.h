@@ -28,9 +28,9 @@ struct BfArgs {
     // A pass transforms G groups of NB maps (maps map0 .. map0 + G NB - 1):
     // every workspace entry holds ES = 2 NB G values (re, im per map) and
     // group g owns values [2 NB g, 2 NB (g + 1)) of each entry.  The
-    // interpolation matrices are streamed from HBM once per pass; the level
-    // workgroups loop over the groups of their node (the repeated reads of a
-    // node's blocks hit the caches).
+    // interpolation matrices are streamed once per pass or pair of groups; the level
+    // workgroups loop over the groups of their node, in synthesis two groups
+    // to a read of its blocks.
     int ES, G;
     // level-1 and fold lists of the plan (work-queue batches address them
     // through the argument block)
