@@ -11,7 +11,9 @@ namespace sht {
 // through the DPP broadcast (row_newbcast), so the per-row operands need
 // neither one LDS broadcast read per value nor a register each.  In each asm
 // block the leading s_nop gives the two wait states that a DPP read needs
-// after a vector-ALU write of rv, and nothing can be scheduled inside it.
+// after a vector-ALU write of rv, and nothing can be scheduled inside it.  The
+// accumulators are early-clobbered: an accumulator that starts from p or rv
+// would else share its register, which the block's later FMAs still read.
 #define SHT_FMAC_BC(c, o) "v_fmac_f64_dpp %" #o ", %[rv], %[p] row_newbcast:" #c " row_mask:0xf bank_mask:0xf\n"
 template <int N, int C0 = 0>
 __device__ __forceinline__ void fmac_row_bcast(double *acc, double rv, double p) {
@@ -21,42 +23,44 @@ __device__ __forceinline__ void fmac_row_bcast(double *acc, double rv, double p)
         fmac_row_bcast<N - 8, C0 + 8>(acc + 8, rv, p);
     } else if constexpr (C0 == 8) {
         if constexpr (N == 2)
-            asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) : "+v"(acc[0]), "+v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
+            asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1)
+                : "+&v"(acc[0]), "+&v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
         else if constexpr (N == 4)
             asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3)
-                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
                 : [rv] "v"(rv), [p] "v"(p));
         else if constexpr (N == 6)
             asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3) SHT_FMAC_BC(12, 4)
                     SHT_FMAC_BC(13, 5)
-                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5])
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3]), "+&v"(acc[4]), "+&v"(acc[5])
                 : [rv] "v"(rv), [p] "v"(p));
         else if constexpr (N == 8)
             asm("s_nop 1\n" SHT_FMAC_BC(8, 0) SHT_FMAC_BC(9, 1) SHT_FMAC_BC(10, 2) SHT_FMAC_BC(11, 3) SHT_FMAC_BC(12, 4)
                     SHT_FMAC_BC(13, 5) SHT_FMAC_BC(14, 6) SHT_FMAC_BC(15, 7)
-                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-                  "+v"(acc[7])
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3]), "+&v"(acc[4]), "+&v"(acc[5]),
+                  "+&v"(acc[6]), "+&v"(acc[7])
                 : [rv] "v"(rv), [p] "v"(p));
         else
             static_assert(N == 2, "unsupported lane count");
     } else {
         static_assert(C0 == 0, "rows are read from lane 0 or 8");
         if constexpr (N == 2)
-            asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) : "+v"(acc[0]), "+v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
+            asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1)
+                : "+&v"(acc[0]), "+&v"(acc[1]) : [rv] "v"(rv), [p] "v"(p));
         else if constexpr (N == 4)
             asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3)
-                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3])
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
                 : [rv] "v"(rv), [p] "v"(p));
         else if constexpr (N == 6)
             asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3) SHT_FMAC_BC(4, 4)
                     SHT_FMAC_BC(5, 5)
-                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5])
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3]), "+&v"(acc[4]), "+&v"(acc[5])
                 : [rv] "v"(rv), [p] "v"(p));
         else
             asm("s_nop 1\n" SHT_FMAC_BC(0, 0) SHT_FMAC_BC(1, 1) SHT_FMAC_BC(2, 2) SHT_FMAC_BC(3, 3) SHT_FMAC_BC(4, 4)
                     SHT_FMAC_BC(5, 5) SHT_FMAC_BC(6, 6) SHT_FMAC_BC(7, 7)
-                : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "+v"(acc[4]), "+v"(acc[5]), "+v"(acc[6]),
-                  "+v"(acc[7])
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3]), "+&v"(acc[4]), "+&v"(acc[5]),
+                  "+&v"(acc[6]), "+&v"(acc[7])
                 : [rv] "v"(rv), [p] "v"(p));
     }
 }
