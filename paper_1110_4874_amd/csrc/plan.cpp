@@ -56,7 +56,7 @@ void parallel_for(long n, int nthreads, void (*fn)(long, void *), void *ctx) {
 // integer ratios, pixel count J, half-pixel shift s (phi_j = pi(2j+s)/J),
 // first pixel index.
 // ---------------------------------------------------------------------
-static void ring_geometry(int N, int i, ld *z, ld *sin2, int *J, int *s, long long *off) {
+void ring_geometry(int N, int i, ld *z, ld *sin2, int *J, int *s, long long *off) {
     int ii = (i > 2 * N) ? 4 * N - i : i;  // northern counterpart
     ld zz, w;
     if (ii < N) {

@@ -322,9 +322,39 @@ uint64_t header_hash(const FileHeader &h) {
     return hash_bytes((const unsigned char *)&h, offsetof(FileHeader, header_hash), 0x5a5a5a5a);
 }
 
+// Ring tables: the pixel layout is the grid's own, and every transform (of
+// half length J/2, a power of two, or of the chirp convolution's size) has its
+// twiddles, chirp and spectrum within the tables.  The upload permutes the
+// spectra on the host and sorts the rings into launches by these sizes.
+bool rings_consistent(const sht_plan_s *p) {
+    if (p->tw_log < 1 || p->tw_log > 12 || p->tw.size() != 2 * ((size_t)1 << (p->tw_log - 1))) return false;
+    if (p->ring_bs_off.size() != (size_t)p->nrings || p->ring_chirp_off.size() != (size_t)p->nrings) return false;
+    const long long nbs = (long long)(p->bs_table.size() / 2), nch = (long long)(p->chirp.size() / 2);
+    for (int r = 0; r < p->nrings; r++) {
+        long double z, w;
+        int J, s;
+        long long off;
+        ring_geometry(p->nside, r + 1, &z, &w, &J, &s, &off);
+        if (p->ring_J[r] != J || p->ring_s[r] != s || p->ring_off[r] != off) return false;
+        const int n = J / 2, h = n / 2;
+        int S = n;
+        if (n & (n - 1)) {
+            for (S = 1; S < 2 * h - 1;) S *= 2;
+            if (p->ring_M[r] != S) return false;
+            const long long b = p->ring_bs_off[r], c = p->ring_chirp_off[r];
+            if (b < 0 || b > nbs - S || c < 0 || c > nch - h) return false;
+        } else if (p->ring_M[r] != 0) {
+            return false;
+        }
+        if (S > 1 << p->tw_log) return false;
+    }
+    return true;
+}
+
 // Cross-field consistency that the checksum cannot vouch for (a file from a
 // buggy writer with a valid checksum must still not drive the kernels out of
-// bounds): table sizes against the geometry the header states.
+// bounds): table sizes against the geometry the header states, and the values
+// that host and kernels index with.
 bool consistent(const sht_plan_s *p) {
     const size_t L = (size_t)p->L, np = (size_t)p->n_north_pad;
     if (p->nrings != 4 * p->nside - 1 || p->n_north != 2 * p->nside) return false;
@@ -336,7 +366,7 @@ bool consistent(const sht_plan_s *p) {
     if ((size_t)p->coef_off[L + 1] * 4 != p->coef_hi.size() || p->coef_lo.size() != p->coef_hi.size()) return false;
     if (p->start_idx.size() != (L + 1) * 2 * np || p->start_val.size() != (L + 1) * 4 * np) return false;
     if (p->grp_lo.size() != (L + 1) * (np / kLanes)) return false;
-    if (p->tw.size() != 2 * ((size_t)1 << (p->tw_log - 1))) return false;
+    if (!rings_consistent(p)) return false;
     for (const auto &c : p->classes)
         for (int r : c.rings)
             if (r < 0 || r >= p->nrings) return false;
