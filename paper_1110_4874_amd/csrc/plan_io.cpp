@@ -351,6 +351,38 @@ bool rings_consistent(const sht_plan_s *p) {
     return true;
 }
 
+// Chain tables: the coefficient runs are laid out as the build lays them out
+// (device tables of the same layout are derived from them), chains start at a
+// chunk boundary of their own run (the start indexes those tables), and the
+// groups' ranges are those of their chains.
+bool chains_consistent(const sht_plan_s *p) {
+    const int L = p->L, np = p->n_north_pad, ng = np / kLanes;
+    if (p->n_dd_rings < 0 || p->n_dd_rings > p->n_north) return false;
+    if (p->n_dd_groups != (p->n_dd_rings + kLanes - 1) / kLanes || p->n_dd_pad != p->n_dd_groups * kLanes) return false;
+    if (p->z2_lo.size() != (size_t)np || p->grp_hi.size() != p->grp_lo.size()) return false;
+    if (p->start_lo.size() != (size_t)(L + 1) * 4 * std::max(p->n_dd_pad, 1)) return false;
+    if (p->coef_off[0] != 0) return false;
+    for (int m = 0; m <= L; m++) {
+        const long long cnt = (L - m + 1) + kCoefPad;
+        if (p->coef_off[m + 1] != p->coef_off[m] + cnt + (cnt & 1)) return false;
+        for (int g = 0; g < ng; g++) {
+            int lo = kDead, hi = -1;
+            for (int t = 0; t < 2; t++) {
+                const int n = L - m - t >= 0 ? (L - m - t) / 2 + 1 : 0;
+                const int *s = p->start_idx.data() + (size_t)(2 * m + t) * np + g * kLanes;
+                for (int k = 0; k < kLanes; k++) {
+                    if (s[k] == kDead) continue;
+                    if (s[k] < 0 || s[k] >= n || s[k] % kChunk || g * kLanes + k >= p->n_north) return false;
+                    lo = std::min(lo, s[k]);
+                    hi = std::max(hi, s[k]);
+                }
+            }
+            if (p->grp_lo[(size_t)m * ng + g] != lo || p->grp_hi[(size_t)m * ng + g] != hi) return false;
+        }
+    }
+    return true;
+}
+
 // Cross-field consistency that the checksum cannot vouch for (a file from a
 // buggy writer with a valid checksum must still not drive the kernels out of
 // bounds): table sizes against the geometry the header states, and the values
@@ -363,10 +395,11 @@ bool consistent(const sht_plan_s *p) {
         p->ring_off.size() != (size_t)p->nrings || p->ring_M.size() != (size_t)p->nrings)
         return false;
     if (p->z2_hi.size() != np || p->coef_off.size() != L + 2) return false;
+    if (p->n_north_pad != (p->n_north + kLanes - 1) / kLanes * kLanes) return false;
     if ((size_t)p->coef_off[L + 1] * 4 != p->coef_hi.size() || p->coef_lo.size() != p->coef_hi.size()) return false;
     if (p->start_idx.size() != (L + 1) * 2 * np || p->start_val.size() != (L + 1) * 4 * np) return false;
     if (p->grp_lo.size() != (L + 1) * (np / kLanes)) return false;
-    if (!rings_consistent(p)) return false;
+    if (!chains_consistent(p) || !rings_consistent(p)) return false;
     for (const auto &c : p->classes)
         for (int r : c.rings)
             if (r < 0 || r >= p->nrings) return false;

@@ -165,3 +165,18 @@ def test_ring_tables(sht, brute, tmp_path, change):
     f = File(brute)
     change(f)
     refused(sht, f, tmp_path)
+
+
+# L = 40, nside 12: 24 north rings in 64 lanes; order 0 has 41 + 24 coefficients (66 with padding)
+@pytest.mark.parametrize("change", [
+    changed("coef_off", "i8", 0, 2), changed("coef_off", "i8", 5, 1 << 40), changed("coef_off", "i8", 5, -4),
+    changed("start_idx", "i4", 0, -8), changed("start_idx", "i4", 0, 4), changed("start_idx", "i4", 0, 24),
+    changed("start_idx", "i4", 63, 0x3FFFFFFE), changed("start_idx", "i4", -1, 0),
+    changed("grp_lo", "i4", 0, -8), changed("grp_lo", "i4", 3, 8), changed("grp_hi", "i4", 0, 1 << 20), cut("grp_hi", "i4"),
+    changed("n_dd_groups", "i4", 0, 1), changed("n_dd_groups", "i4", 0, -1), changed("n_dd_pad", "i4", 0, 64),
+    changed("n_dd_rings", "i4", 0, 25), cut("start_lo", "f8"), cut("z2_lo", "f8"),
+], ids=range(18))
+def test_chain_tables(sht, brute, tmp_path, change):
+    f = File(brute)
+    change(f)
+    refused(sht, f, tmp_path)
