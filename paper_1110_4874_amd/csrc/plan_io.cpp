@@ -383,6 +383,22 @@ bool chains_consistent(const sht_plan_s *p) {
     return true;
 }
 
+// Lane records {node or ring, first row} of residual and node tasks (unused
+// lanes: a first row past every task).
+bool lanes_consistent(const std::vector<int> &lane, long long count) {
+    for (size_t i = 0; i + 1 < lane.size(); i += 2)
+        if (lane[i] < 0 || lane[i] >= count || lane[i + 1] < 0) return false;
+    return true;
+}
+
+// Ranges of the nb batches in a list of n entries.
+bool ranges_consistent(const std::vector<long long> &off, int nb, size_t n) {
+    if (off.size() != (size_t)nb + 1 || off[0] != 0 || off[nb] != (long long)n) return false;
+    for (int i = 0; i < nb; i++)
+        if (off[i + 1] < off[i]) return false;
+    return true;
+}
+
 // Cross-field consistency that the checksum cannot vouch for (a file from a
 // buggy writer with a valid checksum must still not drive the kernels out of
 // bounds): table sizes against the geometry the header states, and the values
@@ -413,7 +429,7 @@ bool consistent(const sht_plan_s *p) {
             return false;
         if (ip.lamN.size() != (L + 1) * 2 * np || ip.sub.size() % 8 || ip.lane.size() != ip.val.size()) return false;
         if (ip.dd_task.size() % 8 || ip.dd_lane.size() * 2 != ip.dd_val.size()) return false;
-        if (ip.patch.size() % 4) return false;
+        if (ip.patch.size() % 4 || !lanes_consistent(ip.lane, ip.nodes)) return false;
         for (size_t i = 0; i < ip.patch.size(); i += 4) {
             const int m = ip.patch[i], k = ip.patch[i + 1];
             if (m < 0 || m > (int)L || k < 0 || k >= p->n_north) return false;
@@ -429,7 +445,11 @@ bool consistent(const sht_plan_s *p) {
         if (b.node_i.size() % kBfNodeInts || b.res_task.size() % 8 || b.res_sub.size() % 8) return false;
         if (b.lv_off.size() != (size_t)b.nbatch * (kBfMaxLv + 1) + 1) return false;
         if (b.batch_sub.size() != (size_t)b.nbatch + 1 || b.batch_task.size() != (size_t)b.nbatch + 1) return false;
-        if (b.res_lane.size() != b.res_val.size()) return false;
+        if (b.res_lane.size() != b.res_val.size() || !lanes_consistent(b.res_lane, p->n_north)) return false;
+        if (b.f1_unit.size() % 4 || !ranges_consistent(b.f1_off, b.nbatch, b.f1_unit.size() / 4) ||
+            !ranges_consistent(b.l1_off, b.nbatch, b.l1_plain.size()) ||
+            !ranges_consistent(b.fold_off, b.nbatch, b.fold_slot.size()))
+            return false;
     }
     return true;
 }

@@ -180,3 +180,23 @@ def test_chain_tables(sht, brute, tmp_path, change):
     f = File(brute)
     change(f)
     refused(sht, f, tmp_path)
+
+
+@pytest.fixture(scope="module")
+def compressed(sht, tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("plans") / "c.plan")
+    p = sht.Plan(47, 12, 1e-6, max_levels=1, host_only=True)
+    assert p.info()["bf_depth_hist"][1] > 0
+    p.save(path)
+    return path
+
+
+@pytest.mark.parametrize("change", [
+    changed("f1_off", "i8", 0, -1), changed("f1_off", "i8", -1, 1 << 40), cut("f1_off", "i8"), cut("f1_unit", "i4"),
+    changed("l1_off", "i8", -1, 1 << 40), changed("fold_off", "i8", 0, 1),
+    changed("res_lane", "i4", 1, -8), changed("res_lane", "i4", 0, 24), changed("res_lane", "i4", 0, -1),
+], ids=range(9))
+def test_compressed_tables(sht, compressed, tmp_path, change):
+    f = File(compressed)
+    change(f)
+    refused(sht, f, tmp_path)
