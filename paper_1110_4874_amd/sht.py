@@ -266,11 +266,18 @@ class Plan:
         d["bf_level_nodes"] = list(inf.bf_level_nodes)
         return d
 
+    def _chain(self, m, t, x):
+        """x as the n_t values of chain (m, t) that the library reads; a shorter x ends in zeros."""
+        import numpy as np
+        n = max((self.L - int(m) - int(t)) // 2 + 1, 0)
+        x = np.asarray(x, dtype=np.float64).ravel()
+        return np.concatenate([x, np.zeros(n - x.size)]) if x.size < n else np.ascontiguousarray(x)
+
     def butterfly_apply_host(self, m, t, x):
         """Host evaluation of Lambda^T x for (m, parity t) from the compressed
         records (private test entry point); x: numpy float64 of length n_t."""
         import numpy as np
-        x = np.ascontiguousarray(x, dtype=np.float64)
+        x = self._chain(m, t, x)
         y = np.zeros(2 * self.nside, dtype=np.float64)
         _check(load().sht_debug_butterfly_apply(self._h, int(m), int(t), x.ctypes.data_as(_c.c_void_p),
                                                 y.ctypes.data_as(_c.c_void_p)))
@@ -278,9 +285,9 @@ class Plan:
 
     def interp_apply_host(self, m, t, x):
         """Host evaluation of q^t_m on the north rings through the plan's
-        interpolation form (private test entry point)."""
+        interpolation form (private test entry point); x as in butterfly_apply_host."""
         import numpy as np
-        x = np.ascontiguousarray(x, dtype=np.float64)
+        x = self._chain(m, t, x)
         y = np.zeros(2 * self.nside, dtype=np.float64)
         _check(load().sht_debug_interp_apply(self._h, int(m), int(t), x.ctypes.data_as(_c.c_void_p),
                                              y.ctypes.data_as(_c.c_void_p)))
