@@ -541,7 +541,7 @@ static std::vector<int> fold_unit_order(const BflyPlan &f) {
 // recurrence's is 1e-12 and 3e-13; the two meet at 0.7.
 constexpr double kPoleSin = 0.3, kPoleSinMax = 0.6;
 
-int upload_tables(sht_plan_s *p) {
+static hipError_t upload_all(sht_plan_s *p, size_t *bytes) {
     size_t b = 0;
     hipError_t e = hipSuccess;
 #define UP(d, h) \
@@ -688,7 +688,18 @@ int upload_tables(sht_plan_s *p) {
             f.host_T_kept = false;
         }
     }
-    p->device_bytes = b;
+    *bytes = b;
+    return e;
+}
+
+int upload_tables(sht_plan_s *p) {
+    hipError_t e;
+    try {
+        e = upload_all(p, &p->device_bytes);
+    } catch (const std::bad_alloc &) {  // no exception may leave the C entry points
+        free_device_tables(p);
+        return fail(SHT_ENOMEM, "out of host memory while uploading the plan");
+    }
     if (e != hipSuccess) {
         free_device_tables(p);
         return fail(e == hipErrorOutOfMemory ? SHT_ENOMEM : SHT_EDEVICE,
