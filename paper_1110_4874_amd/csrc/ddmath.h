@@ -35,6 +35,20 @@ __host__ __device__ __forceinline__ dd dd_add(dd a, dd b) {
     double e = s.l + (a.l + b.l);
     return fast_two_sum(s.h, e);
 }
+// The same without the final renormalisation: the low part may reach a few
+// units in the last place of the high one.  For chains that renormalise once a
+// step (a product and a sum of such operands still lose only a few 2^-104).
+__host__ __device__ __forceinline__ dd dd_mul_raw(dd a, dd b) {
+    double p = a.h * b.h;
+    double e = __builtin_fma(a.h, b.h, -p);
+    e = __builtin_fma(a.h, b.l, e);
+    e = __builtin_fma(a.l, b.h, e);
+    return {p, e};
+}
+__host__ __device__ __forceinline__ dd dd_add_raw(dd a, dd b) {
+    dd s = two_sum(a.h, b.h);
+    return {s.h, s.l + (a.l + b.l)};
+}
 __host__ __device__ __forceinline__ dd dd_neg(dd a) { return {-a.h, -a.l}; }
 __host__ __device__ __forceinline__ dd dd_sub(dd a, dd b) { return dd_add(a, dd_neg(b)); }
 // a / b: three quotient digits (Newton-free long division, each digit a

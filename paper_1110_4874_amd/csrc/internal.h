@@ -258,7 +258,7 @@ struct LegArgs {
     int L, nrings, n_north, np, n_dd_pad, n_pole_pad, ng;
     int nmaps, map0;   // map stride of alm/q and first map of this pass
     int pole_groups;   // 64-ring groups run by the split recurrence (from the pole)
-    int dd_groups;     // or, in double-double
+    int dd_groups;     // or, in double-double (a block each)
     int first_plain;   // the groups after them run the plain recurrence
     int pole_blocks, plain_blocks;  // blocks of R groups of each
 };
@@ -356,24 +356,23 @@ hipError_t fill_scaled_coef(const sht_plan_s *p);
 // uploaded ones.
 hipError_t fill_pole_tables(const sht_plan_s *p);
 // Work-queue batches on the brute-force path: one persistent launch per pass
-// shape (0, 1: double-double waves of 2 or 1 maps; 2: workgroups of 8 maps;
-// 3 .. 8: of 6 .. 1 maps).
-constexpr int kQueueShapes = 9;
+// shape (0: workgroups of 8 maps; 1 .. 6: of 6 .. 1 maps).
+constexpr int kQueueShapes = 7;
+constexpr int kQueueThreads = 128;  // threads of a workgroup
 // Internal streams for fork/join inside one call (batch.cpp).
 constexpr int kMaxStreams = 8;
 int pool_streams(int dev, hipStream_t *out);
-int queue_shape(bool dd, int nb);
+int queue_shape(int nb);
 int queue_rings(int nb, int R);  // rings per lane of a pass of nb maps
-int queue_threads(int shape);    // threads of a workgroup of the shape's launch
-hipError_t legendre_queue_grid(int shape, int rings_per_lane, int *grid);
-// items {pass, m, ring block, first map}: per shape eight lists back to back,
+hipError_t legendre_queue_grid(int shape, int rings_per_lane, bool dd, int *grid);
+// items {pass, m, ring block, 0}: per shape eight lists back to back,
 // cut into chunks; chunk c covers items [chunk_off[c], chunk_off[c+1]) and
 // list x of shape v the chunks [list_off[9v+x], list_off[9v+x+1]); counter:
-// 9 x 8 x 16 unsigned of device memory, cleared by launch_queue_reset before
-// the shapes' launches; grid: workgroups of the shape's launch (0: no items).
+// kQueueShapes x 8 x 16 unsigned of device memory, cleared by launch_queue_reset before
+// the shapes' launches; dd: some pass has double-double groups; grid: workgroups of the shape's launch (0: no items).
 hipError_t launch_queue_reset(unsigned *counter, hipStream_t st);
 hipError_t launch_legendre_queue(int shape, const LegArgs *passes, const int4 *items, const unsigned *chunk_off,
-                                 const unsigned *list_off, unsigned *counter, int rings_per_lane, int grid,
+                                 const unsigned *list_off, unsigned *counter, int rings_per_lane, bool dd, int grid,
                                  hipStream_t st);
 RingArgs ring_args(const sht_plan_s *p, int nmaps, const double *q, double *map);
 int ring_group_entries(int S, int T);  // LDS entries of a group of T threads, transforms up to S

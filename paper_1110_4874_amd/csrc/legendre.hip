@@ -35,11 +35,17 @@
 // h_l r_{l-2} P~_{l-2} exactly, so
 //   P~_{l+2} = r_l P~_l + d_l,   d_{l+2} = h_{l+2} d_l - sin^2 beta_{l+2} P~_{l+2}
 // where sin^2(theta) enters with its own relative accuracy (in the scaled
-// variables with the coefficients scaled likewise).  Four FP64
-// operations a step instead of three; relative errors of 2e-15 to 2e-14 at
-// L = 4095 for sin(theta) <= 0.1 (double-double arithmetic, which these rings
-// ran before at about 45 operations a step and chain, made one wave's serial
-// chain the length of the whole launch below L ~ 2000).
+// variables with the coefficients scaled likewise).  Four FP64 operations a
+// step instead of two; relative errors of 2e-15 to 2e-14 at L = 4095 for
+// sin(theta) <= 0.1.
+//
+// Plans whose threshold the caller set, and polar groups that reach too far
+// from the pole for the split recurrence, run those groups in double-double (31
+// operations a step, one ring a lane, with priority over the other waves: the
+// chain is serial).  Bound by the issue of those operations where most rings
+// are such, else by the chain.  As launches of their own, with operands read
+// step by step, they took 540 us at L = 1400, nside = 40, one map, and 2017 us
+// at L = 4095, nside = 32 (whole syntheses); so 190 and 749 us.
 #include <type_traits>
 
 #include "ddmath.h"
@@ -48,54 +54,71 @@
 
 namespace sht {
 
-// Staged row of a chain step: a_lm of NB maps (2 NB values), then the two
-// (split recurrence: three) coefficients, in rows of 8, 16 or 32 doubles.  Two
+// The recurrence of a ring group: scaled two-step, split about the pole, or
+// two-step in double-double.
+enum class Chain { PLAIN, SPLIT, DD };
+
+// Staged row of a chain step: a_lm of NB maps (2 NB values), then the
+// coefficients (two; split recurrence three; double-double three high and
+// three low parts), in rows of 8, 16 or 32 doubles.  Two
 // rows of 8 share one 16-lane read, and half as many values are fetched and
 // staged (Legendre phase with rows of 16 and of 8: L = 1023, 1 map 121 and 113
 // us, 3 maps 176 and 165; L = 2047, 1 map 780 and 750, 2 maps 961 and 919).
-template <int NB, bool POLE>
+constexpr int leg_coefs(Chain K) { return K == Chain::DD ? 6 : K == Chain::SPLIT ? 3 : 2; }
+template <int NB, Chain K>
 constexpr int leg_row() {
-    constexpr int v = 2 * NB + (POLE ? 3 : 2);
+    constexpr int v = 2 * NB + leg_coefs(K);
     return v <= 8 ? 8 : v <= 16 ? 16 : 32;
 }
 // LDS doubles of one wave: two staged chunks, and the chains' start values
-// (R rings) whose room holds one ring group's sums at the fold.
-template <int NB, int R>
+// (R rings, or one in double-double) whose room holds one ring group's sums at
+// the fold.  DD: of a kernel that has double-double blocks.
+template <int NB, int R, bool DD>
 constexpr int leg_wave_lds() {
-    return 2 * kChunk * leg_row<NB, true>() + (R * 128 > 128 * NB ? R * 128 : 128 * NB);
+    constexpr int sums = 128 * NB, starts = 128 * (DD && R < 2 ? 2 : R);
+    return 2 * kChunk * leg_row<NB, DD ? Chain::DD : Chain::SPLIT>() + (starts > sums ? starts : sums);
 }
 
 // One workgroup: order m, rings of the 64-ring groups g0 .. min(g0 + R, gend) - 1
-// (R per lane); wave t = threadIdx.x / 64 runs parity t.  POLE: the split
-// recurrence of the file's head, else the scaled two-step recurrence.
-template <int NB, int R, bool POLE>
+// (R per lane); wave t = threadIdx.x / 64 runs parity t.  W: LDS doubles of a wave.
+template <int NB, int R, Chain K, int W>
 __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const int g0, const int gend, double *lds) {
+    constexpr bool SPLIT = K == Chain::SPLIT, DD = K == Chain::DD;
     constexpr int NC = 2 * NB;
-    constexpr int CW = leg_row<NB, POLE>(), CS = kChunk * CW, E = CS / 64;
-    constexpr int CO = NC % 16;           // lane of the first coefficient within its 16-lane row
-    static_assert(NC + (POLE ? 3 : 2) <= 16 || NC == 16, "the coefficients share one 16-lane row");
+    constexpr int CW = leg_row<NB, K>(), CS = kChunk * CW, E = CS / 64;
+    constexpr int CB = CW == 32 ? 16 : NC;  // component of the first coefficient
+    constexpr int CO = CB % 16;             // its lane within its 16-lane row
+    static_assert(CO + leg_coefs(K) <= 16, "the coefficients share one 16-lane row");
+    static_assert(2 * CS + 128 * NB <= W && 2 * CS + 128 * (DD ? 2 : R) <= W, "chunks, sums and starts fit");
+    static_assert(!DD || R == 1, "one ring a lane in double-double");
     constexpr int KU = 4;                 // rows read from LDS at once
     constexpr int PK = CW < 16 ? 16 / CW : 1;  // rows within one 16-lane read
     const int t = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int L = a.L;
     const int n = L - m - t >= 0 ? (L - m - t) / 2 + 1 : 0;  // chain length
-    double *room = lds + t * leg_wave_lds<NB, R>();
-    double *stg = room + (leg_wave_lds<NB, R>() - 2 * CS);
+    double *room = lds + t * W;
+    double *stg = room + (W - 2 * CS);
     const double4 *cf = reinterpret_cast<const double4 *>(a.coef_sc) + a.coef_off[m] + t;
 
     int sid[R], lo = kDead, hi = -1;
     double x[R], P0[R], P1[R], acc[R][NC];
+    double xl = 0.0, P0l = 0.0, P1l = 0.0, s0l = 0.0, s1l = 0.0;  // low parts (double-double)
     const size_t row = (size_t)(2 * m + t);
     const double *v0p = a.start_val + row * 2 * a.np;
-    const double *v1p = POLE ? a.start_d + row * a.n_pole_pad : v0p + a.np;
+    const double *v1p = SPLIT ? a.start_d + row * a.n_pole_pad : v0p + a.np;
     double s0[R], s1[R];
 #pragma unroll
     for (int r = 0; r < R; r++) {  // groups past the last repeat it and never start
         const int g = min(g0 + r, gend - 1), k = g * kLanes + lane;
         sid[r] = a.start_idx[row * a.np + k] | (g0 + r < gend ? 0 : kDead);
-        x[r] = POLE ? a.s2[k] : a.z2_hi[k];
+        x[r] = SPLIT ? a.s2[k] : a.z2_hi[k];
         s0[r] = v0p[k];
         s1[r] = v1p[k];
+        if constexpr (DD) {
+            xl = a.z2_lo[k];
+            s0l = a.start_lo[row * 2 * a.n_dd_pad + k];
+            s1l = a.start_lo[(row * 2 + 1) * a.n_dd_pad + k];
+        }
         lo = min(lo, a.grp_lo[(size_t)m * a.ng + g]);
         hi = max(hi, a.grp_hi[(size_t)m * a.ng + g]);
         P0[r] = P1[r] = 0.0;
@@ -116,10 +139,16 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             base = a.alm + 2 * (((size_t)m * (2 * L + 3 - m) / 2 + t) * a.nmaps + a.map0) + comp;
             stride = 4u * (unsigned)a.nmaps;
         } else {
-            base = (POLE ? a.coef_pole : a.coef_sc) + 4 * (a.coef_off[m] + t + 2) + min(comp - NC, POLE ? 2 : 1);
+            const int ci = min(max(comp - CB, 0), leg_coefs(K) - 1);
+            if constexpr (DD)
+                base = ci < 3 ? a.coef_hi + ci : a.coef_lo + (ci - 3);
+            else
+                base = (SPLIT ? a.coef_pole : a.coef_sc) + ci;
+            base += 4 * (a.coef_off[m] + t + 2);
             stride = 8u;
         }
-        const double f1 = is_a ? 1.0 : 0.0, f0 = 1.0 - f1;  // factor of a staged value: f_l, or 1 for a coefficient
+        // factor of a staged value: f_l, or 1 for a coefficient and in double-double
+        const double f1 = is_a ? 1.0 : 0.0, f0 = 1.0 - f1;
         const double *fb = reinterpret_cast<const double *>(cf) + 2;
         double pre[E], fac[E];
         auto fetch = [&](int c) {  // rows c .. c + kChunk - 1
@@ -127,13 +156,17 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             for (int e = 0; e < E; e++) {
                 const unsigned i = (unsigned)min(c + (lane + 64 * e) / CW, n - 1);
                 pre[e] = base[(size_t)i * stride];
-                fac[e] = fb[8 * i];
+                if constexpr (!DD) fac[e] = fb[8 * i];
             }
         };
         auto stage = [&](int sl, int c) {  // rows c .. c + kChunk - 1
 #pragma unroll
-            for (int e = 0; e < E; e++)
-                stg[sl * CS + lane + 64 * e] = pre[e] * __builtin_fma(fac[e], f1, f0);
+            for (int e = 0; e < E; e++) {
+                if constexpr (DD)
+                    stg[sl * CS + lane + 64 * e] = pre[e];
+                else
+                    stg[sl * CS + lane + 64 * e] = pre[e] * __builtin_fma(fac[e], f1, f0);
+            }
             if (c + kChunk > n) {
 #pragma unroll
                 for (int e = 0; e < E; e++)
@@ -143,11 +176,21 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
         auto step = [&](auto first, double rv, double rc) {  // first: the row's first lane
             constexpr int C0 = decltype(first)::value;
             const double c0 = row_bcast<C0 + CO>(rc), c1 = row_bcast<C0 + CO + 1>(rc);
-            const double c2 = POLE ? row_bcast<(C0 + CO + 2) % 16>(rc) : 0.0;
+            const double c2 = leg_coefs(K) > 2 ? row_bcast<(C0 + CO + 2) % 16>(rc) : 0.0;
 #pragma unroll
             for (int r = 0; r < R; r++) {
                 fmac_row_bcast<NC, C0>(acc[r], rv, P0[r]);
-                if constexpr (POLE) {  // c0 = h, c1 = -b (both of the next l), c2 = r
+                if constexpr (DD) {  // B, AB and G of App. A.2, high and low parts
+                    const double l0 = row_bcast<(C0 + CO + 3) % 16>(rc), l1 = row_bcast<(C0 + CO + 4) % 16>(rc);
+                    const double l2 = row_bcast<(C0 + CO + 5) % 16>(rc);
+                    const dd A = dd_add_raw(dd_mul_raw({x[r], xl}, {c0, l0}), {c1, l1});
+                    const dd y = dd_add_raw(dd_mul_raw(A, {P1[r], P1l}), dd_mul_raw({c2, l2}, {P0[r], P0l}));
+                    const dd nx = fast_two_sum(y.h, y.l);
+                    P0[r] = P1[r];
+                    P0l = P1l;
+                    P1[r] = nx.h;
+                    P1l = nx.l;
+                } else if constexpr (SPLIT) {  // c0 = h, c1 = -b (both of the next l), c2 = r
                     const double nx = __builtin_fma(c2, P0[r], P1[r]);
                     P1[r] = __builtin_fma(c0, P1[r], (c1 * x[r]) * nx);
                     P0[r] = nx;
@@ -159,24 +202,35 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             }
         };
         fetch(lo);
-        // start values in the scaled variables wait in LDS until their chain joins
+        // start values (in the scaled variables, or in two parts) wait in LDS until their chain joins
+        double2 *starts = reinterpret_cast<double2 *>(room);
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const int i = sid[r] >= kDead ? 0 : sid[r];
-            *reinterpret_cast<double2 *>(room + 2 * (r * 64 + lane)) =
-                make_double2(s0[r] * cf[2 * i].w, POLE ? s1[r] : s1[r] * cf[2 * i + 2].w);
+            if constexpr (DD) {
+                starts[lane] = make_double2(s0[r], s1[r]);
+                starts[64 + lane] = make_double2(s0l, s1l);
+            } else {
+                const int i = sid[r] >= kDead ? 0 : sid[r];
+                starts[r * 64 + lane] = make_double2(s0[r] * cf[2 * i].w, SPLIT ? s1[r] : s1[r] * cf[2 * i + 2].w);
+            }
         }
         stage(0, lo);
         fetch(lo + kChunk);
+        if constexpr (DD) __builtin_amdgcn_s_setprio(3);  // a long serial chain among short ones
         int sl = 0;
         for (int c = lo; c < n; c += kChunk, sl ^= 1) {
             if (c <= hi) {
 #pragma unroll
                 for (int r = 0; r < R; r++)
                     if (sid[r] == c) {
-                        const double2 s = *reinterpret_cast<const double2 *>(room + 2 * (r * 64 + lane));
+                        const double2 s = starts[r * 64 + lane];
                         P0[r] = s.x;
                         P1[r] = s.y;
+                        if constexpr (DD) {
+                            const double2 sw = starts[64 + lane];
+                            P0l = sw.x;
+                            P1l = sw.y;
+                        }
                     }
             }
             const double *cur = stg + sl * CS + (lane & 15);
@@ -197,11 +251,12 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
             stage(sl ^ 1, c + kChunk);
             fetch(c + 2 * kChunk);
         }
+        if constexpr (DD) __builtin_amdgcn_s_setprio(0);
     }
 
     // fused even/odd fold and store (Eqs. 13-14), one ring group at a time:
     // wave 0 stores the north rings, wave 1 their mirrors
-    const double *other = lds + (1 - t) * leg_wave_lds<NB, R>();
+    const double *other = lds + (1 - t) * W;
 #pragma unroll
     for (int r = 0; r < R; r++) {
         if (g0 + r >= gend) break;
@@ -223,100 +278,35 @@ __device__ __forceinline__ void leg_block(const LegArgs &a, const int m, const i
     }
 }
 
-// The block of work rb of an order: pole blocks first (R groups each, the
-// last one partial), then the plain ones.
-template <int NB, int R>
-__device__ __forceinline__ void leg_item(const LegArgs &a, const int m, const int rb, double *lds) {
+// The block of work rb of an order: double-double groups first (one each),
+// then split ones (R groups each, the last block partial), then the plain ones.
+template <int NB, int R, bool DD>
+__device__ __forceinline__ void leg_item(const LegArgs &a, const int m, int rb, double *lds) {
+    constexpr int W = leg_wave_lds<NB, R, DD>();
+    if constexpr (DD) {
+        if (rb < a.dd_groups) return leg_block<NB, 1, Chain::DD, W>(a, m, rb, rb + 1, lds);
+        rb -= a.dd_groups;
+    }
     if (rb < a.pole_blocks)
-        leg_block<NB, R, true>(a, m, rb * R, a.pole_groups, lds);
+        leg_block<NB, R, Chain::SPLIT, W>(a, m, rb * R, a.pole_groups, lds);
     else
-        leg_block<NB, R, false>(a, m, a.first_plain + (rb - a.pole_blocks) * R, a.ng, lds);
+        leg_block<NB, R, Chain::PLAIN, W>(a, m, a.first_plain + (rb - a.pole_blocks) * R, a.ng, lds);
 }
 
-// Double-double form of the recurrence, for plans whose dd_sin was chosen by
-// the caller (and for polar groups that reach too far from the pole for the
-// split recurrence): one wave, order m, the 64 rings of group g, both
-// parities.
-template <int NB>
-__device__ __forceinline__ void legendre_dd_wave(const LegArgs &a, const int m, const int g) {
-    const int lane = threadIdx.x;
-    const int L = a.L;
-    const int k = g * kLanes + lane;
-    // wave-uniform chain range
-    const int lo = a.grp_lo[(size_t)m * a.ng + g], hi = a.grp_hi[(size_t)m * a.ng + g];
-    const int n0 = (L - m) / 2 + 1;                         // even chain length
-    const int n1 = (L - m >= 1) ? (L - m - 1) / 2 + 1 : 0;  // odd chain length
-
-    double acc[2][2 * NB];  // [parity][map, re/im]
-#pragma unroll
-    for (int c = 0; c < 2 * NB; c++) acc[0][c] = acc[1][c] = 0.0;
-
-    if (lo < n0) {
-        const dd z2 = {a.z2_hi[k], a.z2_lo[k]};
-        int sid[2];
-        dd p0[2], p1[2];
-#pragma unroll
-        for (int t = 0; t < 2; t++) {
-            sid[t] = a.start_idx[(size_t)(2 * m + t) * a.np + k];
-            p0[t] = p1[t] = {0.0, 0.0};
-        }
-        const double *__restrict__ ch = a.coef_hi + 4 * a.coef_off[m];
-        const double *__restrict__ cl = a.coef_lo + 4 * a.coef_off[m];
-        const double *__restrict__ al = a.alm + 2 * ((size_t)m * (2 * L + 3 - m) / 2 * a.nmaps + a.map0);
-        const int astride = 2 * a.nmaps;  // doubles between consecutive l
-        for (int i = lo; i < n0; i++) {
-            if (i % kChunk == 0 && i <= hi) {
-#pragma unroll
-                for (int t = 0; t < 2; t++)
-                    if (sid[t] == i) {
-                        const size_t row = (size_t)(2 * m + t) * 2;
-                        p0[t] = {a.start_val[row * a.np + k], a.start_lo[row * a.n_dd_pad + k]};
-                        p1[t] = {a.start_val[(row + 1) * a.np + k], a.start_lo[(row + 1) * a.n_dd_pad + k]};
-                    }
-            }
-#pragma unroll
-            for (int t = 0; t < 2; t++) {
-                const double *ap = al + (size_t)(2 * i + t) * astride;
-#pragma unroll
-                for (int c = 0; c < 2 * NB; c++)
-                    acc[t][c] = __builtin_fma(p0[t].h, t == 0 || i < n1 ? ap[c] : 0.0, acc[t][c]);
-                const int e = 4 * (2 * i + 2 + t);
-                const dd A = dd_add(dd_mul(z2, {ch[e], cl[e]}), {ch[e + 1], cl[e + 1]});
-                const dd nx = dd_add(dd_mul(A, p1[t]), dd_mul({ch[e + 2], cl[e + 2]}, p0[t]));
-                p0[t] = p1[t];
-                p1[t] = nx;
-            }
-        }
-    }
-    if (k >= a.n_north) return;
-    const int ks = a.nrings - 1 - k;
-    double2 *qn = reinterpret_cast<double2 *>(a.q) + ((size_t)k * (L + 1) + m) * a.nmaps + a.map0;
-    double2 *qs = reinterpret_cast<double2 *>(a.q) + ((size_t)ks * (L + 1) + m) * a.nmaps + a.map0;
-#pragma unroll
-    for (int b = 0; b < NB; b++) {
-        const double er = acc[0][2 * b], ei = acc[0][2 * b + 1], od = acc[1][2 * b], oi = acc[1][2 * b + 1];
-        qn[b] = make_double2(er + od, m == 0 ? 0.0 : ei + oi);  // real field: Im a_l0 is ignored
-        if (ks != k) qs[b] = make_double2(er - od, m == 0 ? 0.0 : ei - oi);
-    }
-}
-
-template <int NB>
-__global__ __launch_bounds__(64) void k_legendre_dd(LegArgs a) {
-    legendre_dd_wave<NB>(a, blockIdx.x / a.dd_groups, blockIdx.x % a.dd_groups);
-}
-
-// One launch covers every (m, ring block), in the order of xcd_order().
-template <int NB, int R>
+// One launch covers every (m, ring block), in the order of xcd_order().  DD: for
+// plans with double-double groups (its registers and LDS would cost the one
+// ring a lane kernels of the others a fifth of their wavefronts).
+template <int NB, int R, bool DD>
 __global__ __launch_bounds__(128, (R == 4 ? 4 : 1)) void k_legendre(LegArgs a) {
-    __shared__ __attribute__((aligned(16))) double lds[2 * leg_wave_lds<NB, R>()];
-    const int nrb = a.pole_blocks + a.plain_blocks;
+    __shared__ __attribute__((aligned(16))) double lds[2 * leg_wave_lds<NB, R, DD>()];
+    const int nrb = a.dd_groups + a.pole_blocks + a.plain_blocks;
     const int slot = blockIdx.x >> 3, s = slot / nrb;
     const int m = xcd_order(blockIdx.x & 7, s);
     if (m > a.L) return;
     // an XCD deals its workgroups to its shader engines round robin: the
     // first block of each order moves on by one, so that no engine gets the
     // same (long or short) ring blocks of every order
-    leg_item<NB, R>(a, m, (slot + s) % nrb, lds);
+    leg_item<NB, R, DD>(a, m, (slot + s) % nrb, lds);
 }
 
 // Rings per lane of a pass of nb maps: the plan's choice, or by the number
@@ -341,8 +331,10 @@ int leg_pass_maps(int left) { return left >= 8 ? 8 : left == 7 ? 4 : left; }
 
 template <int NB, int R>
 static hipError_t launch_nbr(const sht_plan_s *p, LegArgs a, hipStream_t st) {
-    const long long grid = (long long)((p->L + 64) / 64 * 64) * (a.pole_blocks + a.plain_blocks);
-    if (grid > 0) hipLaunchKernelGGL((k_legendre<NB, R>), dim3((unsigned)grid), dim3(128), 0, st, a);
+    const long long grid = (long long)((p->L + 64) / 64 * 64) * (a.dd_groups + a.pole_blocks + a.plain_blocks);
+    if (grid <= 0) return hipSuccess;
+    if (a.dd_groups > 0) hipLaunchKernelGGL((k_legendre<NB, R, true>), dim3((unsigned)grid), dim3(128), 0, st, a);
+    else hipLaunchKernelGGL((k_legendre<NB, R, false>), dim3((unsigned)grid), dim3(128), 0, st, a);
     return hipGetLastError();
 }
 
@@ -355,18 +347,16 @@ static hipError_t launch_nb(const sht_plan_s *p, const LegArgs &a, int R, hipStr
 }
 
 // Persistent form for batches of requests (the many-transform regime of
-// Sec. 3.4): one launch per pass shape (double-double waves of 2 or 1 maps,
-// workgroups of 8, 6, 5, 4, 3, 2 or 1 maps) for every request of a batch, so
-// that each launch runs one specialised body at its own occupancy.  Work
-// items {pass, m, ring block, first map} of one shape come in eight lists,
+// Sec. 3.4): one launch per pass shape (workgroups of 8, 6, 5, 4, 3, 2 or 1
+// maps) for every request of a batch, so that each launch runs one specialised
+// body at its own occupancy.  Work items {pass, m, ring block, 0} of one shape come in eight lists,
 // one per XCD (the items of one pass and order share a list, so that XCD's L2
 // serves the order's coefficient and a_lm stream to all of them), each sorted
 // longest first and cut into chunks that shrink along the list.  A workgroup
 // takes chunks from its own XCD's list through a device counter (a
 // vector-memory atomic) and, once that list is exhausted, from the others in
 // turn; it leaves when every counter has passed the end of its list, so every
-// workgroup reaches the exit.  The bodies are k_legendre's and
-// k_legendre_dd's.
+// workgroup reaches the exit.  The bodies are k_legendre's.
 constexpr int kQueueLists = 8;
 constexpr int kQueueStride = 16;  // counters 64 bytes apart
 
@@ -376,12 +366,12 @@ __global__ void k_queue_reset(unsigned *c) {
 }
 
 template <int NB, int R, bool DD>
-__global__ __launch_bounds__(DD ? 64 : 128) void k_legendre_queue(const LegArgs *__restrict__ passes,
-                                                                  const int4 *__restrict__ items,
-                                                                  const unsigned *__restrict__ chunk_off,
-                                                                  const unsigned *__restrict__ list_off,
-                                                                  unsigned *__restrict__ counter) {
-    __shared__ __attribute__((aligned(16))) double lds[DD ? 2 : 2 * leg_wave_lds<NB, R>()];
+__global__ __launch_bounds__(128) void k_legendre_queue(const LegArgs *__restrict__ passes,
+                                                        const int4 *__restrict__ items,
+                                                        const unsigned *__restrict__ chunk_off,
+                                                        const unsigned *__restrict__ list_off,
+                                                        unsigned *__restrict__ counter) {
+    __shared__ __attribute__((aligned(16))) double lds[2 * leg_wave_lds<NB, R, DD>()];
     __shared__ unsigned taken;
     const int home = blockIdx.x & (kQueueLists - 1);  // workgroups are dealt to the XCDs round robin
     for (int s = 0; s < kQueueLists; s++) {
@@ -397,15 +387,9 @@ __global__ __launch_bounds__(DD ? 64 : 128) void k_legendre_queue(const LegArgs 
             for (unsigned i = i0; i < i1; i++) {
                 const int4 w = items[i];
                 const int pi = __builtin_amdgcn_readfirstlane(w.x), m = __builtin_amdgcn_readfirstlane(w.y);
-                const int rb = __builtin_amdgcn_readfirstlane(w.z), b0 = __builtin_amdgcn_readfirstlane(w.w);
-                LegArgs a = passes[pi];
-                a.map0 += b0;
-                if constexpr (DD) {
-                    legendre_dd_wave<NB>(a, m, rb);
-                } else {
-                    if (i != i0) __syncthreads();  // the previous item has left the LDS
-                    leg_item<NB, R>(a, m, rb, lds);
-                }
+                const LegArgs a = passes[pi];
+                if (i != i0) __syncthreads();  // the previous item has left the LDS
+                leg_item<NB, R, DD>(a, m, __builtin_amdgcn_readfirstlane(w.z), lds);
             }
         }
     }
@@ -413,43 +397,45 @@ __global__ __launch_bounds__(DD ? 64 : 128) void k_legendre_queue(const LegArgs 
 
 typedef void (*QueueKernel)(const LegArgs *, const int4 *, const unsigned *, const unsigned *, unsigned *);
 
-template <int R>
+template <int R, bool DD>
 static QueueKernel queue_kernel_r(int shape) {
     constexpr int R2 = R < 2 ? R : 2;
     switch (shape) {
-        case 0: return k_legendre_queue<2, 1, true>;
-        case 1: return k_legendre_queue<1, 1, true>;
-        case 2: return k_legendre_queue<8, R2, false>;
-        case 3: return k_legendre_queue<6, R2, false>;
-        case 4: return k_legendre_queue<5, R2, false>;
-        case 5: return k_legendre_queue<4, R, false>;
-        case 6: return k_legendre_queue<3, R, false>;
-        case 7: return k_legendre_queue<2, R, false>;
-        default: return k_legendre_queue<1, R, false>;
+        case 0: return k_legendre_queue<8, R2, DD>;
+        case 1: return k_legendre_queue<6, R2, DD>;
+        case 2: return k_legendre_queue<5, R2, DD>;
+        case 3: return k_legendre_queue<4, R, DD>;
+        case 4: return k_legendre_queue<3, R, DD>;
+        case 5: return k_legendre_queue<2, R, DD>;
+        default: return k_legendre_queue<1, R, DD>;
     }
 }
 
-static QueueKernel queue_kernel(int shape, int R) {
+template <bool DD>
+static QueueKernel queue_kernel_d(int shape, int R) {
     switch (R) {
-        case 1: return queue_kernel_r<1>(shape);
-        case 4: return queue_kernel_r<4>(shape);
-        default: return queue_kernel_r<2>(shape);
+        case 1: return queue_kernel_r<1, DD>(shape);
+        case 4: return queue_kernel_r<4, DD>(shape);
+        default: return queue_kernel_r<2, DD>(shape);
     }
 }
 
-int queue_shape(bool dd, int nb) { return dd ? (nb >= 2 ? 0 : 1) : nb >= 8 ? 2 : 9 - nb; }
+static QueueKernel queue_kernel(int shape, int R, bool dd) {
+    return dd ? queue_kernel_d<true>(shape, R) : queue_kernel_d<false>(shape, R);
+}
+
+int queue_shape(int nb) { return nb >= 8 ? 0 : 7 - nb; }
 int queue_rings(int nb, int R) { return nb > 4 ? std::min(R, 2) : R; }
-int queue_threads(int shape) { return shape < 2 ? 64 : 128; }
 
 // Workgroups of the persistent launch of one shape: as many as the current
 // device keeps resident at once.
-hipError_t legendre_queue_grid(int shape, int rings_per_lane, int *grid) {
+hipError_t legendre_queue_grid(int shape, int rings_per_lane, bool dd, int *grid) {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)queue_kernel(shape, rings_per_lane),
-                                                         queue_threads(shape), 0);
+        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)queue_kernel(shape, rings_per_lane, dd),
+                                                         kQueueThreads, 0);
     *grid = std::max(std::max(per_cu, 1) * std::max(cus, 1) / kQueueLists, 1) * kQueueLists;
     return e;
 }
@@ -460,11 +446,11 @@ hipError_t launch_queue_reset(unsigned *counter, hipStream_t st) {
 }
 
 hipError_t launch_legendre_queue(int shape, const LegArgs *passes, const int4 *items, const unsigned *chunk_off,
-                                 const unsigned *list_off, unsigned *counter, int rings_per_lane, int grid,
+                                 const unsigned *list_off, unsigned *counter, int rings_per_lane, bool dd, int grid,
                                  hipStream_t st) {
     if (shape < 0 || shape >= kQueueShapes || grid < 0) return hipErrorInvalidValue;
     if (grid == 0) return hipSuccess;  // no items of this shape
-    hipLaunchKernelGGL(queue_kernel(shape, rings_per_lane), dim3((unsigned)grid), dim3(queue_threads(shape)), 0, st,
+    hipLaunchKernelGGL(queue_kernel(shape, rings_per_lane, dd), dim3((unsigned)grid), dim3(kQueueThreads), 0, st,
                        passes, items, chunk_off, list_off + shape * (kQueueLists + 1),
                        counter + shape * kQueueLists * kQueueStride);
     return hipGetLastError();
@@ -522,20 +508,6 @@ hipError_t launch_legendre(const sht_plan_s *p, int nmaps, const double *alm, do
             case 2: e = launch_nb<2>(p, a, R, stream); break;
             default: e = launch_nb<1>(p, a, R, stream); break;
         }
-        b += nb;
-    }
-    // double-double rings, two maps at a time
-    const LegArgs d = leg_args(p, nmaps, 0, 1, alm, q);
-    for (int b = 0; d.dd_groups > 0 && b < nmaps && e == hipSuccess;) {
-        const int nb = std::min(2, nmaps - b);
-        LegArgs a = d;
-        a.map0 = b;
-        const dim3 grid((unsigned)((p->L + 1) * d.dd_groups));
-        if (nb == 2)
-            hipLaunchKernelGGL(k_legendre_dd<2>, grid, dim3(64), 0, stream, a);
-        else
-            hipLaunchKernelGGL(k_legendre_dd<1>, grid, dim3(64), 0, stream, a);
-        e = hipGetLastError();
         b += nb;
     }
     return e;

@@ -33,7 +33,7 @@ using namespace sht;
 
 namespace {
 
-constexpr double kDdCost = 4.0;  // double-double step relative to an FP64 step
+constexpr double kDdOps = 62.0;  // FP64 operations of a double-double step, both parities
 
 struct RingGroup {
     int threads = 0;
@@ -69,6 +69,7 @@ struct sht_batch_s {
     int path = SHT_PATH_BRUTE, fp32 = 0;
     std::vector<BfGroup> bf;
     int rings_per_lane = 2;
+    bool dd = false;  // some request has double-double ring groups
     std::vector<sht_request> reqs;
     LegArgs *d_passes = nullptr;
     int4 *d_items = nullptr;
@@ -284,6 +285,7 @@ int build_brute(sht_batch_s *b, const sht_batch_opts *o) {
             const LegArgs a = leg_args(p, q.nmaps, m0, Rp, q.alm, qbuf);
             const int pi = (int)passes.size();
             passes.push_back(a);
+            b->dd = b->dd || a.dd_groups > 0;
             for (int m = 0; m <= p->L; m++) {
                 const int n0 = (p->L - m) / 2 + 1;
                 auto steps = [&](int g0, int g1) {  // chain steps of the groups [g0, g1)
@@ -292,20 +294,18 @@ int build_brute(sht_batch_s *b, const sht_batch_opts *o) {
                     return lo < n0 ? (double)(n0 - lo) : 0.0;
                 };
                 // chain steps (both parities) times rings, plus the stores
-                for (int rb = 0; rb < a.pole_blocks + a.plain_blocks; rb++) {
-                    const bool pole = rb < a.pole_blocks;
-                    const int g0 = pole ? rb * Rp : a.first_plain + (rb - a.pole_blocks) * Rp;
-                    const int g1 = std::min(g0 + Rp, pole ? a.pole_groups : ng);
-                    const double cost = steps(g0, g1) * (g1 - g0) * (5.0 + 4.0 * nb) + 64.0 * (g1 - g0) * nb;
-                    items.push_back({cost, make_int4(pi, m, rb, 0), queue_shape(false, nb)});
-                }
-                // double-double waves take the maps two at a time
-                for (int g = 0; g < a.dd_groups; g++)
-                    for (int b0 = 0; b0 < nb; b0 += 2) {
-                        const int nw = std::min(2, nb - b0);
-                        const double cost = kDdCost * steps(g, g + 1) * (5.0 + 4.0 * nw) + 64.0 * nw;
-                        items.push_back({cost, make_int4(pi, m, g, b0), queue_shape(true, nw)});
+                for (int rb = 0; rb < a.dd_groups + a.pole_blocks + a.plain_blocks; rb++) {
+                    int g0 = rb, g1 = rb + 1;
+                    if (rb >= a.dd_groups) {
+                        const int bi = rb - a.dd_groups;
+                        const bool pole = bi < a.pole_blocks;
+                        g0 = pole ? bi * Rp : a.first_plain + (bi - a.pole_blocks) * Rp;
+                        g1 = std::min(g0 + Rp, pole ? a.pole_groups : ng);
                     }
+                    const double ops = rb < a.dd_groups ? kDdOps : 5.0;
+                    const double cost = steps(g0, g1) * (g1 - g0) * (ops + 4.0 * nb) + 64.0 * (g1 - g0) * nb;
+                    items.push_back({cost, make_int4(pi, m, rb, 0), queue_shape(nb)});
+                }
             }
             m0 += nb;
         }
@@ -341,7 +341,7 @@ int build_brute(sht_batch_s *b, const sht_batch_opts *o) {
             for (int x = 0; x <= kLists; x++) list_off[(size_t)v * (kLists + 1) + x] = (unsigned)chunk_off.size();
             continue;
         }
-        if (e == hipSuccess) e = legendre_queue_grid(v, R, &b->grid[v]);
+        if (e == hipSuccess) e = legendre_queue_grid(v, R, b->dd, &b->grid[v]);
         std::vector<size_t> order(groups.size());
         for (size_t i = 0; i < order.size(); i++) order[i] = i;
         std::stable_sort(order.begin(), order.end(),
@@ -568,7 +568,7 @@ int sht_batch_run(const sht_batch_t *b, void *stream) {
         fork(0, k);
         for (int v = 0; v < kQueueShapes && e == hipSuccess; v++)
             e = launch_legendre_queue(v, b->d_passes, b->d_items, b->d_chunk_off, b->d_list_off, b->d_counter,
-                                      b->rings_per_lane, b->grid[v], b->st[v % kMaxStreams]);
+                                      b->rings_per_lane, b->dd, b->grid[v], b->st[v % kMaxStreams]);
         join(0, k);
     }
     // phase 1: one ring launch per ring size class
@@ -592,7 +592,7 @@ int sht_batch_stats(const sht_batch_t *b, long long *items, int *launches, int *
     *waves = 0;
     for (int v = 0; v < kQueueShapes; v++) {
         *launches += b->grid[v] > 0;
-        *waves += b->grid[v] * (queue_threads(v) / 64);
+        *waves += b->grid[v] * (kQueueThreads / 64);
     }
     if (b->path == SHT_PATH_BUTTERFLY) {
         *items = 0;
