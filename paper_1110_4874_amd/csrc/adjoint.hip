@@ -655,15 +655,15 @@ hipError_t launch_legendre_adjoint(const sht_plan_s *p, int nmaps, const double 
     // groups a wave, four maps: 4 groups (L = 255) 15.0 and 18.9 us, 8 (L = 511)
     // 49 and 48, 12 (L = 767) 130 and 146, 16 (L = 1023) 348 and 245.  Eight maps
     // a pass take 69 us at 8 groups (two passes of four: 98) and 523 at 16 (489).
+    // (opts.rings_per_lane is the synthesis kernel's and has no say here: one
+    // group a wave at 16 groups would take 348 us for 245.)
     const int first = kdd > 0 ? p->n_dd_groups : 0, ng = a.ng - first;
     for (int b = 0; b < nmaps && e == hipSuccess;) {
         const int left = nmaps - b;
         a.map0 = b;
         a.nb = left >= 7 ? (ng <= 8 ? std::min(left, 8) : 4) : left;
         const int NS = (a.nb + 1) / 2;
-        int R = p->opts.rings_per_lane;
-        if (R != 1 && R != 2 && R != 4) R = ng <= 12 ? 1 : 2;
-        R = NS == 4 ? 1 : std::min(R, 2);
+        const int R = NS == 4 || ng <= 12 ? 1 : 2;
         for (int g = first; g < a.ng && e == hipSuccess; g = a.end_group) {
             a.accumulate = kdd > 0 || g > first ? 1 : 0;
             a.first_group = g;
