@@ -171,10 +171,12 @@ typedef struct sht_plan_info {
                                  costs 5 flops of recurrence + 4 per map) */
     long long n_step_exec;    /* recurrence steps the kernel executes (chain
                                  starts rounded down to a chunk boundary) */
-    long long n_step_dd;      /* executed steps in compensated ring blocks */
+    long long n_step_dd;      /* of these, steps in double-double (0 where the
+                                 rings below dd_sin run the split recurrence) */
     long long n_step_lanes;   /* lane-steps the Legendre kernel issues (idle
-                                 lanes of partially active waves included) at
-                                 rings_per_lane rings a lane (0: at 2) */
+                                 lanes of partially active waves and the chains'
+                                 last chunks included) at rings_per_lane rings a
+                                 lane (0: at 2; double-double: 1) */
     size_t device_bytes;      /* device memory held by the plan */
     double build_seconds;     /* wall time of sht_plan */
     /* butterfly (zero unless eps > 0) */

@@ -340,7 +340,7 @@ int sht_plan_info(const sht_plan_t *p, sht_plan_info_t *out) {
     out->eps = p->eps;
     out->n_step = p->n_step;
     out->n_step_exec = p->n_step_exec;
-    out->n_step_dd = p->n_step_dd;
+    out->n_step_dd = split_groups(p) > 0 ? 0 : p->n_step_dd;
     out->n_step_lanes = p->n_step_lanes;
     out->device_bytes = p->device_bytes;
     out->build_seconds = p->build_seconds;

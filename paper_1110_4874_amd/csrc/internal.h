@@ -291,6 +291,7 @@ struct RingArgs {
 
 // Host plan construction (plan.cpp, butterfly_plan.cpp).
 void ring_geometry(int N, int i, long double *z, long double *sin2, int *J, int *s, long long *off);
+int split_groups(const sht_plan_s *p);
 int build_host_tables(sht_plan_s *p);
 int build_butterfly(sht_plan_s *p, const BflyInput &in);
 int build_interp(sht_plan_s *p, const BflyInput &in);

@@ -216,11 +216,37 @@ static void start_worker(long k, void *vctx) {
     c->alive[k] = alive;
 }
 
+// Reach of the split recurrence from the poles, as sin(theta) of the last
+// ring of a 64-ring group: its relative error (L = 4095, against long
+// double) is 2e-15 to 2e-14 up to 0.1 and 4e-14 at 0.4, where the plain
+// recurrence's is 1e-12 and 3e-13; the two meet at 0.7.
+constexpr double kPoleSin = 0.3, kPoleSinMax = 0.6;
+
+// 64-ring groups from the pole that run the split recurrence: with the default
+// threshold, where the polar groups end within kPoleSinMax, those and the groups
+// after them that end below kPoleSin (the plain recurrence loses 10x more there
+// at two FP64 operations less a step).  0: the polar groups run double-double.
+int split_groups(const sht_plan_s *p) {
+    const int ng = p->n_north_pad / kLanes;
+    auto sin_at = [&](int g) {
+        ld z, w;
+        int J, s;
+        long long off;
+        ring_geometry(p->nside, std::min((g + 1) * kLanes, p->n_north), &z, &w, &J, &s, &off);
+        return sqrt((double)w);
+    };
+    if (!(p->opts.dd_sin < 0) || p->n_dd_groups == 0 || sin_at(p->n_dd_groups - 1) > kPoleSinMax) return 0;
+    int g = p->n_dd_groups;
+    while (g < ng && sin_at(g) <= kPoleSin) g++;
+    // an even number where it can be: waves of two groups are whole
+    if (g % 2 && g < ng && sin_at(g) <= kPoleSinMax) g++;
+    return g;
+}
+
 static void group_worker(long m, void *vctx) {
     BuildCtx *c = (BuildCtx *)vctx;
     sht_plan_s *p = c->p;
     const int np = p->n_north_pad, ng = np / kLanes;
-    const int n0 = (p->L - (int)m) / 2 + 1;
     for (int g = 0; g < ng; g++) {
         int lo = kDead, hi = -1;
         for (int t = 0; t < 2; t++)
@@ -234,15 +260,21 @@ static void group_worker(long m, void *vctx) {
         p->grp_lo[(size_t)m * ng + g] = lo;
         p->grp_hi[(size_t)m * ng + g] = hi;
     }
-    // lane-steps the kernel executes for this m (every lane of a wave runs
-    // both parities from the wave's first chunk to the end of the chain)
+    // lane-steps the kernel executes for this m: a wave runs one parity of a
+    // block from the block's first chunk to the last chunk of the chain; the
+    // split groups and the plain ones make blocks of R each, the double-double
+    // ones of one each
     long long lanes = 0;
-    const int R = p->rings_per_lane, gdd = p->n_dd_groups;
-    for (int g0 = 0; g0 < ng; g0 += (g0 < gdd ? 1 : R)) {
-        const int w = g0 < gdd ? 1 : std::min(R, ng - g0);
+    const int gs = split_groups(p), gp = gs > 0 ? gs : p->n_dd_groups;  // plain groups from gp on
+    for (int g0 = 0; g0 < ng;) {
+        const int end = g0 < gp ? gp : ng, w = std::min(g0 < gp && gs == 0 ? 1 : p->rings_per_lane, end - g0);
         int lo = kDead;
         for (int r = 0; r < w; r++) lo = std::min(lo, p->grp_lo[(size_t)m * ng + g0 + r]);
-        if (lo < n0) lanes += 2LL * kLanes * w * (n0 - lo);
+        for (int t = 0; t < 2; t++) {
+            const int n = p->L - (int)m - t >= 0 ? (p->L - (int)m - t) / 2 + 1 : 0;
+            if (lo < n) lanes += (long long)kLanes * w * ((n - lo + kChunk - 1) / kChunk * kChunk);
+        }
+        g0 += w;
     }
     c->lane_steps[m] = lanes;
 }
@@ -535,12 +567,6 @@ static std::vector<int> fold_unit_order(const BflyPlan &f) {
     return out;
 }
 
-// Reach of the split recurrence from the poles, as sin(theta) of the last
-// ring of a 64-ring group: its relative error (L = 4095, against long
-// double) is 2e-15 to 2e-14 up to 0.1 and 4e-14 at 0.4, where the plain
-// recurrence's is 1e-12 and 3e-13; the two meet at 0.7.
-constexpr double kPoleSin = 0.3, kPoleSinMax = 0.6;
-
 static hipError_t upload_all(sht_plan_s *p, size_t *bytes) {
     size_t b = 0;
     hipError_t e = hipSuccess;
@@ -565,31 +591,9 @@ static hipError_t upload_all(sht_plan_s *p, size_t *bytes) {
     UP(d_ring_chirp_off, ring_chirp_off);
     UP(d_pol_ring, pol_ring);
     UP(d_pol_K, pol_K);
-    // Rings nearest the poles: the split recurrence when the plan has the
-    // default threshold and its polar groups end within kPoleSinMax, where
-    // that recurrence is at least as accurate as the plain one; else
-    // double-double, which needs the coefficients' low parts (and so does the
-    // interpolation form).  The split recurrence also takes the groups that
-    // end below kPoleSin: the plain one loses 10x more there, at one FP64
-    // operation less a step.
-    p->pole_groups = 0;
-    std::vector<double> s2(p->n_north_pad, 1.0);
-    for (int k = 0; k < p->n_north; k++) {
-        ld z, w;
-        int J, s;
-        long long off;
-        ring_geometry(p->nside, k + 1, &z, &w, &J, &s, &off);
-        s2[k] = (double)w;
-    }
-    auto group_sin = [&](int g) { return sqrt(s2[std::min((g + 1) * kLanes, p->n_north) - 1]); };
-    if (p->opts.dd_sin < 0 && p->n_dd_groups > 0 && group_sin(p->n_dd_groups - 1) <= kPoleSinMax) {
-        int g = p->n_dd_groups;
-        const int ng = p->n_north_pad / kLanes;
-        while (g < ng && group_sin(g) <= kPoleSin) g++;
-        // an even number where it can be: waves of two groups are whole
-        if (g % 2 && g < ng && group_sin(g) <= kPoleSinMax) g++;
-        p->pole_groups = g;
-    }
+    // double-double groups need the coefficients' low parts, and so does the
+    // interpolation form
+    p->pole_groups = split_groups(p);
     if (p->ip.built || (p->n_dd_groups > 0 && p->pole_groups == 0)) {
         UP(d_coef_lo, coef_lo);
     }
@@ -600,6 +604,14 @@ static hipError_t upload_all(sht_plan_s *p, size_t *bytes) {
         b += nc;
     }
     if (p->pole_groups > 0) {
+        std::vector<double> s2(p->n_north_pad, 1.0);
+        for (int k = 0; k < p->n_north; k++) {
+            ld z, w;
+            int J, s;
+            long long off;
+            ring_geometry(p->nside, k + 1, &z, &w, &J, &s, &off);
+            s2[k] = (double)w;
+        }
         const size_t nc = p->coef_hi.size() * sizeof(double),
                      ns = (size_t)(p->L + 1) * 2 * p->pole_groups * kLanes * sizeof(double);
         if (e == hipSuccess) e = up(&p->d_s2, s2, &b);
