@@ -580,7 +580,6 @@ static hipError_t upload_all(sht_plan_s *p, size_t *bytes) {
     UP(d_ring_off, ring_off);
     UP(d_ring_bs_off, ring_bs_off);
     UP(d_coef_off, coef_off);
-    UP(d_coef_hi, coef_hi);
     UP(d_start_idx, start_idx);
     UP(d_start_val, start_val);
     UP(d_start_lo, start_lo);
@@ -591,10 +590,11 @@ static hipError_t upload_all(sht_plan_s *p, size_t *bytes) {
     UP(d_ring_chirp_off, ring_chirp_off);
     UP(d_pol_ring, pol_ring);
     UP(d_pol_K, pol_K);
-    // double-double groups need the coefficients' low parts, and so does the
-    // interpolation form
+    // only double-double groups and the interpolation form read the unscaled
+    // coefficients (268 MB at L = 4095, and as much of low parts)
     p->pole_groups = split_groups(p);
     if (p->ip.built || (p->n_dd_groups > 0 && p->pole_groups == 0)) {
+        UP(d_coef_hi, coef_hi);
         UP(d_coef_lo, coef_lo);
     }
     {
