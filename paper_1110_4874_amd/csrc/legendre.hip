@@ -23,7 +23,7 @@
 // The two-step recurrence runs in the scaling P~_l = f_l mu_l with f_{l+2} f_l
 // = 1 / c_l, which makes its last coefficient -1:
 //   mu_{l+2} = b_l (z^2 - d_l) mu_l - mu_{l-2},  b_l = f_l^2
-// (c_l, d_l of App. A.2; f stays within the square root of the range of c).
+// (c_l, d_l of App. A.2; f runs from about sqrt(m) to 2).
 // Two FP64 operations a step instead of three; the f_l go into the staged
 // a_lm.
 //
@@ -522,24 +522,54 @@ __device__ __forceinline__ dd pole_Q(double l, double m) {
     return dd_sqrt(dd_div({2 * l + 5, 0.0}, dd_mul({2 * l + 1, 0.0}, D)));
 }
 
+// v rounded to double with the rounding error of the entries before it in the
+// chain added, which it passes on: the errors of a table's entries sum to less
+// than one rounding.  A coefficient's error shifts the chain's phase from there
+// on, so independent errors add up like sqrt(l), these do not.
+__device__ __forceinline__ double round_carry(dd v, double &carry) {
+    const dd t = dd_add(v, {carry, 0.0});
+    carry = t.l;
+    return t.h;
+}
+
 // Scaled recurrence: entry e = l - m of order m holds {b_l, -b_l d_l, f_l,
-// 1 / f_l}, f_m = f_{m+1} = 2; one thread per order and parity follows the
-// product of the c_l in double-double.
+// 1 / f_l}; one thread per order and parity follows the product of the c_l in
+// double-double.  The product fixes f_{l+2} f_l = 1 / c_l only; the first value
+// is chosen so that the last two are equal (a first pass finds the ratio), which
+// lets f_l run smoothly towards 2 and b_l towards 4, as the carried rounding
+// needs (f_m = 2 would make them alternate by a factor of m).  Near the equator,
+// the recurrence's double root, these errors decide: the phases of rings there
+// were off by 1.62e-14 (L = 1023, relative rms, red spectrum) and 2.99e-14 (L =
+// 2047) with f_m = 2 and plain rounding, 1.34e-14 and 2.55e-14 by the unscaled
+// recurrence.
+__device__ __forceinline__ dd scaled_next(double l, double m, dd f) {
+    // 1 / c_l = (2l+3) sqrt((2l+1)(2l+5) / D) = (2l+3)(2l+1) Q_l
+    return dd_div(dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, pole_Q(l, m)), f);
+}
 __global__ __launch_bounds__(64) void k_scaled_coef(const long long *__restrict__ coef_off, double4 *__restrict__ out,
                                                     int rows) {
     const int row = blockIdx.x * 64 + threadIdx.x;
     if (row >= rows) return;
-    const int m = row >> 1;
+    const int m = row >> 1, t = row & 1;
     const long long base = coef_off[m], cnt = coef_off[m + 1] - base;
     const double mm = m;
+    const int n = (int)((cnt - t + 1) / 2);  // entries of this parity (a dozen past L at least)
     dd f = {2.0, 0.0};
-    for (long long e = row & 1; e < cnt; e += 2) {
-        const double l = mm + e;
+    double ratio = 1.0;
+    for (int k = 0; k < n - 1; k++) {
+        const dd nx = scaled_next(mm + t + 2.0 * k, mm, f);
+        ratio = nx.h / f.h;
+        f = nx;
+    }
+    f = {(n & 1) ? 2.0 / sqrt(ratio) : 2.0 * sqrt(ratio), 0.0};
+    double cb = 0.0, ca = 0.0;
+    for (int k = 0; k < n; k++) {
+        const double l = mm + t + 2.0 * k;
         const dd b = dd_mul(f, f);
         const dd d = dd_div({2 * l * (l + 1) - 2 * mm * mm - 1, 0.0}, {(2 * l - 1) * (2 * l + 3), 0.0});
-        out[base + e] = make_double4(b.h, -dd_mul(b, d).h, f.h, 1.0 / f.h);
-        // 1 / c_l = (2l+3) sqrt((2l+1)(2l+5) / D) = (2l+3)(2l+1) Q_l
-        f = dd_div(dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, pole_Q(l, mm)), f);
+        out[base + t + 2 * k] =
+            make_double4(round_carry(b, cb), round_carry(dd_neg(dd_mul(b, d)), ca), f.h, 1.0 / f.h);
+        f = scaled_next(l, mm, f);
     }
 }
 
@@ -553,20 +583,24 @@ hipError_t fill_scaled_coef(const sht_plan_s *p) {
 
 // Split recurrence in the scaled variables (P~_l = f_l mu_l, d_l of the pair
 // (l, l+2) scaled like P~_{l+2}): entry e holds {h_l f_l / f_{l+2},
-// -beta_l f_l / f_{l+2}, r_{l-2} f_{l-2} / f_l, 0}; entries 0 and 1 are not used.
-__global__ __launch_bounds__(256) void k_pole_coef(const long long *__restrict__ coef_off,
-                                                   const double4 *__restrict__ sc, double4 *__restrict__ out) {
-    const int m = blockIdx.x;
+// -beta_l f_l / f_{l+2}, r_{l-2} f_{l-2} / f_l, 0}, with carried rounding; entries
+// 0 and 1 are not used.
+__global__ __launch_bounds__(64) void k_pole_coef(const long long *__restrict__ coef_off,
+                                                  const double4 *__restrict__ sc, double4 *__restrict__ out, int rows) {
+    const int row = blockIdx.x * 64 + threadIdx.x;
+    if (row >= rows) return;
+    const int m = row >> 1;
     const long long base = coef_off[m], cnt = coef_off[m + 1] - base;
-    for (long long e = threadIdx.x; e < cnt; e += 256) {
+    double ch = 0.0, cb = 0.0, cr = 0.0;
+    for (long long e = row & 1; e < cnt; e += 2) {
         double4 v = make_double4(0.0, 0.0, 0.0, 0.0);
         if (e >= 2 && e + 2 < cnt) {
             const double l = (double)(m + e), mm = m;
             const dd Qf = dd_mul(pole_Q(l, mm), dd_div({sc[base + e].z, 0.0}, {sc[base + e + 2].z, 0.0}));
-            v.x = dd_mul(dd_div(dd_mul({(l - mm) * (l - 1 - mm), 0.0}, {2 * l + 3, 0.0}), {2 * l - 1, 0.0}), Qf).h;
-            v.y = -dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, Qf).h;
-            v.z = dd_mul(dd_mul({(l - 1 + mm) * (l + mm), 0.0}, pole_Q(l - 2, mm)),
-                         dd_div({sc[base + e - 2].z, 0.0}, {sc[base + e].z, 0.0})).h;
+            v.x = round_carry(dd_mul(dd_div(dd_mul({(l - mm) * (l - 1 - mm), 0.0}, {2 * l + 3, 0.0}), {2 * l - 1, 0.0}), Qf), ch);
+            v.y = round_carry(dd_neg(dd_mul({(2 * l + 3) * (2 * l + 1), 0.0}, Qf)), cb);
+            v.z = round_carry(dd_mul(dd_mul({(l - 1 + mm) * (l + mm), 0.0}, pole_Q(l - 2, mm)),
+                                     dd_div({sc[base + e - 2].z, 0.0}, {sc[base + e].z, 0.0})), cr);
         }
         out[base + e] = v;
     }
@@ -597,8 +631,9 @@ __global__ __launch_bounds__(256) void k_pole_start(LegArgs a, double *__restric
 }
 
 hipError_t fill_pole_tables(const sht_plan_s *p) {
-    hipLaunchKernelGGL(k_pole_coef, dim3((unsigned)(p->L + 1)), dim3(256), 0, nullptr, p->d_coef_off,
-                       reinterpret_cast<const double4 *>(p->d_coef_sc), reinterpret_cast<double4 *>(p->d_coef_pole));
+    const int rows = 2 * (p->L + 1);
+    hipLaunchKernelGGL(k_pole_coef, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, nullptr, p->d_coef_off,
+                       reinterpret_cast<const double4 *>(p->d_coef_sc), reinterpret_cast<double4 *>(p->d_coef_pole), rows);
     const LegArgs a = leg_args(p, 1, 0, 1, nullptr, nullptr);
     hipLaunchKernelGGL(k_pole_start, dim3((unsigned)(2 * (p->L + 1))), dim3(256), 0, nullptr, a, p->d_start_d);
     hipError_t e = hipGetLastError();
