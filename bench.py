@@ -178,9 +178,9 @@ def batch_bench(np, torch, sht, steps):
         # work-queue form: on the brute-force path one persistent Legendre
         # launch per wave shape over every request's items; on the butterfly
         # path one launch per stage and map-group width over every request;
-        # then one ring launch per ring size class; replayed as a graph.  The
-        # tile shape (rings per lane, ring workgroup size) is swept and the
-        # fastest graph is reported.
+        # then one ring launch per ring workgroup size; replayed as a graph.  The
+        # rings per lane of the brute-force path are swept and the fastest graph
+        # is reported.
         reqs = [(plans[(L, N)], alm, out) for (L, N, alm, out) in inputs]
         seq_ref = []
         for p, a, o in reqs:
@@ -189,35 +189,32 @@ def batch_bench(np, torch, sht, steps):
         rpls = (1, 2, 4) if path == sht.PATH_BRUTE else (2,)
         sweep, best = {}, None
         for rpl in rpls:
-            for thr in (256, 512, 1024):
-                qb = sht.QueueBatch(reqs, path=path, precision=prec, rings_per_lane=rpl, ring_threads=thr)
-                t_run = timed(qb.run, steps)
-                s = torch.cuda.Stream()
-                s.wait_stream(torch.cuda.current_stream())
-                g = torch.cuda.CUDAGraph()
-                with torch.cuda.stream(s):
-                    with torch.cuda.graph(g, stream=s):
-                        qb.run(stream=s)
-                torch.cuda.current_stream().wait_stream(s)
-                t_graph = timed(g.replay, steps)
-                torch.cuda.synchronize()
-                # the ring stage's twiddle stepping depends on the workgroup
-                # size, so shapes other than the plans' agree to rounding
-                diff = max(float((o - r).abs().max() / r.abs().max()) for (_, _, o), r in zip(reqs, seq_ref))
-                st = qb.stats()
-                qb.close()
-                del g
-                key = f"rpl{rpl}_t{thr}" if path == sht.PATH_BRUTE else f"t{thr}"
-                sweep[key] = round(nmaps / t_graph, 1)
-                r = {"run_maps_per_s": round(nmaps / t_run, 2), "graph_maps_per_s": round(nmaps / t_graph, 2),
-                     "work_items": st["items"], "launches_per_run": st["launches"],
-                     "max_rel_diff_vs_sequential": diff, "rings_per_lane": rpl, "ring_threads": thr}
-                if path == sht.PATH_BRUTE:
-                    r["persistent_waves"] = st["waves"]
-                if not diff <= 1e-12:
-                    raise RuntimeError(f"work-queue batch {key} differs from the sequential calls by {diff:.3e}")
-                if best is None or r["graph_maps_per_s"] > best["graph_maps_per_s"]:
-                    best = r
+            qb = sht.QueueBatch(reqs, path=path, precision=prec, rings_per_lane=rpl)
+            t_run = timed(qb.run, steps)
+            s = torch.cuda.Stream()
+            s.wait_stream(torch.cuda.current_stream())
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.stream(s):
+                with torch.cuda.graph(g, stream=s):
+                    qb.run(stream=s)
+            torch.cuda.current_stream().wait_stream(s)
+            t_graph = timed(g.replay, steps)
+            torch.cuda.synchronize()
+            diff = max(float((o - r).abs().max() / r.abs().max()) for (_, _, o), r in zip(reqs, seq_ref))
+            st = qb.stats()
+            qb.close()
+            del g
+            key = f"rpl{rpl}"
+            sweep[key] = round(nmaps / t_graph, 1)
+            r = {"run_maps_per_s": round(nmaps / t_run, 2), "graph_maps_per_s": round(nmaps / t_graph, 2),
+                 "work_items": st["items"], "launches_per_run": st["launches"],
+                 "max_rel_diff_vs_sequential": diff, "rings_per_lane": rpl}
+            if path == sht.PATH_BRUTE:
+                r["persistent_waves"] = st["waves"]
+            if not diff <= 1e-12:
+                raise RuntimeError(f"work-queue batch {key} differs from the sequential calls by {diff:.3e}")
+            if best is None or r["graph_maps_per_s"] > best["graph_maps_per_s"]:
+                best = r
         best["sweep_graph_maps_per_s"] = sweep
         return best
 
@@ -626,7 +623,8 @@ def main():
     ap.add_argument("--no-interp", action="store_true", help="skip the interpolation-form measurement")
     ap.add_argument("--no-pol", action="store_true", help="skip the polarized-synthesis measurement")
     ap.add_argument("--rings-per-lane", type=int, default=0, help="Legendre kernel tile (1, 2, 4; 0 = plan default)")
-    ap.add_argument("--ring-threads", type=int, default=0, help="ring kernel workgroup size (256, 512, 1024; 0 = default)")
+    ap.add_argument("--ring-threads", type=int, default=0,
+                    help="0, 256, 512 or 1024; without effect (the ring kernels choose their workgroups)")
     ap.add_argument("--copy-calibration", type=int, default=0,
                     help="also run a device copy of this many MiB (counter calibration)")
     args = ap.parse_args()

@@ -4,8 +4,9 @@ For a workload (L, nside, nmaps, eps) and an execution path and precision it
 builds one plan per candidate and times full syntheses on the GPU with events
 on the execution stream, keeping the fastest:
 
-  brute force  rings per lane of the Legendre waves x workgroup size of the
-               ring FFT;
+  brute force  rings per lane of the Legendre waves (and ring_threads, which
+               plans accept but the ring kernels do not use any more: its
+               candidates time alike);
   butterfly    the cost model's rho (Sec. 3.4: stored interpolation entries
                against residual recurrence elements; FP32 level products
                stream half the bytes, so their best rho differs from FP64's),

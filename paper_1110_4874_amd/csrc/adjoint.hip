@@ -588,7 +588,7 @@ static hipError_t launch_adj_cfg(AdjArgs a, hipStream_t st) {
 }
 
 // R ring groups per wave (eight maps: 1; the phases take 8 R NS registers of
-// the 128 that 16 waves leave)
+// the 128 that 16 waves leave; six maps at two groups spill 20)
 static hipError_t launch_adj(const AdjArgs &a, int NS, int R, hipStream_t st) {
     switch (NS) {
         case 4: return launch_adj_cfg<4, 1>(a, st);

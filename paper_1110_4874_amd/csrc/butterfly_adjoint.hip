@@ -11,11 +11,11 @@
 //     children, v_ch = A~_ch u (identity rows gather u, the dense part T U
 //     runs on the matrix cores), so no two waves write one entry;
 //  3. k_bf_residual_t: one wave per residual task regenerates the Legendre
-//     values of its skeleton rings row by row, reduces sum_z P~(z) v(z) over
-//     the wave with lane swaps and DPP, and adds the row's result to g with
-//     one atomic per component (several tasks share a row block's rows, so
-//     the order of those few addends, and the last bits of g, may vary from
-//     run to run).
+//     values of its skeleton rings, four rows at a time, multiplies them by
+//     v in FP64 matrix products (sum_z P~(z) v(z)), and adds each row's
+//     result to g with one atomic per component (several tasks share a row
+//     block's rows, so the order of those few addends, and the last bits of
+//     g, may vary from run to run).
 #include "butterfly_common.h"
 #include "dpp.h"
 

@@ -166,7 +166,7 @@ struct sht_plan_s {
     std::vector<int> grp_lo, grp_hi;           // [(L+1)][n_north_pad/64]
     int n_dd_rings = 0, n_dd_groups = 0;
     int rings_per_lane = 2;                    // R of the FP64 Legendre waves
-    int ring_threads = 1024;                   // workgroup size of the ring kernel
+    int ring_threads = 1024;                   // in plan files; no kernel uses it
     long long n_step = 0, n_step_exec = 0, n_step_dd = 0, n_step_lanes = 0;
 
     // ring FFT tables

@@ -637,7 +637,10 @@ __device__ __forceinline__ void ring_synth_item(const RingArgs &a, const int ite
 }
 
 // Groups of T threads; up to T = 64 a workgroup runs G maps of one ring (G
-// divides nmaps), a wavefront and an LDS block each.
+// divides nmaps), a wavefront and an LDS block each.  256 registers, two
+// wavefronts a SIMD: the forms of two and four maps spill 6 of them (28 bytes of
+// scratch a thread; the analysis 16, 68 bytes), its 128 and 256-thread forms 2
+// and 4, the others none.
 template <int T, int G>
 __global__ __launch_bounds__(T * G, 2) void k_ring_synth(RingArgs a) {
     extern __shared__ double2 sm[];
