@@ -102,12 +102,14 @@ typedef struct sht_plan_opts {
                           plain FP64 one loses ~L eps / sin(theta).  < 0 selects
                           the default 0.1 * L / 4095 and the recurrence
                           split about its solution at the pole (relative
-                          error ~1e-14); a value >= 0 runs them in
-                          compensated double-double arithmetic. */
+                          error below 1e-14; double-double where the 64-ring
+                          groups below the threshold reach past sin(theta) =
+                          0.6); a value >= 0 runs them in compensated
+                          double-double arithmetic. */
     int nthreads;      /* host threads for plan construction; 0 = all cores */
     int rings_per_lane;/* rings each lane of the FP64 Legendre kernel owns:
                           1, 2 or 4 (0 = chosen by the transform's size); a
-                          tuning knob */
+                          tuning knob of synthesis (the adjoint has its own rule) */
     int ring_threads;  /* 0, 256, 512 or 1024: kept for programs that set it; the
                           ring FFT sizes its thread groups by the ring (64 to
                           256 threads) */

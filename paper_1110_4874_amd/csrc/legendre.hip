@@ -36,8 +36,8 @@
 //   P~_{l+2} = r_l P~_l + d_l,   d_{l+2} = h_{l+2} d_l - sin^2 beta_{l+2} P~_{l+2}
 // where sin^2(theta) enters with its own relative accuracy (in the scaled
 // variables with the coefficients scaled likewise).  Four FP64 operations a
-// step instead of two; relative errors of 2e-15 to 2e-14 at L = 4095 for
-// sin(theta) <= 0.1.
+// step instead of two; phases on rings with sin(theta) <= 0.1 are off by 2e-15 to
+// 8e-15 at L = 4095 (relative rms of a ring, white spectrum).
 //
 // Plans whose threshold the caller set, and polar groups that reach too far
 // from the pole for the split recurrence, run those groups in double-double (31

@@ -218,7 +218,7 @@ static void start_worker(long k, void *vctx) {
 
 // Reach of the split recurrence from the poles, as sin(theta) of the last
 // ring of a 64-ring group: its relative error (L = 4095, against long
-// double) is 2e-15 to 2e-14 up to 0.1 and 4e-14 at 0.4, where the plain
+// double, tables rounded entry by entry) is 2e-15 to 2e-14 up to 0.1 and 4e-14 at 0.4, where the plain
 // recurrence's is 1e-12 and 3e-13; the two meet at 0.7.
 constexpr double kPoleSin = 0.3, kPoleSinMax = 0.6;
 
